@@ -278,6 +278,15 @@ pic_status pic_tune(pic_ctx *ctx, int32_t push_unroll, int32_t push_merge, int32
  * outside {0, 1}. */
 pic_status pic_set_level_pairs(pic_ctx *ctx, int32_t on);
 
+/* How a context of one instance solved by plain CG (solver 1, or a grid
+ * that multigrid cannot coarsen) runs a refinement pass: 1 (the default) as
+ * one launch where the grid fits the device, 0 as one launch per step of the
+ * iteration, -1 as one launch whose work-groups do not wait for one another
+ * (for tests: on grids of several work-groups it gives up at once and the
+ * pass falls back to 0, as it does when a wait takes over a second).  The
+ * potential is the same bit for bit.  PIC_ERR_ARG for other values. */
+pic_status pic_set_cg_pass(pic_ctx *ctx, int32_t mode);
+
 /* Re-bins species s now (tile sort; drops removed particles). */
 pic_status pic_sort(pic_ctx *ctx, int32_t species);
 

@@ -62,6 +62,7 @@ enum {
     F_ITER1,     // inner iterations of the solve's first pass
     F_ERR,       // sticky device error bits (kErrVWindow)
     F_UNCONV,    // sticky count of pushes whose potential had not met rtol
+    F_CGABORT,   // a one-launch CG pass gave up waiting: its result does not count
     F_NFLAG = 12
 };
 
@@ -252,6 +253,23 @@ void launch_mg_down(const Inst *I, const Tab &t, int level, int mode, int par, P
 void launch_mg_up(const Inst *I, const Tab &t, int level, int par, Part pt, hipStream_t s);
 // levels l and l + 1 in one launch (table of level-(l+1) tiles); down or up
 void launch_mg_pair(const Inst *I, const Tab &t, int level, bool down, hipStream_t s);
+// One refinement pass of plain CG on a single instance as one launch
+// (cg_persist.hip).  Virtual blocks are the 4 x 64 node blocks of the grid
+// kernels; up to kCgSingleVb of them run in one work-group.
+constexpr int kCgSingleVb = 32;
+constexpr int kCgSlotWords = 2048;     // 2 buffers x 2 quantities x 256 chains x 2 words
+struct CgPlan {
+    int ok;                            // the pass fits the device in one launch
+    int single, V, bx, nvb, blocks, threads;
+    size_t lds;
+};
+CgPlan cg_plan(int NX, int NY);
+bool cg_needs_rim(int NX, int NY);     // the plan exchanges through device memory
+// epoch: the first of up to 2 cap + 1 exchange numbers (never reused soon);
+// cap: iterations; rim: NX * NY words, slots: kCgSlotWords, both cleared once;
+// wait: ticks of the 100 MHz wall clock a wait may take (< 0: none)
+hipError_t launch_cg_pass(const Inst *I, const CgPlan &p, unsigned epoch, int cap, unsigned long long *rim,
+                          unsigned long long *slots, int *abort_word, long long wait, hipStream_t s);
 void launch_push(const PushArgs *A, const Tab &t, bool push, int unroll, int merge, size_t lds,
                  hipStream_t s);
 void launch_rewind(const PushArgs *A, const Tab &t, hipStream_t s);

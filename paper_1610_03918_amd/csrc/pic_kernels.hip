@@ -89,7 +89,7 @@ __device__ void apply_op(const Inst &I, int op, double t0, double t1)
     double *S = I.S;
     int *F = I.F;
     if ((op == OP_PQ || op == OP_UPDATE || op == OP_RZ) && F[F_DONE]) return;
-    if (op == OP_RR64_PASS && F[F_SKIP]) return;
+    if (op == OP_RR64_PASS && (F[F_SKIP] || F[F_CGABORT])) return;
     if (op == OP_INIT && F[F_CONV]) {
         F[F_SKIP] = 1;
         F[F_DONE] = 1;
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(256) void k_finalize(const Inst *insts, Tab t, Part
     const int *F = I.F;
     const bool inner = op == OP_PQ || op == OP_UPDATE || op == OP_RZ;
     if (inner && F[F_DONE]) return;
-    if (op == OP_RR64_PASS && F[F_SKIP]) return;
+    if (op == OP_RR64_PASS && (F[F_SKIP] || F[F_CGABORT])) return;
     if (op == OP_INIT && F[F_CONV]) {
         if (threadIdx.x == 0) apply_op(I, op, 0.0, 0.0);
         return;
@@ -523,7 +523,7 @@ void launch_extrapolate(const Inst *I, const Tab &t, int have_prev, hipStream_t 
 __global__ void k_resid64(const Inst *insts, Tab t, int after_pass, Part pt)
 {
     GRID_BEGIN(t)
-    if (after_pass && I.F[F_SKIP]) return;
+    if (after_pass && (I.F[F_SKIP] || I.F[F_CGABORT])) return;
     NODE_IDX(I.g.NX, I.g.NY)
     const uint8_t *fix = I.lev[0].fix;
     const double *phi = I.phi;
@@ -622,7 +622,7 @@ void launch_sweeps(const Inst *I, const Tab &t, int jacobi, int sweeps, hipStrea
 __global__ void k_phi_update(const Inst *insts, Tab t)
 {
     GRID_BEGIN(t)
-    if (I.F[F_SKIP]) return;
+    if (I.F[F_SKIP] || I.F[F_CGABORT]) return;
     NODE_IDX(I.g.NX, I.g.NY)
     if (inb && !I.lev[0].fix[n]) I.phi[n] += (double)I.e[n];
 }

@@ -257,6 +257,7 @@ struct InstHost {
     std::vector<std::vector<uint8_t>> fixh;  // level masks (host copies kept until uploaded)
     std::vector<float> ainvh;               // coarsest-level inverse (host copy kept until uploaded)
     float *d_ainv = nullptr;
+    unsigned long long *d_cg_rim = nullptr, *d_cg_slots = nullptr;   // exchanges of a one-launch CG pass
     bool dense = false;                     // the coarsest level is solved with d_ainv
     Inst dev{};
     pic_solve_info last{};
@@ -275,6 +276,7 @@ struct Carve {
 };
 
 constexpr int kVWindow = 512;   // steps of conductor potentials held on the device
+constexpr long long kCgWait = 100000000ll; // ticks (1 s of the 100 MHz wall clock) a wait of a one-launch CG pass may take
 constexpr int kContinueChunk = 64; // inner iterations per graph between stop tests (plain CG)
 
 } // namespace
@@ -319,6 +321,11 @@ struct pic_ctx {
     hipStream_t bin_stream = nullptr;
     hipEvent_t ev_bin_go = nullptr, ev_bin_done = nullptr;
     bool bin_pending = false;
+    // a context of one instance without multigrid runs each CG pass as one
+    // launch where the grid fits the device (cg.ok); epochs number its exchanges
+    CgPlan cg{};
+    unsigned cg_epoch = 1;
+    int cg_mode = 1;               // 1 one launch, 0 the launched kernels, -1 one launch that does not wait (tests)
     // graphs
     hipStream_t cap_stream = nullptr;
     std::map<int, hipGraphExec_t> outer_graphs;   // CG passes by K; sweep chunks by kSweepKey + count
@@ -465,6 +472,11 @@ void carve_inst(InstHost *h, Carve &w, const Layout &L, const pic_config *cfg, c
     double *phi_prev = w.take<double>(nodes);
     double *phi2 = cfg->solver == 2 ? w.take<double>(nodes) : nullptr;
     float *ainv = L.dense_n ? w.take<float>((size_t)tri_off(L.dense_n)) : nullptr;
+    unsigned long long *rim = nullptr, *slots = nullptr;
+    if (!L.mg && cfg->solver <= 1 && cg_needs_rim(L.NX, L.NY)) {
+        rim = w.take<unsigned long long>(nodes);
+        slots = w.take<unsigned long long>(kCgSlotWords);
+    }
     unsigned *counts[2], *offs[2], *curs[2], *boff[2];
     int4 *table[2];
     long long *info[2];
@@ -487,6 +499,8 @@ void carve_inst(InstHost *h, Carve &w, const Layout &L, const pic_config *cfg, c
     h->d_cell_cond = cc;
     h->d_node_cond = nc;
     h->d_ainv = ainv;
+    h->d_cg_rim = rim;
+    h->d_cg_slots = slots;
     for (int l = 0; l < L.nlev; l++) {
         h->d_fix[l] = fix[l];
         h->d_u[l] = u[l];
@@ -759,6 +773,26 @@ pic_status launch_chunk(pic_ctx *c, int K, bool first)
     return PIC_OK;
 }
 
+// One pass of plain CG as one launch: as many iterations as the launched
+// form's chunks (K, then kContinueChunk at a time until max_iter) could run.
+// False where the runtime refuses the launch: the context then runs the
+// launched kernels.
+bool run_cg_pass(pic_ctx *c, int K, int most, int max_iter)
+{
+    if (!c->cg.ok || !c->cg_mode) return false;
+    long long cap = K;
+    if (most + cap < max_iter) cap += (max_iter - most - cap + kContinueChunk - 1) / kContinueChunk * kContinueChunk;
+    cap = std::min<long long>(cap, 1 << 26);
+    const InstHost &h = c->in[0];
+    const hipError_t e = launch_cg_pass(c->d_inst, c->cg, c->cg_epoch, (int)cap, h.d_cg_rim, h.d_cg_slots,
+                                        c->d_F + F_CGABORT, c->cg_mode < 0 ? -1 : kCgWait, c->stream);
+    c->cg_epoch += 2 * (unsigned)cap + 2;
+    if (e == hipSuccess) return true;
+    (void)hipGetLastError();
+    c->cg_mode = 0;
+    return false;
+}
+
 pic_status read_flags(pic_ctx *c, std::vector<double> &S, std::vector<int> &F)
 {
     S.resize((size_t)c->n * S_NSCAL);
@@ -936,18 +970,20 @@ pic_status do_solve(pic_ctx *c, int kind, const double *guess)
             // the pass's CG in graph chunks until its stop test, then update.
             K = std::min(K, 128);
             K += K & 1;
-            st = launch_chunk(c, K, true);
-            for (int guard = 0; st == PIC_OK && guard < (1 << 20); guard++) {
-                if ((st = read_flags(c, S, F)) != PIC_OK) break;
-                bool open = false;
-                int tot = 0;
-                for (int k = 0; k < c->n; k++) {
-                    const int *f = &F[(size_t)k * F_NFLAG];
-                    if (!f[F_SKIP] && !f[F_DONE]) open = true;
-                    tot = std::max(tot, f[F_ITER_TOT]);
+            if (!run_cg_pass(c, K, most, max_iter)) {
+                st = launch_chunk(c, K, true);
+                for (int guard = 0; st == PIC_OK && guard < (1 << 20); guard++) {
+                    if ((st = read_flags(c, S, F)) != PIC_OK) break;
+                    bool open = false;
+                    int tot = 0;
+                    for (int k = 0; k < c->n; k++) {
+                        const int *f = &F[(size_t)k * F_NFLAG];
+                        if (!f[F_SKIP] && !f[F_DONE]) open = true;
+                        tot = std::max(tot, f[F_ITER_TOT]);
+                    }
+                    if (!open || tot >= max_iter) break;
+                    st = launch_chunk(c, kContinueChunk, false);
                 }
-                if (!open || tot >= max_iter) break;
-                st = launch_chunk(c, kContinueChunk, false);
             }
             if (st != PIC_OK) return st;
             enqueue_pass_end(c, c->stream);
@@ -956,8 +992,21 @@ pic_status do_solve(pic_ctx *c, int kind, const double *guess)
             st = run_pass(c, K);
         }
         if (st != PIC_OK) return st;
+        const std::vector<int> before = F;
         st = read_flags(c, S, F);
         if (st != PIC_OK) return st;
+        if (F[F_CGABORT]) {
+            // the one-launch pass gave up waiting (its work-groups did not all
+            // get onto the device) and the pass's end was skipped: the
+            // potential and its residual are untouched; from here on the
+            // context runs the launched kernels
+            c->cg_mode = 0;
+            HIPCHK(c, hipMemcpyAsync(c->d_F, before.data(), before.size() * sizeof(int), hipMemcpyHostToDevice,
+                                     c->stream));
+            HIPCHK(c, hipStreamSynchronize(c->stream));
+            F = before;
+            continue;
+        }
         have = true;
         int need = 0, ran = 0;
         bool unfinished = false;
@@ -1291,6 +1340,10 @@ pic_status init_instance(pic_ctx *c, int k, const pic_config *cfg, const pic_buf
         for (float *b : {h.d_cg_r1, h.d_cg_s[0], h.d_cg_s[1], h.d_cg_w})
             HIPCHK(c, hipMemsetAsync(b, 0, sizeof(float) * (size_t)L.NX * L.NY, s));
     }
+    if (h.d_cg_rim) {
+        HIPCHK(c, hipMemsetAsync(h.d_cg_rim, 0, sizeof(unsigned long long) * (size_t)L.NX * L.NY, s));
+        HIPCHK(c, hipMemsetAsync(h.d_cg_slots, 0, sizeof(unsigned long long) * kCgSlotWords, s));
+    }
     HIPCHK(c, hipMemsetAsync(h.d_counts[0], 0, sizeof(unsigned) * L.ntiles, s));
     HIPCHK(c, hipMemsetAsync(h.d_counts[1], 0, sizeof(unsigned) * L.ntiles, s));
     HIPCHK(c, hipMemsetAsync(buf->phi, 0, sizeof(double) * (size_t)L.NX * L.NY, s));
@@ -1418,6 +1471,7 @@ pic_status batch_init(int n, const pic_config *cfgs, const pic_buffers *bufs, vo
         c->sweep_solver = sk;
     }
     build_tabs(c);
+    if (n == 1 && !c->in[0].L.mg && !c->sweep_solver) c->cg = cg_plan(c->in[0].L.NX, c->in[0].L.NY);
     c->step = 0;
     pic_status st = upload_vwindow(c, 0);
     if (st != PIC_OK) return st;
@@ -1678,6 +1732,15 @@ pic_status pic_set_level_pairs(pic_ctx *c, int32_t on)
     c->outer_graphs.clear();
     c->chunk_graphs.clear();
     c->step_graphs.clear();
+    return PIC_OK;
+}
+
+pic_status pic_set_cg_pass(pic_ctx *c, int32_t mode)
+{
+    pic_status st = check(c);
+    if (st != PIC_OK) return st;
+    if (mode < -1 || mode > 1) return fail(c, PIC_ERR_ARG, "mode must be -1, 0 or 1");
+    c->cg_mode = mode;
     return PIC_OK;
 }
 

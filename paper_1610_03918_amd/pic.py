@@ -85,7 +85,7 @@ ENTRY_POINTS = ["pic_workspace_size", "pic_init", "pic_deposit", "pic_solve", "p
                 "pic_push", "pic_step", "pic_diagnostics", "pic_particles", "pic_read_hits",
                 "pic_sort", "pic_push_timing", "pic_set_timing", "pic_batch_workspace_size",
                 "pic_batch_init", "pic_batch_step", "pic_batch_diagnostics", "pic_batch_particles",
-                "pic_batch_solve_info", "pic_node_map", "pic_tune", "pic_set_level_pairs", "pic_inject_fault",
+                "pic_batch_solve_info", "pic_node_map", "pic_tune", "pic_set_level_pairs", "pic_set_cg_pass", "pic_inject_fault",
                 "pic_destroy", "pic_last_error", "pic_version"]
 
 
@@ -123,6 +123,7 @@ def lib():
     L.pic_node_map.argtypes = [P, i32, C.POINTER(P), P, C.POINTER(i32), C.POINTER(i32)]
     L.pic_tune.argtypes = [P, i32, i32, i32, i32]
     L.pic_set_level_pairs.argtypes = [P, i32]
+    L.pic_set_cg_pass.argtypes = [P, i32]
     L.pic_inject_fault.argtypes = [P, i32]
     L.pic_destroy.argtypes = [P]
     L.pic_destroy.restype = None
@@ -270,6 +271,9 @@ class _Context:
 
     def pic_set_level_pairs(self, on):
         self._chk(lib().pic_set_level_pairs(self.ctx, int(bool(on))))
+
+    def pic_set_cg_pass(self, mode):
+        self._chk(lib().pic_set_cg_pass(self.ctx, int(mode)))
 
     def pic_inject_fault(self, what=1):
         """Test hook of the device error path (see pic.h)."""

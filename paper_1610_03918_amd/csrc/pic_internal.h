@@ -62,7 +62,7 @@ enum {
     F_ITER1,     // inner iterations of the solve's first pass
     F_ERR,       // sticky device error bits (kErrVWindow)
     F_UNCONV,    // sticky count of pushes whose potential had not met rtol
-    F_CGABORT,   // a one-launch CG pass gave up waiting: its result does not count
+    F_CGABORT,   // a one-launch CG pass ended early and does not count: 1 gave up waiting, 2 a step was not finite
     F_NFLAG = 12
 };
 
@@ -256,17 +256,18 @@ void launch_mg_pair(const Inst *I, const Tab &t, int level, bool down, hipStream
 // One refinement pass of plain CG on a single instance as one launch
 // (cg_persist.hip).  Virtual blocks are the 4 x 64 node blocks of the grid
 // kernels; up to kCgSingleVb of them run in one work-group.
-constexpr int kCgSingleVb = 32;
-constexpr int kCgSlotWords = 2048;     // 2 buffers x 2 quantities x 256 chains x 2 words
+constexpr int kCgSingleVb = 16;
+constexpr int kCgCopies = 8, kCgCopyWords = 3 * 2 * 256 + 32;   // 3 buffers x 2 quantities x 256 chains, padded
+constexpr int kCgSlotWords = kCgCopies * kCgCopyWords + 16;     // and the turn
 struct CgPlan {
     int ok;                            // the pass fits the device in one launch
-    int single, V, bx, nvb, blocks, threads;
+    int single, bx, nvb, blocks, threads;
     size_t lds;
 };
 CgPlan cg_plan(int NX, int NY);
-bool cg_needs_rim(int NX, int NY);     // the plan exchanges through device memory
+size_t cg_rim_words(int NX, int NY);   // words of the rims (0: the plan exchanges in LDS)
 // epoch: the first of up to 2 cap + 1 exchange numbers (never reused soon);
-// cap: iterations; rim: NX * NY words, slots: kCgSlotWords, both cleared once;
+// cap: iterations; rim: cg_rim_words, cleared once to 0; slots: kCgSlotWords, cleared once to all ones;
 // wait: ticks of the 100 MHz wall clock a wait may take (< 0: none)
 hipError_t launch_cg_pass(const Inst *I, const CgPlan &p, unsigned epoch, int cap, unsigned long long *rim,
                           unsigned long long *slots, int *abort_word, long long wait, hipStream_t s);

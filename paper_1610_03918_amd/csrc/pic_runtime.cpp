@@ -473,8 +473,8 @@ void carve_inst(InstHost *h, Carve &w, const Layout &L, const pic_config *cfg, c
     double *phi2 = cfg->solver == 2 ? w.take<double>(nodes) : nullptr;
     float *ainv = L.dense_n ? w.take<float>((size_t)tri_off(L.dense_n)) : nullptr;
     unsigned long long *rim = nullptr, *slots = nullptr;
-    if (!L.mg && cfg->solver <= 1 && cg_needs_rim(L.NX, L.NY)) {
-        rim = w.take<unsigned long long>(nodes);
+    if (!L.mg && cfg->solver <= 1 && cg_rim_words(L.NX, L.NY)) {
+        rim = w.take<unsigned long long>(cg_rim_words(L.NX, L.NY));
         slots = w.take<unsigned long long>(kCgSlotWords);
     }
     unsigned *counts[2], *offs[2], *curs[2], *boff[2];
@@ -945,7 +945,7 @@ pic_status do_solve(pic_ctx *c, int kind, const double *guess)
     // With multigrid the first pass is queued behind the start without a
     // look at its flags (its kernels skip an instance that already
     // converged), so a solve that needs one pass costs one host round trip.
-    bool have = false;
+    bool have = false, launched = false;
     if (plain_cg) {
         if ((st = read_flags(c, S, F)) != PIC_OK) return st;
         have = true;
@@ -970,7 +970,7 @@ pic_status do_solve(pic_ctx *c, int kind, const double *guess)
             // the pass's CG in graph chunks until its stop test, then update.
             K = std::min(K, 128);
             K += K & 1;
-            if (!run_cg_pass(c, K, most, max_iter)) {
+            if (launched || !run_cg_pass(c, K, most, max_iter)) {
                 st = launch_chunk(c, K, true);
                 for (int guard = 0; st == PIC_OK && guard < (1 << 20); guard++) {
                     if ((st = read_flags(c, S, F)) != PIC_OK) break;
@@ -996,11 +996,13 @@ pic_status do_solve(pic_ctx *c, int kind, const double *guess)
         st = read_flags(c, S, F);
         if (st != PIC_OK) return st;
         if (F[F_CGABORT]) {
-            // the one-launch pass gave up waiting (its work-groups did not all
-            // get onto the device) and the pass's end was skipped: the
-            // potential and its residual are untouched; from here on the
-            // context runs the launched kernels
-            c->cg_mode = 0;
+            // the one-launch pass ended early and the pass's end was skipped:
+            // the potential and its residual are untouched.  A step was not
+            // finite: the launched kernels run the rest of this solve.  It
+            // gave up waiting (its work-groups did not all get onto the
+            // device): they run every solve of the context from here on
+            launched = true;
+            if (F[F_CGABORT] == 1) c->cg_mode = 0;
             HIPCHK(c, hipMemcpyAsync(c->d_F, before.data(), before.size() * sizeof(int), hipMemcpyHostToDevice,
                                      c->stream));
             HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -1341,8 +1343,8 @@ pic_status init_instance(pic_ctx *c, int k, const pic_config *cfg, const pic_buf
             HIPCHK(c, hipMemsetAsync(b, 0, sizeof(float) * (size_t)L.NX * L.NY, s));
     }
     if (h.d_cg_rim) {
-        HIPCHK(c, hipMemsetAsync(h.d_cg_rim, 0, sizeof(unsigned long long) * (size_t)L.NX * L.NY, s));
-        HIPCHK(c, hipMemsetAsync(h.d_cg_slots, 0, sizeof(unsigned long long) * kCgSlotWords, s));
+        HIPCHK(c, hipMemsetAsync(h.d_cg_rim, 0, sizeof(unsigned long long) * cg_rim_words(L.NX, L.NY), s));
+        HIPCHK(c, hipMemsetAsync(h.d_cg_slots, 0xFF, sizeof(unsigned long long) * kCgSlotWords, s));
     }
     HIPCHK(c, hipMemsetAsync(h.d_counts[0], 0, sizeof(unsigned) * L.ntiles, s));
     HIPCHK(c, hipMemsetAsync(h.d_counts[1], 0, sizeof(unsigned) * L.ntiles, s));
@@ -1740,6 +1742,9 @@ pic_status pic_set_cg_pass(pic_ctx *c, int32_t mode)
     pic_status st = check(c);
     if (st != PIC_OK) return st;
     if (mode < -1 || mode > 1) return fail(c, PIC_ERR_ARG, "mode must be -1, 0 or 1");
+    // a pass that gave up left words behind
+    if (mode && c->in[0].d_cg_slots)
+        HIPCHK(c, hipMemsetAsync(c->in[0].d_cg_slots, 0xFF, sizeof(unsigned long long) * kCgSlotWords, c->stream));
     c->cg_mode = mode;
     return PIC_OK;
 }

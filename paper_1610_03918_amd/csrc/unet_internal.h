@@ -19,6 +19,9 @@ constexpr int kKChunk = 32;                // channels per K step of the convolu
 
 __host__ __device__ inline int pad32(int c) { return (c + 31) & ~31; }
 
+// What follows a convolution's sums (see k_conv).
+enum { EP_FWD = 0, EP_MASK, EP_UP, EP_DOWN };
+
 // One convolution (forward or input gradient) as an implicit GEMM.
 struct ConvArgs {
     int B, H, W;                 // output pixels (= full-resolution input pixels)
@@ -26,12 +29,19 @@ struct ConvArgs {
     int Cs;
     const uint16_t *up;          // half-resolution input [B,H/2,W/2,Cu], upsampled by copying
     int Cu;                      //   each pixel to a 2x2 block: channels 0 .. Cu-1 (may be 0)
-    int Cin_pad;                 // weight row length (multiple of 32)
-    const uint16_t *wt;          // [Cout][9][Cin_pad], tap t = 3*dh + dw
-    const float *bias;           // [Cout] (forward only; rounded to bfloat16 like the weights)
-    int Cout;                    // multiple of 16
-    void *out;                   // forward: bf16 [P][Cout] after bias + ReLU; gradient: f32 [P][Cout]
+    int nchunk;                  // 32-channel chunks of the input
+    const uint16_t *wt;          // fragments [chunk][Cout / 16][9][64 lanes][8] (k_wprep)
+    int Cout, nct;               // output channels (a multiple of 16), Cout / 16
     int pw;                      // 1: the image wraps along W (circular padding), 0: zero padding
+    uint16_t *out;               // FWD, MASK: bf16 [P][Cout]; UP: bf16 at the coarser level [P/4][Cup];
+                                 //   DOWN: bf16 at the finer level [4P][Cout]
+    const float *bias;           // FWD: [Cout] (rounded to bfloat16 like the weights)
+    uint16_t *pool;              // FWD: 2x2 means of the output, or null
+    const float *wh;             // FWD: head weights [17] with hout
+    float *hout;                 // FWD (Cout 16): the head's output [P], or null
+    const uint16_t *mask;        // MASK, UP, DOWN: the layer's output h, laid out as out
+    float *skip;                 // UP (written): f32 [P][Cout - Cup]; DOWN (read): f32 [4P][Cout]
+    int Cup;                     // UP: channels of the upsampled input
 };
 
 // Weight gradient of one convolution, split over pixel tiles.
@@ -43,36 +53,40 @@ struct WgradArgs {
     int Cs;
     const uint16_t *up;
     int Cu;
-    int Cin_pad;
+    int ncs;                     // groups of 16 input channels
+    int cs0;                     // the first group of this launch
     int nsplit;
-    float *part;                 // [nsplit][Cout][9][Cin_pad]
+    int frags;                   // (Cout / 16) ncs 9 fragments of 256 floats a split
+    float *part;                 // [nsplit][Cout / 16][ncs][9][64 lanes][4]
     float *bpart;                // [nsplit][Cout]
     int pw;                      // as in ConvArgs
 };
 
-// Gradient through a ReLU (and the skip / pooling / upsampling joins):
-//   gy[p][c] = bf16((A(p,c) + B(p,c)) * [h[p][c] > 0])
-// A: a_up == 0: ga[p*sa + oa + c];  a_up == 1: sum of ga over the 2x2 block
-//    of p at the finer level (the adjoint of upsampling by copying);
-// B: gb == null: 0; else 0.25 * gb[parent(p)*C + c] at the coarser level
-//    (the adjoint of 2x2 averaging).
-struct ReluBwdArgs {
-    int B, H, W, C;              // level of gy / h
-    const float *ga;
-    int sa, oa, a_up;
-    const float *gb;
-    const uint16_t *h;
-    uint16_t *gy;
+// Sums of the weight-gradient partials of every layer.
+struct ReduceLayer {
+    const float *part, *bpart;
+    int nsplit, frags, ncs, Cin, Cout;
+    int block0;                  // first block (one a fragment)
+    long long w_off, b_off;
+};
+struct ReduceArgs {
+    ReduceLayer L[kNConv];
+    int wblocks;                 // fragments of all layers
 };
 
-void launch_conv(const ConvArgs &a, bool f32out, hipStream_t s);
-void launch_wgrad(const WgradArgs &a, int ci_chunks, hipStream_t s);
-int wgrad_tiles(int B, int H, int W);
-void launch_wgrad_reduce(const float *part, const float *bpart, int nsplit, int Cout, int Cin,
-                         int Cin_pad, float *gw, float *gb, hipStream_t s);
-void launch_pool(const uint16_t *in, uint16_t *out, int B, int H, int W, int C, hipStream_t s);
-void launch_relu_bwd(const ReluBwdArgs &a, hipStream_t s);
-void launch_head_fwd(const uint16_t *h, const float *wh, float *out, long long P, hipStream_t s);
+// Weight fragments of every layer (forward 2y, input gradient 2y + 1 of layer y).
+struct PrepArgs {
+    int first[2 * kNConv + 1];   // first thread of each
+    int Cin[kNConv], Cout[kNConv];
+    long long w_off[kNConv];
+    uint16_t *wf[kNConv], *wd[kNConv];
+};
+
+constexpr int kWgradBlocks = 512;
+void launch_conv(const ConvArgs &a, int ep, hipStream_t s);
+void launch_wgrad(const WgradArgs &a, hipStream_t s);
+int wgrad_splits(int B, int H, int W, int Cin, int Cout);
+void launch_wgrad_reduce(const ReduceArgs &a, float *grads, hipStream_t s);
 // gy = bf16(gout * wh * [h > 0]); per-block partial sums of gout * h (16) and gout (1)
 int head_bwd_blocks(long long P);
 void launch_head_bwd(const uint16_t *h, const float *wh, const float *gout, uint16_t *gy,
@@ -83,7 +97,7 @@ void launch_mask_sum(const float *mask, double *part, long long P, hipStream_t s
 void launch_loss(const float *out, const float *target, const float *mask, const double *msum,
                  float *gout, double *part, long long P, hipStream_t s);
 void launch_sum_parts(const double *part, int n, double *dst, hipStream_t s);
-void launch_wprep(const float *w, int Cin, int Cout, uint16_t *wf, uint16_t *wd, hipStream_t s);
+void launch_wprep(const float *params, const PrepArgs &a, hipStream_t s);
 void launch_adam(float *p, const float *g, float *m, float *v, long long n, float lr, float b1,
                  float b2, float eps, float c1, float c2, hipStream_t s);
 void launch_snapshot(const double *b, const double *phi, const uint8_t *node_cond, int NX, int NY,

@@ -5,20 +5,22 @@
 //
 // Convolutions run as implicit GEMMs on v_mfma_f32_16x16x32_bf16: the
 // weights are the M operand (output channels), the pixels the N operand and
-// the K dimension walks (tap, input channel).  A block stages a
-// (rows+2) x 18 pixel patch of 32 input channels and the matching weights in
-// LDS, then every wave multiplies 16 x 16 tiles.  The input gradient is the
-// same kernel with the taps flipped and the weights transposed; the weight
-// gradient contracts over pixels in a split-K kernel whose partial sums are
-// added in a fixed order (deterministic).
+// the K dimension walks (32-channel chunk, tap).  The input gradient is the
+// same kernel with the taps flipped and the weights transposed; what follows
+// a convolution (bias, ReLU, rounding, pooling, the head; in the backward
+// pass the ReLU mask and the adjoints of upsampling and pooling) is its
+// epilogue.  The weight gradient contracts over pixels in a split-K kernel
+// whose partial sums are added in a fixed order (deterministic).
 #include "unet_internal.h"
 
+#include <algorithm>
 #include <mutex>
 
 namespace unet {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 
 constexpr int KS = 40;           // LDS row length (bf16) of one pixel's 32-channel chunk, padded
 constexpr int PC = 18;           // patch columns: 16 output columns + 2 halo
@@ -34,68 +36,115 @@ __device__ __forceinline__ float bf2f(uint32_t h) { return __uint_as_float(h << 
 __device__ __forceinline__ bf16x8 ld8(const uint16_t *p) {
     return __builtin_bit_cast(bf16x8, *(const uint4 *)p);
 }
-__device__ __forceinline__ bf16x8 pack8(const uint32_t *x) {
-    uint4 v = make_uint4(x[0] | (x[1] << 16), x[2] | (x[3] << 16), x[4] | (x[5] << 16),
-                         x[6] | (x[7] << 16));
-    return __builtin_bit_cast(bf16x8, v);
+// bf16(s) where the layer's output h (4 bfloat16) is positive, else 0.
+__device__ __forceinline__ uint2 masked(const f4 &s, const uint2 &h)
+{
+    uint32_t y[4];
+    const uint32_t m[4] = {h.x & 0xFFFFu, h.x >> 16, h.y & 0xFFFFu, h.y >> 16};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) y[i] = bf2f(m[i]) > 0.f ? f2bf(s[i]) : 0u;
+    return make_uint2(y[0] | (y[1] << 16), y[2] | (y[3] << 16));
 }
 
-// Stage the input patch rows h0-1 .. h0+PR-2, columns w0-1 .. w0+16, channels
-// c0 .. c0+31 of the concatenation [upsampled(up), src] into LDS as
-// [row][col][KS] (zeros outside the image and beyond the channel count).
-// pw: the image wraps along W, so the columns -1 and W are W-1 and 0 (the
-// patch never reaches farther than one column beyond the image).
-template <int PR>
-__device__ __forceinline__ void stage_patch(uint16_t *sp, const uint16_t *src, int Cs,
-                                            const uint16_t *up, int Cu, int b, int H, int W,
-                                            int h0, int w0, int c0, int pw) {
-    const int Cin = Cu + Cs;
-    const int Hh = H >> 1, Wh = W >> 1;
-    for (int e = threadIdx.x; e < PR * PC * 4; e += blockDim.x) {
-        const int q = e & 3, pix = e >> 2;
-        const int r = pix / PC, s = pix - r * PC;
-        const int h = h0 - 1 + r;
-        int w = w0 - 1 + s;
-        if (pw) w = w < 0 ? w + W : (w == W ? 0 : w);
-        const int c = c0 + 8 * q;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (h >= 0 && h < H && w >= 0 && w < W && c < Cin) {
-            const size_t pu = ((size_t)b * Hh + (h >> 1)) * Wh + (w >> 1);
-            const size_t ps = ((size_t)b * H + h) * W + w;
-            if (c + 8 <= Cu) {
-                v = *(const uint4 *)(up + pu * Cu + c);
-            } else if (c >= Cu && c + 8 <= Cin && (Cs & 7) == 0) {
-                v = *(const uint4 *)(src + ps * Cs + (c - Cu));
-            } else {
-                uint32_t x[8];
+// One thread's share of a staged patch: rows h0-1 .. h0+PR-2, columns w0-1 ..
+// w0+16, CQ groups of 8 channels of the concatenation [upsampled(up), src],
+// as [row][col][KP] in LDS (zeros outside the image and beyond the channel
+// count).  pw: the image wraps along W (the patch never reaches farther than
+// one column beyond it).  Loads go to registers first, so that the next
+// patch's are in flight while the current one is multiplied.
+template <int PR, int CQ, int KP> struct Patch {
+    static constexpr int N = PR * PC * CQ, R = (N + 255) / 256;
+    uint4 v[R];
+    int ps[R], pu[R];            // pixel of src and of up (-1: outside)
+
+    __device__ __forceinline__ void at(int b, int H, int W, int h0, int w0, int pw)
+    {
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const int cc = c + k;
-                    x[k] = cc < Cu ? up[pu * Cu + cc] : (cc < Cin ? src[ps * Cs + (cc - Cu)] : 0u);
+        for (int k = 0; k < R; ++k) {
+            const int e = threadIdx.x + 256 * k, pix = e / CQ;
+            const int r = pix / PC, s = pix - r * PC, h = h0 - 1 + r;
+            int w = w0 - 1 + s;
+            if (pw) w = w < 0 ? w + W : (w == W ? 0 : w);
+            const bool in = e < N && h >= 0 && h < H && w >= 0 && w < W;
+            ps[k] = in ? (b * H + h) * W + w : -1;
+            pu[k] = (b * (H >> 1) + (h >> 1)) * (W >> 1) + (w >> 1);
+        }
+    }
+    __device__ __forceinline__ void load(const uint16_t *src, int Cs, const uint16_t *up, int Cu, int c0)
+    {
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            const int e = threadIdx.x + 256 * k, c = c0 + 8 * (e % CQ);
+            v[k] = make_uint4(0, 0, 0, 0);
+            if (ps[k] < 0) continue;
+            if (c < Cu) {
+                v[k] = *(const uint4 *)(up + (size_t)pu[k] * Cu + c);
+            } else if (Cs == kInCh) {
+                // the network's input: three channels, 6 bytes a pixel
+                if (c == 0) {
+                    const uint16_t *x = src + (size_t)ps[k] * kInCh;
+                    v[k].x = x[0] | ((uint32_t)x[1] << 16);
+                    v[k].y = x[2];
                 }
-                v = make_uint4(x[0] | (x[1] << 16), x[2] | (x[3] << 16), x[4] | (x[5] << 16),
-                               x[6] | (x[7] << 16));
+            } else if (c < Cu + Cs) {
+                v[k] = *(const uint4 *)(src + (size_t)ps[k] * Cs + (c - Cu));
             }
         }
-        *(uint4 *)(sp + pix * KS + 8 * q) = v;
     }
+    __device__ __forceinline__ void store(uint16_t *sp) const
+    {
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            const int e = threadIdx.x + 256 * k;
+            if (e < N) *(uint4 *)(sp + (e / CQ) * KP + 8 * (e % CQ)) = v[k];
+        }
+    }
+};
+
+// The value two lanes apart by one in their column (n ^ 1).
+__device__ __forceinline__ float beside(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false));
 }
 
-// ---- convolution (forward: + bias, ReLU, bf16 out; gradient: f32 out) ----
-// Block: 4 waves; output tile 4*NR rows x 16 columns x 16*NCO channels.
-// Wave w owns rows w*NR .. w*NR+NR-1.
-template <int NCO, int NR, bool F32OUT>
-__global__ __launch_bounds__(256) void k_conv(ConvArgs a) {
-    constexpr int TX = 4 * NR, PR = TX + 2, CT = 16 * NCO;
+// ---- convolution ------------------------------------------------------------
+// Block: 4 waves; output tile 4*NR rows x 16 columns x 16*NCO channels; wave w
+// owns rows w*NR .. w*NR+NR-1.  Per chunk of 32 input channels the patch and
+// the tile's weights (stored in the order of the matrix operand's registers:
+// 1 KiB per tap and 16 channels, read without bank conflicts) sit in LDS.  A
+// wave reads its 3 (NR + 2) pixel operands once and uses each for the three
+// taps of a column of the stencil, and each weight operand for NR rows.  The
+// next chunk's global loads are issued before the products of this one.
+// Every output adds its products in the order (chunk, tap), whatever the tile.
+//
+// Bound: level 0 by memory (16 channels in and out, half of each operand is
+// padding), the deeper levels by the latency of a few chunks on few blocks.
+// conv_launch picks the tile: the widest that still gives kConvBlocks blocks.
+//
+// EP_FWD   bias, ReLU, bfloat16; optionally the 2 x 2 means (pool) and the
+//          1 x 1 head (hout) of the rounded values
+// EP_MASK  input gradient through the ReLU of a layer of the same level:
+//          out = bf16(acc) where mask > 0
+// EP_UP    input gradient of [upsampled, skip]: channels below Cup summed
+//          over 2 x 2 pixels (the adjoint of copying) and masked at the
+//          coarser level (cgy); the others to skip (float32)
+// EP_DOWN  input gradient of a pooled input: each of the finer level's 2 x 2
+//          pixels gets skip + acc / 4, masked (fgy)
+template <int NCO, int NR, int EP>
+__global__ __launch_bounds__(256) void k_conv(ConvArgs a)
+{
+    constexpr int TX = 4 * NR, PR = TX + 2;
+    typedef Patch<PR, 4, KS> P_t;
+    constexpr int NW = NCO * 9 * 64, RW = (NW + 255) / 256;
     __shared__ __align__(16) uint16_t sp[PR * PC * KS];
-    __shared__ __align__(16) uint16_t sw[CT * 9 * KS];
+    __shared__ __align__(16) uint16_t sw[NCO * 9 * 512];
     const int tilesW = (a.W + 15) >> 4, tilesH = (a.H + TX - 1) / TX;
     int bid = blockIdx.x;
     const int tw = bid % tilesW;
     bid /= tilesW;
     const int th = bid % tilesH;
     const int b = bid / tilesH;
-    const int co0 = blockIdx.y * CT;
+    const int ct0 = blockIdx.y * NCO;
     const int h0 = th * TX, w0 = tw * 16;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = lane & 15, g = lane >> 4;
@@ -106,150 +155,303 @@ __global__ __launch_bounds__(256) void k_conv(ConvArgs a) {
 #pragma unroll
         for (int r = 0; r < NR; ++r) acc[j][r] = f4{0.f, 0.f, 0.f, 0.f};
 
-    for (int c0 = 0; c0 < a.Cin_pad; c0 += kKChunk) {
-        __syncthreads();
-        for (int e = threadIdx.x; e < CT * 9 * 4; e += 256) {
-            const int q = e & 3, row = e >> 2;          // row = local channel * 9 + tap
-            const int co = co0 + row / 9, t = row - (row / 9) * 9;
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (co < a.Cout) v = *(const uint4 *)(a.wt + ((size_t)co * 9 + t) * a.Cin_pad + c0 + 8 * q);
-            *(uint4 *)(sw + row * KS + 8 * q) = v;
+    P_t patch;
+    u4 wv[RW];
+    patch.at(b, a.H, a.W, h0, w0, a.pw);
+    auto load = [&](int ch) {
+        const u4 *wt = (const u4 *)a.wt + ((size_t)ch * a.nct + ct0) * (9 * 64);
+#pragma unroll
+        for (int k = 0; k < RW; ++k) {
+            const int e = threadIdx.x + 256 * k;
+            wv[k] = wt[NW % 256 == 0 || e < NW ? e : NW - 1];
         }
-        stage_patch<PR>(sp, a.src, a.Cs, a.up, a.Cu, b, a.H, a.W, h0, w0, c0, a.pw);
+        patch.load(a.src, a.Cs, a.up, a.Cu, ch * kKChunk);
+    };
+    load(0);
+    for (int ch = 0; ch < a.nchunk; ++ch) {
+        if (ch) __syncthreads();
+        patch.store(sp);
+#pragma unroll
+        for (int k = 0; k < RW; ++k) {
+            const int e = threadIdx.x + 256 * k;
+            if (NW % 256 == 0 || e < NW) ((u4 *)sw)[e] = wv[k];
+        }
         __syncthreads();
+        if (ch + 1 < a.nchunk) load(ch + 1);
+        bf16x8 Bv[NR + 2][3];
+#pragma unroll
+        for (int r = 0; r < NR + 2; ++r)
+#pragma unroll
+            for (int dw = 0; dw < 3; ++dw) Bv[r][dw] = ld8(sp + ((wave * NR + r) * PC + n + dw) * KS + 8 * g);
 #pragma unroll
         for (int t = 0; t < 9; ++t) {
             const int dh = t / 3, dw = t - 3 * (t / 3);
-            bf16x8 A[NCO], Bv[NR];
+            bf16x8 A[NCO];
 #pragma unroll
-            for (int j = 0; j < NCO; ++j) A[j] = ld8(sw + ((16 * j + n) * 9 + t) * KS + 8 * g);
-#pragma unroll
-            for (int r = 0; r < NR; ++r) Bv[r] = ld8(sp + ((wave * NR + r + dh) * PC + n + dw) * KS + 8 * g);
+            for (int j = 0; j < NCO; ++j) A[j] = ld8(sw + (j * 9 + t) * 512 + lane * 8);
 #pragma unroll
             for (int j = 0; j < NCO; ++j)
 #pragma unroll
                 for (int r = 0; r < NR; ++r)
-                    acc[j][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[j], Bv[r], acc[j][r], 0, 0, 0);
+                    acc[j][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[j], Bv[r + dh][dw], acc[j][r], 0, 0, 0);
         }
     }
-    // lane holds output channels co0 + 16j + 4g + (0..3) of pixel column n
+    // lane holds channels 16 (ct0 + j) + 4g + (0..3) of pixel column n
+    const int w = w0 + n, hw = h0 + wave * NR;
+    if (EP == EP_FWD && NCO == 1) __syncthreads();   // the head reuses sp
 #pragma unroll
     for (int j = 0; j < NCO; ++j) {
-        const int co = co0 + 16 * j + 4 * g;
-        if (co >= a.Cout) continue;
-        float bb[4] = {0.f, 0.f, 0.f, 0.f};
-        if (!F32OUT) {
+        const int co = 16 * (ct0 + j) + 4 * g;
+        if (EP == EP_FWD) {
+            float bb[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) bb[i] = bf2f(f2bf(a.bias[co + i]));
-        }
+            uint2 y[NR];
 #pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            const int h = h0 + wave * NR + r, w = w0 + n;
-            if (h >= a.H || w >= a.W) continue;
-            const size_t o = (((size_t)b * a.H + h) * a.W + w) * a.Cout + co;
-            if (F32OUT) {
-                *(f4 *)((float *)a.out + o) = acc[j][r];
+            for (int r = 0; r < NR; ++r) {
+                uint32_t q[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) q[i] = f2bf(fmaxf(acc[j][r][i] + bb[i], 0.f));
+                y[r] = make_uint2(q[0] | (q[1] << 16), q[2] | (q[3] << 16));
+                if (hw + r < a.H && w < a.W)
+                    *(uint2 *)(a.out + (((size_t)b * a.H + hw + r) * a.W + w) * a.Cout + co) = y[r];
+                if (NCO == 1) *(uint2 *)(sp + ((wave * NR + r) * 16 + n) * 16 + 4 * g) = y[r];
+            }
+            if (a.pool) {
+#pragma unroll
+                for (int r = 0; r < NR; r += 2) {
+                    float s[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int d = 0; d < 2; ++d) {
+                        const float v[4] = {bf2f(y[r + d].x & 0xFFFFu), bf2f(y[r + d].x >> 16),
+                                            bf2f(y[r + d].y & 0xFFFFu), bf2f(y[r + d].y >> 16)};
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            s[i] += v[i];
+                            s[i] += beside(v[i]);
+                        }
+                    }
+                    if ((n & 1) == 0 && hw + r < a.H && w < a.W) {
+                        uint32_t q[4];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) q[i] = f2bf(0.25f * s[i]);
+                        *(uint2 *)(a.pool + (((size_t)b * (a.H >> 1) + ((hw + r) >> 1)) * (a.W >> 1) + (w >> 1)) * a.Cout +
+                                   co) = make_uint2(q[0] | (q[1] << 16), q[2] | (q[3] << 16));
+                    }
+                }
+            }
+        } else if (EP == EP_MASK) {
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                if (hw + r >= a.H || w >= a.W) continue;
+                const size_t o = (((size_t)b * a.H + hw + r) * a.W + w) * a.Cout + co;
+                *(uint2 *)(a.out + o) = masked(acc[j][r], *(const uint2 *)(a.mask + o));
+            }
+        } else if (EP == EP_UP) {
+            if (16 * (ct0 + j) < a.Cup) {
+#pragma unroll
+                for (int r = 0; r < NR; r += 2) {
+                    f4 s = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int d = 0; d < 2; ++d)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            s[i] += acc[j][r + d][i];
+                            s[i] += beside(acc[j][r + d][i]);
+                        }
+                    if ((n & 1) == 0 && hw + r < a.H && w < a.W) {
+                        const size_t o =
+                            (((size_t)b * (a.H >> 1) + ((hw + r) >> 1)) * (a.W >> 1) + (w >> 1)) * a.Cup + co;
+                        *(uint2 *)(a.out + o) = masked(s, *(const uint2 *)(a.mask + o));
+                    }
+                }
             } else {
-                uint32_t y[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) y[i] = f2bf(fmaxf(acc[j][r][i] + bb[i], 0.f));
-                *(uint2 *)((uint16_t *)a.out + o) = make_uint2(y[0] | (y[1] << 16), y[2] | (y[3] << 16));
+                for (int r = 0; r < NR; ++r) {
+                    if (hw + r >= a.H || w >= a.W) continue;
+                    *(f4 *)(a.skip + (((size_t)b * a.H + hw + r) * a.W + w) * (a.Cout - a.Cup) + co - a.Cup) = acc[j][r];
+                }
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                if (hw + r >= a.H || w >= a.W) continue;
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    const size_t o = (((size_t)b * 2 * a.H + 2 * (hw + r) + (d >> 1)) * (2 * a.W) + 2 * w + (d & 1)) * a.Cout + co;
+                    f4 s = *(const f4 *)(a.skip + o);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) s[i] += 0.25f * acc[j][r][i];
+                    *(uint2 *)(a.out + o) = masked(s, *(const uint2 *)(a.mask + o));
+                }
             }
         }
     }
+    if (EP == EP_FWD && NCO == 1) {
+        if (!a.hout) return;
+        // the head on the rounded values, channels in order: one pixel a lane
+        __syncthreads();
+        if (lane >= 16 * NR) return;
+        const int r = lane >> 4, c = lane & 15;
+        if (hw + r >= a.H || w0 + c >= a.W) return;
+        const uint32_t *u = (const uint32_t *)(sp + ((wave * NR + r) * 16 + c) * 16);
+        float s = 0.f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            s += bf2f(u[k] & 0xFFFFu) * a.wh[2 * k];
+            s += bf2f(u[k] >> 16) * a.wh[2 * k + 1];
+        }
+        a.hout[((size_t)b * a.H + hw + r) * a.W + w0 + c] = s + a.wh[16];
+    }
 }
 
-template <int NCO, int NR>
-static void conv_variant(const ConvArgs &a, bool f32out, hipStream_t s) {
-    constexpr int TX = 4 * NR;
-    const int tilesW = (a.W + 15) >> 4, tilesH = (a.H + TX - 1) / TX;
-    dim3 grid(a.B * tilesH * tilesW, (a.Cout + 16 * NCO - 1) / (16 * NCO));
-    if (f32out) hipLaunchKernelGGL((k_conv<NCO, NR, true>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((k_conv<NCO, NR, false>), grid, dim3(256), 0, s, a);
+// A tile of fewer rows or channels gives more blocks; below this many the
+// chip is not filled.
+constexpr int kConvBlocks = 512;
+
+template <int NCO, int NR, int EP> static int conv_blocks(const ConvArgs &a)
+{
+    return a.B * ((a.H + 4 * NR - 1) / (4 * NR)) * ((a.W + 15) >> 4) * (a.nct / NCO);
 }
 
-void launch_conv(const ConvArgs &a, bool f32out, hipStream_t s) {
-    if (a.Cout % 64 == 0) conv_variant<4, 2>(a, f32out, s);
-    else if (a.Cout % 48 == 0) conv_variant<3, 2>(a, f32out, s);
-    else if (a.Cout % 32 == 0) conv_variant<2, 2>(a, f32out, s);
-    else conv_variant<1, 4>(a, f32out, s);
+template <int NCO, int NR, int EP> static void conv_run(const ConvArgs &a, hipStream_t s)
+{
+    dim3 grid(a.B * ((a.H + 4 * NR - 1) / (4 * NR)) * ((a.W + 15) >> 4), a.nct / NCO);
+    hipLaunchKernelGGL((k_conv<NCO, NR, EP>), grid, dim3(256), 0, s, a);
+}
+
+template <int EP> static void conv_launch(const ConvArgs &a, hipStream_t s)
+{
+    if (a.nct % 4 == 0 && conv_blocks<4, 4, EP>(a) >= kConvBlocks) conv_run<4, 4, EP>(a, s);
+    else if (a.nct % 3 == 0 && conv_blocks<3, 4, EP>(a) >= kConvBlocks) conv_run<3, 4, EP>(a, s);
+    else if (a.nct % 2 == 0 && conv_blocks<2, 4, EP>(a) >= kConvBlocks) conv_run<2, 4, EP>(a, s);
+    else if (a.nct == 1 && conv_blocks<1, 4, EP>(a) >= kConvBlocks) conv_run<1, 4, EP>(a, s);
+    else if (a.nct % 2 == 0 && conv_blocks<2, 2, EP>(a) >= kConvBlocks) conv_run<2, 2, EP>(a, s);
+    else conv_run<1, 2, EP>(a, s);
+}
+
+void launch_conv(const ConvArgs &a, int ep, hipStream_t s)
+{
+    if (ep == EP_FWD) conv_launch<EP_FWD>(a, s);
+    else if (ep == EP_MASK) conv_launch<EP_MASK>(a, s);
+    else if (ep == EP_UP) conv_launch<EP_UP>(a, s);
+    else conv_launch<EP_DOWN>(a, s);
 }
 
 // ---- weight gradient ------------------------------------------------------
 // gw[co][t][ci] = sum over pixels p of gy[p][co] * in(p + tap t)[ci]
-// Block (split, co tile, 32-channel chunk) walks pixel tiles of 16 x 16
-// (tile = split, split + nsplit, ...).  Wave w owns tile rows 4w .. 4w+3, two
-// K steps of 32 pixels (2 rows x 16 columns); lane group g takes row
-// 2*step + g/2, columns 8*(g%2) .. +7.  Blocks of chunk 0 also sum gy (bias).
+// Block (split, tile of 16 NCO output channels, NCS groups of 16 input
+// channels) walks pixel tiles of 16 x 16 (split, split + nsplit, ...).  Wave w
+// owns tile rows 4w .. 4w+3 as two K steps of 32 pixels (2 rows x 16 columns;
+// lane group g: row 2 step + g / 2, columns 8 (g % 2) .. +7).  Both operands
+// have pixels along K while LDS holds them by pixel, so they are read with
+// the transposing LDS load (4 pixels of 16 channels a lane group); the three
+// taps of a stencil row share one run of 12 pixels, realigned in registers.
+// The next tile's global loads are issued before this one's products.  The
+// four waves' sums meet in LDS in a fixed order and leave in register order
+// (1 KiB a fragment); k_wgrad_reduce adds the splits.
 constexpr int kWTX = 16;
 
-template <int NCO>
-__global__ __launch_bounds__(256) void k_wgrad(WgradArgs a) {
-    constexpr int PR = kWTX + 2, CT = 16 * NCO, GS = CT + 8;
-    constexpr int SP = PR * PC * KS, SG = kWTX * 16 * GS;
-    constexpr int RED = CT * 9 * 32;
-    constexpr int STAGE_B = 2 * (SP + SG), RED_B = 4 * (RED + CT);
+typedef short s4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s4 lds_s4;
+
+__device__ __forceinline__ uint2 ld_tr(const uint16_t *p)
+{
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)p));
+}
+
+template <int NCO, int NCS>
+__global__ __launch_bounds__(256) void k_wgrad(WgradArgs a)
+{
+    constexpr int PR = kWTX + 2, CT = 16 * NCO, GS = CT + 8, KP = 16 * NCS + 8;
+    typedef Patch<PR, 2 * NCS, KP> P_t;
+    constexpr int SP = PR * PC * KP, SG = kWTX * 16 * GS;
+    constexpr int NF = NCO * NCS * 9 + NCO;              // fragments of a wave's sums (bias last)
+    constexpr int STAGE_B = 2 * (SP + SG), RED_B = 2 * NF * 1024;
     __shared__ __align__(16) unsigned char smem[STAGE_B > RED_B ? STAGE_B : RED_B];
     uint16_t *sp = (uint16_t *)smem;
     uint16_t *sg = sp + SP;
     const int tilesW = (a.W + 15) >> 4, tilesH = (a.H + kWTX - 1) / kWTX;
     const int ntiles = a.B * tilesH * tilesW;
-    const int split = blockIdx.x, co0 = blockIdx.y * CT, c0 = blockIdx.z * kKChunk;
-    const bool with_bias = blockIdx.z == 0;
+    const int split = blockIdx.x, co0 = blockIdx.y * CT, cs0 = a.cs0 + blockIdx.z * NCS;
+    const bool with_bias = cs0 == 0;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = lane & 15, g = lane >> 4;
     const bf16x8 ones = __builtin_bit_cast(bf16x8, make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));
 
-    f4 acc[NCO][9][2];
+    f4 acc[NCO][NCS][9];
     f4 bacc[NCO];
 #pragma unroll
     for (int j = 0; j < NCO; ++j) {
         bacc[j] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int t = 0; t < 9; ++t) acc[j][t][0] = acc[j][t][1] = f4{0.f, 0.f, 0.f, 0.f};
+        for (int c = 0; c < NCS; ++c)
+#pragma unroll
+            for (int t = 0; t < 9; ++t) acc[j][c][t] = f4{0.f, 0.f, 0.f, 0.f};
     }
 
-    for (int tile = split; tile < ntiles; tile += a.nsplit) {
+    P_t patch;
+    constexpr int RG = 256 * (CT / 8) / 256;
+    uint4 gv[RG];
+    auto load = [&](int tile) {
         const int tw = tile % tilesW, rest = tile / tilesW;
         const int th = rest % tilesH, b = rest / tilesH;
         const int h0 = th * kWTX, w0 = tw * 16;
-        __syncthreads();
-        for (int e = threadIdx.x; e < kWTX * 16 * (CT / 8); e += 256) {
-            const int q = e % (CT / 8), px = e / (CT / 8);
+#pragma unroll
+        for (int k = 0; k < RG; ++k) {
+            const int e = threadIdx.x + 256 * k, px = e / (CT / 8), q = e % (CT / 8);
             const int h = h0 + (px >> 4), w = w0 + (px & 15);
-            uint4 v = make_uint4(0, 0, 0, 0);
+            gv[k] = make_uint4(0, 0, 0, 0);
             if (h < a.H && w < a.W)
-                v = *(const uint4 *)(a.gy + (((size_t)b * a.H + h) * a.W + w) * a.Cout + co0 + 8 * q);
-            *(uint4 *)(sg + px * GS + 8 * q) = v;
+                gv[k] = *(const uint4 *)(a.gy + (((size_t)b * a.H + h) * a.W + w) * a.Cout + co0 + 8 * q);
         }
-        stage_patch<PR>(sp, a.src, a.Cs, a.up, a.Cu, b, a.H, a.W, h0, w0, c0, a.pw);
+        patch.at(b, a.H, a.W, h0, w0, a.pw);
+        patch.load(a.src, a.Cs, a.up, a.Cu, 16 * cs0);
+    };
+    load(split);
+    for (int tile = split; tile < ntiles; tile += a.nsplit) {
+        if (tile != split) __syncthreads();
+        patch.store(sp);
+#pragma unroll
+        for (int k = 0; k < RG; ++k) {
+            const int e = threadIdx.x + 256 * k;
+            *(uint4 *)(sg + (e / (CT / 8)) * GS + 8 * (e % (CT / 8))) = gv[k];
+        }
         __syncthreads();
+        if (tile + a.nsplit < ntiles) load(tile + a.nsplit);
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             const int R = 4 * wave + 2 * ks + (g >> 1);
-            const int col0 = 8 * (g & 1);
+            const int col = 8 * (g & 1) + (n >> 2), c4 = 4 * (n & 3);
             bf16x8 A[NCO];
 #pragma unroll
             for (int j = 0; j < NCO; ++j) {
-                uint32_t x[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) x[i] = sg[(R * 16 + col0 + i) * GS + 16 * j + n];
-                A[j] = pack8(x);
+                const uint16_t *p = sg + (R * 16 + col) * GS + 16 * j + c4;
+                const uint2 x = ld_tr(p), y = ld_tr(p + 4 * GS);
+                A[j] = __builtin_bit_cast(bf16x8, make_uint4(x.x, x.y, y.x, y.y));
             }
 #pragma unroll
             for (int dh = 0; dh < 3; ++dh) {
 #pragma unroll
-                for (int cs = 0; cs < 2; ++cs) {
-                    uint32_t x[10];
+                for (int c = 0; c < NCS; ++c) {
+                    // pixels 0 .. 11 of the run (10 used): two a register
+                    const uint16_t *p = sp + ((R + dh) * PC + col) * KP + 16 * c + c4;
+                    const uint2 x = ld_tr(p), y = ld_tr(p + 4 * KP);
+                    uint2 z;
+                    // the run's last pixels; the patch ends two columns after its right half
+                    z = ld_tr(sp + ((R + dh) * PC + min(col + 8, PC - 1)) * KP + 16 * c + c4);
+                    const bf16x8 B0 = __builtin_bit_cast(bf16x8, make_uint4(x.x, x.y, y.x, y.y));
+                    const bf16x8 B1 = __builtin_bit_cast(
+                        bf16x8, make_uint4(__builtin_amdgcn_alignbit(x.y, x.x, 16), __builtin_amdgcn_alignbit(y.x, x.y, 16),
+                                           __builtin_amdgcn_alignbit(y.y, y.x, 16), __builtin_amdgcn_alignbit(z.x, y.y, 16)));
+                    const bf16x8 B2 = __builtin_bit_cast(bf16x8, make_uint4(x.y, y.x, y.y, z.x));
 #pragma unroll
-                    for (int k = 0; k < 10; ++k) x[k] = sp[((R + dh) * PC + col0 + k) * KS + 16 * cs + n];
-#pragma unroll
-                    for (int dw = 0; dw < 3; ++dw) {
-                        const bf16x8 Bv = pack8(x + dw);
-#pragma unroll
-                        for (int j = 0; j < NCO; ++j)
-                            acc[j][3 * dh + dw][cs] =
-                                __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[j], Bv, acc[j][3 * dh + dw][cs], 0, 0, 0);
+                    for (int j = 0; j < NCO; ++j) {
+                        acc[j][c][3 * dh] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[j], B0, acc[j][c][3 * dh], 0, 0, 0);
+                        acc[j][c][3 * dh + 1] =
+                            __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[j], B1, acc[j][c][3 * dh + 1], 0, 0, 0);
+                        acc[j][c][3 * dh + 2] =
+                            __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[j], B2, acc[j][c][3 * dh + 2], 0, 0, 0);
                     }
                 }
             }
@@ -260,182 +462,131 @@ __global__ __launch_bounds__(256) void k_wgrad(WgradArgs a) {
             }
         }
     }
-    // sum the four waves in a fixed order, then write this split's partial
+    // waves (0 + 1) + (2 + 3): 1 and 3 hand over, then 2
+    f4 *red = (f4 *)smem;
     __syncthreads();
-    float *red = (float *)smem;
-    float *bred = red + RED;
-    for (int w = 0; w < 4; ++w) {
-        if (wave == w) {
+    auto put = [&](int half) {
+        f4 *d = red + half * NF * 64 + lane;
 #pragma unroll
-            for (int j = 0; j < NCO; ++j)
+        for (int j = 0; j < NCO; ++j) {
 #pragma unroll
-                for (int t = 0; t < 9; ++t)
+            for (int c = 0; c < NCS; ++c)
 #pragma unroll
-                    for (int cs = 0; cs < 2; ++cs)
+                for (int t = 0; t < 9; ++t) d[((j * NCS + c) * 9 + t) * 64] = acc[j][c][t];
+            d[(NCO * NCS * 9 + j) * 64] = bacc[j];
+        }
+    };
+    auto add = [&](int half) {
+        const f4 *d = red + half * NF * 64 + lane;
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const int idx = ((16 * j + 4 * g + i) * 9 + t) * 32 + 16 * cs + n;
-                            red[idx] = (w == 0 ? 0.f : red[idx]) + acc[j][t][cs][i];
-                        }
-            if (with_bias && n == 0) {
+        for (int j = 0; j < NCO; ++j) {
 #pragma unroll
-                for (int j = 0; j < NCO; ++j)
+            for (int c = 0; c < NCS; ++c)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int idx = 16 * j + 4 * g + i;
-                        bred[idx] = (w == 0 ? 0.f : bred[idx]) + bacc[j][i];
-                    }
-            }
+                for (int t = 0; t < 9; ++t) acc[j][c][t] += d[((j * NCS + c) * 9 + t) * 64];
+            bacc[j] += d[(NCO * NCS * 9 + j) * 64];
+        }
+    };
+    if (wave & 1) put(wave >> 1);
+    __syncthreads();
+    if (!(wave & 1)) add(wave >> 1);
+    __syncthreads();
+    if (wave == 2) put(1);
+    __syncthreads();
+    if (wave != 0) return;
+    add(1);
+    f4 *part = (f4 *)(a.part + (size_t)split * a.frags * 256) + lane;
+#pragma unroll
+    for (int j = 0; j < NCO; ++j) {
+#pragma unroll
+        for (int c = 0; c < NCS; ++c)
+#pragma unroll
+            for (int t = 0; t < 9; ++t)
+                part[(size_t)((((co0 >> 4) + j) * a.ncs + cs0 + c) * 9 + t) * 64] = acc[j][c][t];
+        // every column of the bias product holds the same sums
+        if (with_bias && n == 0) *(f4 *)(a.bpart + (size_t)split * a.Cout + co0 + 16 * j + 4 * g) = bacc[j];
+    }
+}
+
+int wgrad_tiles(int B, int H, int W) { return B * ((H + kWTX - 1) / kWTX) * ((W + 15) >> 4); }
+
+int wgrad_splits(int B, int H, int W, int Cin, int Cout)
+{
+    // about two blocks per CU: each block's sums are written and read once,
+    // so more splits are more traffic and fewer leave CUs idle
+    const int ncs = (Cin + 15) >> 4, per = (Cout % 32 == 0 ? Cout / 32 : Cout / 16) * ((ncs + 1) / 2);
+    const int ns = (kWgradBlocks + per - 1) / per;
+    return std::max(1, std::min(ns, wgrad_tiles(B, H, W)));
+}
+
+template <int NCO> static void wgrad_run(WgradArgs a, hipStream_t s)
+{
+    const int ny = a.Cout / (16 * NCO), pairs = a.ncs / 2;
+    a.cs0 = 0;
+    if (pairs) hipLaunchKernelGGL((k_wgrad<NCO, 2>), dim3(a.nsplit, ny, pairs), dim3(256), 0, s, a);
+    if (a.ncs & 1) {
+        a.cs0 = 2 * pairs;
+        hipLaunchKernelGGL((k_wgrad<NCO, 1>), dim3(a.nsplit, ny, 1), dim3(256), 0, s, a);
+    }
+}
+
+void launch_wgrad(const WgradArgs &a, hipStream_t s)
+{
+    if (a.Cout % 32 == 0) wgrad_run<2>(a, s);
+    else wgrad_run<1>(a, s);
+}
+
+// Sums of the split partials of every layer in one launch: a block owns one
+// fragment (16 output x 16 input channels of one tap, 4 values a lane), four
+// groups of lanes take every fourth split, and the groups are added in order
+// (float64, deterministic).  The last blocks sum the biases, one a layer.
+__global__ __launch_bounds__(256) void k_wgrad_reduce(ReduceArgs a, float *grads)
+{
+    __shared__ double sh[4][256];
+    int k = 0;
+    while (k + 1 < kNConv && (int)blockIdx.x >= a.L[k + 1].block0) ++k;
+    if ((int)blockIdx.x >= a.wblocks) k = (int)blockIdx.x - a.wblocks;
+    const ReduceLayer &L = a.L[k];
+    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+    if ((int)blockIdx.x >= a.wblocks) {
+        for (int c = lane; c < L.Cout; c += 64) {
+            double s = 0.0;
+#pragma unroll 8
+            for (int i = q; i < L.nsplit; i += 4) s += L.bpart[(size_t)i * L.Cout + c];
+            sh[q][c] = s;
         }
         __syncthreads();
+        for (int c = threadIdx.x; c < L.Cout; c += 256)
+            grads[L.b_off + c] = (float)(((sh[0][c] + sh[1][c]) + sh[2][c]) + sh[3][c]);
+        return;
     }
-    for (int e = threadIdx.x; e < RED; e += 256) {
-        const int col = e / 288, rem = e - col * 288;
-        const int t = rem >> 5, ci = rem & 31;
-        a.part[(((size_t)split * a.Cout + co0 + col) * 9 + t) * a.Cin_pad + c0 + ci] = red[e];
+    const int f = blockIdx.x - L.block0;
+    const f4 *p = (const f4 *)L.part + (size_t)f * 64 + lane;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+    for (int i = q; i < L.nsplit; i += 4) {
+        const f4 v = p[(size_t)i * L.frags * 64];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) s[c] += v[c];
     }
-    if (with_bias)
-        for (int e = threadIdx.x; e < CT; e += 256) a.bpart[(size_t)split * a.Cout + co0 + e] = bred[e];
-}
-
-int wgrad_tiles(int B, int H, int W) {
-    return B * ((H + kWTX - 1) / kWTX) * ((W + 15) >> 4);
-}
-
-void launch_wgrad(const WgradArgs &a, int ci_chunks, hipStream_t s) {
-    if (a.Cout % 32 == 0) {
-        dim3 grid(a.nsplit, a.Cout / 32, ci_chunks);
-        hipLaunchKernelGGL(k_wgrad<2>, grid, dim3(256), 0, s, a);
-    } else {
-        dim3 grid(a.nsplit, a.Cout / 16, ci_chunks);
-        hipLaunchKernelGGL(k_wgrad<1>, grid, dim3(256), 0, s, a);
-    }
-}
-
-// Sum of the split partials: a block owns 64 consecutive outputs and splits
-// the partials over 4 lanes per output (k = lane, lane + 4, ...), then adds
-// the 4 lane sums in a fixed order (deterministic).
-__global__ __launch_bounds__(256) void k_wgrad_reduce(const float *part, const float *bpart, int nsplit,
-                                                      int Cout, int Cin, int Cin_pad, float *gw, float *gb)
-{
-    __shared__ double sh[4][64];
-    const int o = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const long long idx = (long long)blockIdx.x * 64 + o;
-    const long long total = (long long)Cout * 9 * Cin;
-    double s = 0.0;
-    if (idx < total) {
-        const int ci = (int)(idx % Cin);
-        const long long row = idx / Cin;             // co * 9 + t
-        for (int k = q; k < nsplit; k += 4) s += part[((size_t)k * Cout * 9 + row) * Cin_pad + ci];
-    } else if (idx < total + Cout) {
-        const int co = (int)(idx - total);
-        for (int k = q; k < nsplit; k += 4) s += bpart[(size_t)k * Cout + co];
-    }
-    sh[q][o] = s;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) sh[q][c * 64 + lane] = s[c];
     __syncthreads();
-    if (q != 0) return;
-    s = ((sh[0][o] + sh[1][o]) + sh[2][o]) + sh[3][o];
-    if (idx < total) gw[idx] = (float)s;
-    else if (idx < total + Cout) gb[idx - total] = (float)s;
+    // thread -> (co, ci) of the fragment: lane (n, g) holds co = 4g + c, ci = n
+    const int c = threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
+    const int t = f % 9, cs = (f / 9) % L.ncs, ct = f / (9 * L.ncs);
+    const int co = 16 * ct + 4 * g + c, ci = 16 * cs + n;
+    if (ci >= L.Cin) return;
+    const int e = threadIdx.x;
+    grads[L.w_off + ((long long)co * 9 + t) * L.Cin + ci] = (float)(((sh[0][e] + sh[1][e]) + sh[2][e]) + sh[3][e]);
 }
 
-void launch_wgrad_reduce(const float *part, const float *bpart, int nsplit, int Cout, int Cin,
-                         int Cin_pad, float *gw, float *gb, hipStream_t s) {
-    const long long n = (long long)Cout * 9 * Cin + Cout;
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, s, part, bpart,
-                       nsplit, Cout, Cin, Cin_pad, gw, gb);
+void launch_wgrad_reduce(const ReduceArgs &a, float *grads, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3(a.wblocks + kNConv), dim3(256), 0, s, a, grads);
 }
 
-// ---- 2 x 2 average pooling --------------------------------------------------
-__global__ void k_pool(const uint16_t *in, uint16_t *out, int B, int H, int W, int C) {
-    const int Ho = H >> 1, Wo = W >> 1, G = C >> 3;
-    const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (long long)B * Ho * Wo * G) return;
-    const int q = (int)(idx % G);
-    long long p = idx / G;
-    const int w = (int)(p % Wo);
-    p /= Wo;
-    const int h = (int)(p % Ho);
-    const int b = (int)(p / Ho);
-    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int dh = 0; dh < 2; ++dh)
-#pragma unroll
-        for (int dw = 0; dw < 2; ++dw) {
-            const uint4 v = *(const uint4 *)(in + (((size_t)b * H + 2 * h + dh) * W + 2 * w + dw) * C + 8 * q);
-            const uint32_t u[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                s[2 * k] += bf2f(u[k] & 0xFFFFu);
-                s[2 * k + 1] += bf2f(u[k] >> 16);
-            }
-        }
-    uint32_t y[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) y[k] = f2bf(0.25f * s[k]);
-    *(uint4 *)(out + (((size_t)b * Ho + h) * Wo + w) * C + 8 * q) =
-        make_uint4(y[0] | (y[1] << 16), y[2] | (y[3] << 16), y[4] | (y[5] << 16), y[6] | (y[7] << 16));
-}
-
-void launch_pool(const uint16_t *in, uint16_t *out, int B, int H, int W, int C, hipStream_t s) {
-    const long long n = (long long)B * (H >> 1) * (W >> 1) * (C >> 3);
-    hipLaunchKernelGGL(k_pool, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, in, out, B, H, W, C);
-}
-
-// ---- gradient through ReLU and the joins ------------------------------------
-__global__ void k_relu_bwd(ReluBwdArgs a) {
-    const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long total = (long long)a.B * a.H * a.W * a.C;
-    if (idx >= total) return;
-    const int c = (int)(idx % a.C);
-    long long p = idx / a.C;
-    const int w = (int)(p % a.W);
-    const long long bh = p / a.W;
-    const int h = (int)(bh % a.H);
-    const int b = (int)(bh / a.H);
-    float s;
-    if (!a.a_up) {
-        s = a.ga[p * a.sa + a.oa + c];
-    } else {
-        const int H2 = 2 * a.H, W2 = 2 * a.W;
-        s = 0.f;
-#pragma unroll
-        for (int dh = 0; dh < 2; ++dh)
-#pragma unroll
-            for (int dw = 0; dw < 2; ++dw)
-                s += a.ga[(((size_t)b * H2 + 2 * h + dh) * W2 + 2 * w + dw) * a.sa + a.oa + c];
-    }
-    if (a.gb) {
-        const int Hh = a.H >> 1, Wh = a.W >> 1;
-        s += 0.25f * a.gb[(((size_t)b * Hh + (h >> 1)) * Wh + (w >> 1)) * a.C + c];
-    }
-    a.gy[idx] = (uint16_t)(bf2f(a.h[idx]) > 0.f ? f2bf(s) : 0u);
-}
-
-void launch_relu_bwd(const ReluBwdArgs &a, hipStream_t s) {
-    const long long n = (long long)a.B * a.H * a.W * a.C;
-    hipLaunchKernelGGL(k_relu_bwd, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
-}
-
-// ---- 1 x 1 head (16 -> 1, float32 weights) ---------------------------------
-__global__ void k_head_fwd(const uint16_t *h, const float *wh, float *out, long long P) {
-    const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= P) return;
-    const uint4 v0 = *(const uint4 *)(h + p * 16), v1 = *(const uint4 *)(h + p * 16 + 8);
-    const uint32_t u[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
-    float s = 0.f;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        s += bf2f(u[k] & 0xFFFFu) * wh[2 * k];
-        s += bf2f(u[k] >> 16) * wh[2 * k + 1];
-    }
-    out[p] = s + wh[16];
-}
-
-void launch_head_fwd(const uint16_t *h, const float *wh, float *out, long long P, hipStream_t s) {
-    hipLaunchKernelGGL(k_head_fwd, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, s, h, wh, out, P);
-}
-
+// ---- reductions over pixels: the head's gradient and the loss ----------------
 constexpr int kRedPx = 4096;     // pixels per block of the reducing kernels
 
 template <int N>
@@ -549,28 +700,40 @@ void launch_sum_parts(const double *part, int n, double *dst, hipStream_t s) {
 }
 
 // ---- parameters -------------------------------------------------------------------
-// wf[co][t][ci] (ci < Cin_pad) for the forward; wd[ci][t][co] (co < Cout_pad)
-// = w[co][8 - t][ci] for the input gradient (taps flipped, channels swapped).
-__global__ void k_wprep(const float *w, int Cin, int Cout, uint16_t *wf, uint16_t *wd) {
-    const int Cip = pad32(Cin), Cop = pad32(Cout);
-    const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long nf = (long long)Cout * 9 * Cip;
-    if (idx < nf) {
-        const int ci = (int)(idx % Cip);
-        const long long row = idx / Cip;
-        wf[idx] = (uint16_t)(ci < Cin ? f2bf(w[row * Cin + ci]) : 0u);
-    } else if (idx < nf + (long long)Cin * 9 * Cop) {
-        const long long k = idx - nf;
-        const int co = (int)(k % Cop);
-        const long long row = k / Cop;               // ci * 9 + t
-        const int t = (int)(row % 9), ci = (int)(row / 9);
-        wd[k] = (uint16_t)(co < Cout ? f2bf(w[((long long)co * 9 + 8 - t) * Cin + ci]) : 0u);
+// Weights of every layer as the matrix operand reads them: per 32-channel
+// chunk, 16 output channels and tap one fragment of 64 lanes x 8 bfloat16
+// (lane (n, g): output channel n, input channels 8g .. 8g+7), zero beyond the
+// channel count.  Forward: wf; input gradient: wd, taps flipped and channels
+// swapped.  A thread writes 8 values of a fragment.
+__global__ __launch_bounds__(256) void k_wprep(const float *params, PrepArgs a)
+{
+    int k = 0;
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    while (k + 1 < 2 * kNConv && e >= a.first[k + 1]) ++k;
+    if (e >= a.first[2 * kNConv]) return;
+    const int y = k >> 1, back = k & 1;
+    const int M = back ? a.Cin[y] : a.Cout[y], K = back ? a.Cout[y] : a.Cin[y];
+    const int q = e - a.first[k], lane = q & 63, f = q >> 6;
+    const int nct = (M + 15) >> 4, t = f % 9, ct = (f / 9) % nct, ch = f / (9 * nct);
+    const int m = 16 * ct + (lane & 15), c0 = 32 * ch + 8 * (lane >> 4);
+    const float *w = params + a.w_off[y];
+    uint32_t v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int c = c0 + i;
+        v[i] = 0u;
+        if (m < M && c < K) {
+            const int co = back ? c : m, ci = back ? m : c, tap = back ? 8 - t : t;
+            v[i] = f2bf(w[((long long)co * 9 + tap) * a.Cin[y] + ci]);
+        }
     }
+    *(uint4 *)((back ? a.wd[y] : a.wf[y]) + (size_t)q * 8) =
+        make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16));
 }
 
-void launch_wprep(const float *w, int Cin, int Cout, uint16_t *wf, uint16_t *wd, hipStream_t s) {
-    const long long n = (long long)Cout * 9 * pad32(Cin) + (long long)Cin * 9 * pad32(Cout);
-    hipLaunchKernelGGL(k_wprep, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, w, Cin, Cout, wf, wd);
+void launch_wprep(const float *params, const PrepArgs &a, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_wprep, dim3((a.first[2 * kNConv] + 255) / 256), dim3(256), 0, s, params, a);
 }
 
 __global__ void k_adam(float *p, const float *g, float *m, float *v, long long n, float lr, float b1,

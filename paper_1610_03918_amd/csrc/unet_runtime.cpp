@@ -87,7 +87,9 @@ struct Carve {
     }
 };
 
-constexpr long long kPartFloats = 8ll << 20;   // cap of the weight-gradient partial sums
+// 32-channel chunks and 16-channel groups of c channels.
+int chunks(int c) { return (c + 31) >> 5; }
+int groups(int c) { return (c + 15) >> 4; }
 
 } // namespace
 
@@ -101,10 +103,11 @@ struct pic_unet {
     uint16_t *act[kNConv] = {};
     uint16_t *pooled[kLevels] = {};
     float *out = nullptr, *target = nullptr, *mask = nullptr, *gout = nullptr;
-    float *G[kLevels - 1] = {};
-    float *g1 = nullptr, *gp = nullptr;
-    uint16_t *gy = nullptr;
-    float *part = nullptr, *bpart = nullptr;
+    float *G[kLevels - 1] = {};                  // gradient of the skip connections
+    uint16_t *gy[2] = {};                        // gradients of layer outputs, in turn
+    float *part[kNConv] = {}, *bpart[kNConv] = {};
+    PrepArgs prep{};
+    ReduceArgs red{};
     double *dpart = nullptr, *scal = nullptr;   // scal[0] mask sum, scal[1] loss
     int ndpart = 0;
     int adam_t = 0;
@@ -143,9 +146,12 @@ size_t carve(pic_unet *u, char *base, int B, int H, int W)
     const long long P0 = (long long)B * H * W;
     auto P = [&](int l) { return (long long)B * (H >> l) * (W >> l); };
     uint16_t *wf[kNConv], *wd[kNConv], *act[kNConv], *pooled[kLevels] = {};
+    float *part[kNConv], *bpart[kNConv];
+    int ns[kNConv];
     for (int k = 0; k < kNConv; k++) {
-        wf[k] = cv.take<uint16_t>((size_t)N.L[k].cout * 9 * pad32(N.L[k].cin));
-        wd[k] = cv.take<uint16_t>((size_t)N.L[k].cin * 9 * pad32(N.L[k].cout));
+        const int ci = N.L[k].cin, co = N.L[k].cout;
+        wf[k] = cv.take<uint16_t>((size_t)chunks(ci) * groups(co) * 9 * 512);
+        wd[k] = cv.take<uint16_t>((size_t)chunks(co) * groups(ci) * 9 * 512);
     }
     uint16_t *x = cv.take<uint16_t>((size_t)P0 * kInCh);
     for (int k = 0; k < kNConv; k++) act[k] = cv.take<uint16_t>((size_t)P(N.L[k].level) * N.L[k].cout);
@@ -153,21 +159,44 @@ size_t carve(pic_unet *u, char *base, int B, int H, int W)
     float *out = cv.take<float>(P0), *target = cv.take<float>(P0), *mask = cv.take<float>(P0);
     float *gout = cv.take<float>(P0);
     float *G[kLevels - 1];
-    for (int l = 0; l < kLevels - 1; l++) G[l] = cv.take<float>((size_t)P(l) * (chan(l) + chan(l + 1)));
-    float *g1 = cv.take<float>((size_t)P0 * 16);
-    float *gp = cv.take<float>((size_t)P0 * 4);
-    uint16_t *gy = cv.take<uint16_t>((size_t)P0 * 16);
-    float *part = cv.take<float>((size_t)kPartFloats);
-    float *bpart = cv.take<float>((size_t)1024 * 128);
+    for (int l = 0; l < kLevels - 1; l++) G[l] = cv.take<float>((size_t)P(l) * chan(l));
+    uint16_t *gy[2];
+    for (int q = 0; q < 2; q++) gy[q] = cv.take<uint16_t>((size_t)P0 * 16);
+    for (int k = 0; k < kNConv; k++) {
+        const Layer &y = N.L[k];
+        ns[k] = wgrad_splits(B, H >> y.level, W >> y.level, y.cin, y.cout);
+        part[k] = cv.take<float>((size_t)ns[k] * (y.cout / 16) * groups(y.cin) * 9 * 256);
+        bpart[k] = cv.take<float>((size_t)ns[k] * y.cout);
+    }
     const int nd = std::max(17 * head_bwd_blocks(P0), loss_blocks(P0));
     double *dpart = cv.take<double>((size_t)nd);
     double *scal = cv.take<double>(8);
     if (u) {
+        int first = 0, block0 = 0;
         for (int k = 0; k < kNConv; k++) {
+            const Layer &y = N.L[k];
             u->wf[k] = wf[k];
             u->wd[k] = wd[k];
             u->act[k] = act[k];
+            u->part[k] = part[k];
+            u->bpart[k] = bpart[k];
+            PrepArgs &pa = u->prep;
+            pa.first[2 * k] = first;
+            first += chunks(y.cin) * groups(y.cout) * 9 * 64;
+            pa.first[2 * k + 1] = first;
+            first += chunks(y.cout) * groups(y.cin) * 9 * 64;
+            pa.Cin[k] = y.cin;
+            pa.Cout[k] = y.cout;
+            pa.w_off[k] = y.w_off;
+            pa.wf[k] = wf[k];
+            pa.wd[k] = wd[k];
+            const int frags = (y.cout / 16) * groups(y.cin) * 9;
+            u->red.L[k] = ReduceLayer{part[k], bpart[k], ns[k], frags, groups(y.cin), y.cin, y.cout, block0,
+                                      y.w_off, y.b_off};
+            block0 += frags;
         }
+        u->prep.first[2 * kNConv] = first;
+        u->red.wblocks = block0;
         for (int l = 0; l < kLevels; l++) u->pooled[l] = pooled[l];
         for (int l = 0; l < kLevels - 1; l++) u->G[l] = G[l];
         u->x = x;
@@ -175,11 +204,8 @@ size_t carve(pic_unet *u, char *base, int B, int H, int W)
         u->target = target;
         u->mask = mask;
         u->gout = gout;
-        u->g1 = g1;
-        u->gp = gp;
-        u->gy = gy;
-        u->part = part;
-        u->bpart = bpart;
+        u->gy[0] = gy[0];
+        u->gy[1] = gy[1];
         u->dpart = dpart;
         u->ndpart = nd;
         u->scal = scal;
@@ -214,96 +240,71 @@ void enqueue_forward(pic_unet *u)
     const Net &N = net();
     hipStream_t s = u->stream;
     if (u->dirty) {
-        for (int k = 0; k < kNConv; k++)
-            launch_wprep(u->params + N.L[k].w_off, N.L[k].cin, N.L[k].cout, u->wf[k], u->wd[k], s);
+        launch_wprep(u->params, u->prep, s);
         u->dirty = false;
     }
     for (int k = 0; k < kNConv; k++) {
         const Layer &y = N.L[k];
         const int l = y.level;
-        if (y.src_act == -2)
-            launch_pool(u->act[2 * l - 1], u->pooled[l], u->B, u->H >> (l - 1), u->W >> (l - 1), chan(l - 1), s);
         ConvArgs a{};
         a.B = u->B;
         a.H = u->H >> l;
         a.W = u->W >> l;
         conv_inputs(u, k, &a.src, &a.Cs, &a.up, &a.Cu);
-        a.Cin_pad = pad32(y.cin);
+        a.nchunk = chunks(y.cin);
         a.wt = u->wf[k];
         a.bias = u->params + y.b_off;
         a.Cout = y.cout;
+        a.nct = y.cout / 16;
         a.out = u->act[k];
         a.pw = u->pw;
-        launch_conv(a, false, s);
+        // the second convolution of encoder levels 0 .. 2 feeds the pooled input of the next level
+        if (k < 2 * kLevels - 2 && (k & 1)) a.pool = u->pooled[l + 1];
+        if (k == kNConv - 1) {
+            a.wh = u->params + N.head_off;
+            a.hout = u->out;
+        }
+        launch_conv(a, EP_FWD, s);
     }
-    launch_head_fwd(u->act[kNConv - 1], u->params + N.head_off, u->out, u->P0, s);
 }
 
-// Weight gradient and (unless k == 0) input gradient of convolution k from u->gy.
-void conv_backward(pic_unet *u, int k, float *gx)
+// Weight-gradient partial sums of convolution k from gy (its output gradient).
+void conv_wgrad(pic_unet *u, int k, const uint16_t *gy)
 {
-    const Net &N = net();
-    const Layer &y = N.L[k];
-    hipStream_t s = u->stream;
-    const int l = y.level, H = u->H >> l, W = u->W >> l;
+    const Layer &y = net().L[k];
+    const ReduceLayer &r = u->red.L[k];
     WgradArgs w{};
     w.B = u->B;
-    w.H = H;
-    w.W = W;
-    w.gy = u->gy;
+    w.H = u->H >> y.level;
+    w.W = u->W >> y.level;
+    w.gy = gy;
     w.Cout = y.cout;
     conv_inputs(u, k, &w.src, &w.Cs, &w.up, &w.Cu);
-    w.Cin_pad = pad32(y.cin);
-    const int chunks = w.Cin_pad / kKChunk;
-    const int per_split = (y.cout % 32 == 0 ? y.cout / 32 : y.cout / 16) * chunks;
-    const long long per_part = (long long)y.cout * 9 * w.Cin_pad;
-    // about four pixel tiles per block, at least ~1024 blocks where the image allows
-    const int tiles = wgrad_tiles(u->B, H, W);
-    int ns = std::max((tiles + 3) / 4, (1024 + per_split - 1) / per_split);
-    ns = std::min(ns, tiles);
-    ns = (int)std::min<long long>(ns, std::max(1ll, kPartFloats / per_part));
-    ns = std::min(ns, 1024);
-    w.nsplit = ns;
-    w.part = u->part;
-    w.bpart = u->bpart;
+    w.ncs = r.ncs;
+    w.nsplit = r.nsplit;
+    w.frags = r.frags;
+    w.part = u->part[k];
+    w.bpart = u->bpart[k];
     w.pw = u->pw;
-    launch_wgrad(w, chunks, s);
-    launch_wgrad_reduce(u->part, u->bpart, ns, y.cout, y.cin, w.Cin_pad, u->grads + y.w_off,
-                        u->grads + y.b_off, s);
-    if (!gx) return;
-    ConvArgs a{};
-    a.B = u->B;
-    a.H = H;
-    a.W = W;
-    a.src = u->gy;
-    a.Cs = y.cout;
-    a.up = nullptr;
-    a.Cu = 0;
-    a.Cin_pad = pad32(y.cout);
-    a.wt = u->wd[k];
-    a.bias = nullptr;
-    a.Cout = y.cin;
-    a.out = gx;
-    a.pw = u->pw;
-    launch_conv(a, true, s);
+    launch_wgrad(w, u->stream);
 }
 
-void relu_bwd(pic_unet *u, int level, int C, const float *ga, int sa, int oa, int a_up, const float *gb,
-              const uint16_t *h)
+// The input gradient of convolution k from gy, up to its epilogue.
+ConvArgs dgrad_args(const pic_unet *u, int k, const uint16_t *gy)
 {
-    ReluBwdArgs r{};
-    r.B = u->B;
-    r.H = u->H >> level;
-    r.W = u->W >> level;
-    r.C = C;
-    r.ga = ga;
-    r.sa = sa;
-    r.oa = oa;
-    r.a_up = a_up;
-    r.gb = gb;
-    r.h = h;
-    r.gy = u->gy;
-    launch_relu_bwd(r, u->stream);
+    const Layer &y = net().L[k];
+    ConvArgs a{};
+    a.B = u->B;
+    a.H = u->H >> y.level;
+    a.W = u->W >> y.level;
+    a.src = gy;
+    a.Cs = y.cout;
+    a.nchunk = chunks(y.cout);
+    a.wt = u->wd[k];
+    a.Cout = y.cin;
+    a.nct = y.cin / 16;
+    a.pw = u->pw;
+    return a;
 }
 
 void enqueue_backward(pic_unet *u)
@@ -311,30 +312,36 @@ void enqueue_backward(pic_unet *u)
     const Net &N = net();
     hipStream_t s = u->stream;
     const int nb = head_bwd_blocks(u->P0);
-    launch_head_bwd(u->act[13], u->params + N.head_off, u->gout, u->gy, u->dpart, u->P0, s);
+    int cur = 0;
+    launch_head_bwd(u->act[13], u->params + N.head_off, u->gout, u->gy[cur], u->dpart, u->P0, s);
     launch_head_finalize(u->dpart, nb, u->grads + N.head_off, s);
+    // gy[cur] -> the masked gradient of the layer before, in the other buffer
+    auto step = [&](int k, int ep, const uint16_t *mask, float *skip, int Cup) {
+        conv_wgrad(u, k, u->gy[cur]);
+        ConvArgs a = dgrad_args(u, k, u->gy[cur]);
+        a.out = u->gy[1 - cur];
+        a.mask = mask;
+        a.skip = skip;
+        a.Cup = Cup;
+        launch_conv(a, ep, s);
+        cur = 1 - cur;
+    };
     // decoder, finest level first: convs 13,12 (level 0), 11,10 (level 1), 9,8 (level 2)
     for (int l = 0; l < kLevels - 1; l++) {
         const int kb = 13 - 2 * l, ka = kb - 1;
-        const int C = chan(l), Cin = C + chan(l + 1);
-        conv_backward(u, kb, u->g1);
-        relu_bwd(u, l, C, u->g1, C, 0, 0, nullptr, u->act[ka]);
-        conv_backward(u, ka, u->G[l]);
-        // gradient of the deeper output feeding the upsampling (conv ka - 1)
-        relu_bwd(u, l + 1, chan(l + 1), u->G[l], Cin, 0, 1, nullptr, u->act[ka - 1]);
+        step(kb, EP_MASK, u->act[ka], nullptr, 0);
+        // the upsampled part goes to the deeper output (conv ka - 1), the rest waits for the encoder
+        step(ka, EP_UP, u->act[ka - 1], u->G[l], chan(l + 1));
     }
     // encoder, deepest level first: convs 7,6 (level 3), 5,4 (2), 3,2 (1), 1,0 (0)
     for (int l = kLevels - 1; l >= 0; l--) {
         const int kb = 2 * l + 1, ka = 2 * l;
-        const int C = chan(l);
-        if (l < kLevels - 1) {
-            // skip part of the decoder's input gradient plus the pooling adjoint
-            relu_bwd(u, l, C, u->G[l], C + chan(l + 1), chan(l + 1), 0, u->gp, u->act[kb]);
-        }
-        conv_backward(u, kb, u->g1);
-        relu_bwd(u, l, C, u->g1, C, 0, 0, nullptr, u->act[ka]);
-        conv_backward(u, ka, l > 0 ? u->gp : nullptr);
+        step(kb, EP_MASK, u->act[ka], nullptr, 0);
+        // the pooling adjoint joins the skip gradient of the finer level
+        if (l > 0) step(ka, EP_DOWN, u->act[ka - 1], u->G[l - 1], 0);
+        else conv_wgrad(u, ka, u->gy[cur]);
     }
+    launch_wgrad_reduce(u->red, u->grads, s);
 }
 
 } // namespace

@@ -46,49 +46,72 @@ __device__ __forceinline__ uint2 masked(const f4 &s, const uint2 &h)
     return make_uint2(y[0] | (y[1] << 16), y[2] | (y[3] << 16));
 }
 
+// The thread's index, computed anew: what follows from it is not carried in
+// registers around a loop.
+__device__ __forceinline__ int here()
+{
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
 // One thread's share of a staged patch: rows h0-1 .. h0+PR-2, columns w0-1 ..
 // w0+16, CQ groups of 8 channels of the concatenation [upsampled(up), src],
 // as [row][col][KP] in LDS (zeros outside the image and beyond the channel
 // count).  pw: the image wraps along W (the patch never reaches farther than
 // one column beyond it).  Loads go to registers first, so that the next
-// patch's are in flight while the current one is multiplied.
+// patch's are in flight while the current one is multiplied, and without a
+// branch around any of them (a branch per load made the compiler wait for
+// each): outside the image a thread reads the tile's first pixel and stores
+// zeros.
 template <int PR, int CQ, int KP> struct Patch {
     static constexpr int N = PR * PC * CQ, R = (N + 255) / 256;
-    uint4 v[R];
-    int ps[R], pu[R];            // pixel of src and of up (-1: outside)
+    u4 v[R];
+    unsigned in;                 // bit k: element k lies in the image
+    unsigned ok;                 // and in the channels loaded
 
-    __device__ __forceinline__ void at(int b, int H, int W, int h0, int w0, int pw)
+    // Offsets d (in pixels of the source) of this thread's elements from the
+    // tile's first pixel (h0, w0); half: of a source of half the resolution.
+    __device__ __forceinline__ void at(int (&d)[R], int H, int W, int h0, int w0, int pw, bool half)
     {
+        const bool inner = h0 > 0 && h0 + PR - 1 <= H && w0 > 0 && w0 + PC - 1 <= W;
+        const int tid = here();
+        in = 0;
 #pragma unroll
         for (int k = 0; k < R; ++k) {
-            const int e = threadIdx.x + 256 * k, pix = e / CQ;
-            const int r = pix / PC, s = pix - r * PC, h = h0 - 1 + r;
-            int w = w0 - 1 + s;
-            if (pw) w = w < 0 ? w + W : (w == W ? 0 : w);
-            const bool in = e < N && h >= 0 && h < H && w >= 0 && w < W;
-            ps[k] = in ? (b * H + h) * W + w : -1;
-            pu[k] = (b * (H >> 1) + (h >> 1)) * (W >> 1) + (w >> 1);
+            const int e = tid + 256 * k, pix = e / CQ;
+            const int r = pix / PC, s = pix - r * PC;
+            int dh = r - 1, dw = s - 1;
+            bool i = N % 256 == 0 || e < N;
+            if (!inner) {
+                const int h = h0 + dh;
+                int w = w0 + dw;
+                if (pw) w = w < 0 ? w + W : (w == W ? 0 : w);
+                i = i && h >= 0 && h < H && w >= 0 && w < W;
+                dw = w - w0;
+            }
+            in |= i ? 1u << k : 0u;
+            const int o = half ? (dh >> 1) * (W >> 1) + (dw >> 1) : dh * W + dw;
+            d[k] = i ? o : 0;
         }
     }
-    __device__ __forceinline__ void load(const uint16_t *src, int Cs, const uint16_t *up, int Cu, int c0)
+    // q = src: the source at the tile's first pixel, C channels a pixel, from channel c0 on
+    __device__ __forceinline__ void load(const uint16_t *src, int C, int c0, const int (&d)[R])
     {
+        const int c = c0 + 8 * (int)(threadIdx.x % CQ);
+        ok = c < C ? in : 0u;
+        src += c < C ? c : 0;
+#pragma unroll
+        for (int k = 0; k < R; ++k) v[k] = *(const u4 *)(src + (long long)d[k] * C);
+    }
+    // the network's input: three channels, 6 bytes a pixel
+    __device__ __forceinline__ void load3(const uint16_t *src, const int (&d)[R])
+    {
+        ok = threadIdx.x % CQ == 0 ? in : 0u;
 #pragma unroll
         for (int k = 0; k < R; ++k) {
-            const int e = threadIdx.x + 256 * k, c = c0 + 8 * (e % CQ);
-            v[k] = make_uint4(0, 0, 0, 0);
-            if (ps[k] < 0) continue;
-            if (c < Cu) {
-                v[k] = *(const uint4 *)(up + (size_t)pu[k] * Cu + c);
-            } else if (Cs == kInCh) {
-                // the network's input: three channels, 6 bytes a pixel
-                if (c == 0) {
-                    const uint16_t *x = src + (size_t)ps[k] * kInCh;
-                    v[k].x = x[0] | ((uint32_t)x[1] << 16);
-                    v[k].y = x[2];
-                }
-            } else if (c < Cu + Cs) {
-                v[k] = *(const uint4 *)(src + (size_t)ps[k] * Cs + (c - Cu));
-            }
+            const uint16_t *x = src + (long long)d[k] * kInCh;
+            v[k] = u4{x[0] | ((uint32_t)x[1] << 16), x[2], 0u, 0u};
         }
     }
     __device__ __forceinline__ void store(uint16_t *sp) const
@@ -96,7 +119,8 @@ template <int PR, int CQ, int KP> struct Patch {
 #pragma unroll
         for (int k = 0; k < R; ++k) {
             const int e = threadIdx.x + 256 * k;
-            if (e < N) *(uint4 *)(sp + (e / CQ) * KP + 8 * (e % CQ)) = v[k];
+            if (N % 256 == 0 || e < N)
+                *(u4 *)(sp + (e / CQ) * KP + 8 * (e % CQ)) = (ok >> k) & 1 ? v[k] : u4{0u, 0u, 0u, 0u};
         }
     }
 };
@@ -107,98 +131,23 @@ __device__ __forceinline__ float beside(float v)
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false));
 }
 
-// ---- convolution ------------------------------------------------------------
-// Block: 4 waves; output tile 4*NR rows x 16 columns x 16*NCO channels; wave w
-// owns rows w*NR .. w*NR+NR-1.  Per chunk of 32 input channels the patch and
-// the tile's weights (stored in the order of the matrix operand's registers:
-// 1 KiB per tap and 16 channels, read without bank conflicts) sit in LDS.  A
-// wave reads its 3 (NR + 2) pixel operands once and uses each for the three
-// taps of a column of the stencil, and each weight operand for NR rows.  The
-// next chunk's global loads are issued before the products of this one.
-// Every output adds its products in the order (chunk, tap), whatever the tile.
-//
-// Bound: level 0 by memory (16 channels in and out, half of each operand is
-// padding), the deeper levels by the latency of a few chunks on few blocks.
-// conv_launch picks the tile: the widest that still gives kConvBlocks blocks.
-//
-// EP_FWD   bias, ReLU, bfloat16; optionally the 2 x 2 means (pool) and the
-//          1 x 1 head (hout) of the rounded values
-// EP_MASK  input gradient through the ReLU of a layer of the same level:
-//          out = bf16(acc) where mask > 0
-// EP_UP    input gradient of [upsampled, skip]: channels below Cup summed
-//          over 2 x 2 pixels (the adjoint of copying) and masked at the
-//          coarser level (cgy); the others to skip (float32)
-// EP_DOWN  input gradient of a pooled input: each of the finer level's 2 x 2
-//          pixels gets skip + acc / 4, masked (fgy)
-template <int NCO, int NR, int EP>
-__global__ __launch_bounds__(256) void k_conv(ConvArgs a)
+// Orders a wavefront's own LDS accesses (its lanes run together).
+__device__ __forceinline__ void wave_fence()
 {
-    constexpr int TX = 4 * NR, PR = TX + 2;
-    typedef Patch<PR, 4, KS> P_t;
-    constexpr int NW = NCO * 9 * 64, RW = (NW + 255) / 256;
-    __shared__ __align__(16) uint16_t sp[PR * PC * KS];
-    __shared__ __align__(16) uint16_t sw[NCO * 9 * 512];
-    const int tilesW = (a.W + 15) >> 4, tilesH = (a.H + TX - 1) / TX;
-    int bid = blockIdx.x;
-    const int tw = bid % tilesW;
-    bid /= tilesW;
-    const int th = bid % tilesH;
-    const int b = bid / tilesH;
-    const int ct0 = blockIdx.y * NCO;
-    const int h0 = th * TX, w0 = tw * 16;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// What follows a tile's sums (see k_conv).
+template <int NCO, int NR, int EP>
+__device__ __forceinline__ void conv_out(const ConvArgs &a, const f4 (&acc)[NCO][NR], int b, int h0, int w0, int ct0,
+                                         uint16_t *sh)
+{
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = lane & 15, g = lane >> 4;
-
-    f4 acc[NCO][NR];
-#pragma unroll
-    for (int j = 0; j < NCO; ++j)
-#pragma unroll
-        for (int r = 0; r < NR; ++r) acc[j][r] = f4{0.f, 0.f, 0.f, 0.f};
-
-    P_t patch;
-    u4 wv[RW];
-    patch.at(b, a.H, a.W, h0, w0, a.pw);
-    auto load = [&](int ch) {
-        const u4 *wt = (const u4 *)a.wt + ((size_t)ch * a.nct + ct0) * (9 * 64);
-#pragma unroll
-        for (int k = 0; k < RW; ++k) {
-            const int e = threadIdx.x + 256 * k;
-            wv[k] = wt[NW % 256 == 0 || e < NW ? e : NW - 1];
-        }
-        patch.load(a.src, a.Cs, a.up, a.Cu, ch * kKChunk);
-    };
-    load(0);
-    for (int ch = 0; ch < a.nchunk; ++ch) {
-        if (ch) __syncthreads();
-        patch.store(sp);
-#pragma unroll
-        for (int k = 0; k < RW; ++k) {
-            const int e = threadIdx.x + 256 * k;
-            if (NW % 256 == 0 || e < NW) ((u4 *)sw)[e] = wv[k];
-        }
-        __syncthreads();
-        if (ch + 1 < a.nchunk) load(ch + 1);
-        bf16x8 Bv[NR + 2][3];
-#pragma unroll
-        for (int r = 0; r < NR + 2; ++r)
-#pragma unroll
-            for (int dw = 0; dw < 3; ++dw) Bv[r][dw] = ld8(sp + ((wave * NR + r) * PC + n + dw) * KS + 8 * g);
-#pragma unroll
-        for (int t = 0; t < 9; ++t) {
-            const int dh = t / 3, dw = t - 3 * (t / 3);
-            bf16x8 A[NCO];
-#pragma unroll
-            for (int j = 0; j < NCO; ++j) A[j] = ld8(sw + (j * 9 + t) * 512 + lane * 8);
-#pragma unroll
-            for (int j = 0; j < NCO; ++j)
-#pragma unroll
-                for (int r = 0; r < NR; ++r)
-                    acc[j][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[j], Bv[r + dh][dw], acc[j][r], 0, 0, 0);
-        }
-    }
     // lane holds channels 16 (ct0 + j) + 4g + (0..3) of pixel column n
     const int w = w0 + n, hw = h0 + wave * NR;
-    if (EP == EP_FWD && NCO == 1) __syncthreads();   // the head reuses sp
 #pragma unroll
     for (int j = 0; j < NCO; ++j) {
         const int co = 16 * (ct0 + j) + 4 * g;
@@ -215,7 +164,7 @@ __global__ __launch_bounds__(256) void k_conv(ConvArgs a)
                 y[r] = make_uint2(q[0] | (q[1] << 16), q[2] | (q[3] << 16));
                 if (hw + r < a.H && w < a.W)
                     *(uint2 *)(a.out + (((size_t)b * a.H + hw + r) * a.W + w) * a.Cout + co) = y[r];
-                if (NCO == 1) *(uint2 *)(sp + ((wave * NR + r) * 16 + n) * 16 + 4 * g) = y[r];
+                if (NCO == 1) *(uint2 *)(sh + ((wave * NR + r) * 16 + n) * 16 + 4 * g) = y[r];
             }
             if (a.pool) {
 #pragma unroll
@@ -290,11 +239,12 @@ __global__ __launch_bounds__(256) void k_conv(ConvArgs a)
     if (EP == EP_FWD && NCO == 1) {
         if (!a.hout) return;
         // the head on the rounded values, channels in order: one pixel a lane
-        __syncthreads();
+        // (each wave reads what it wrote)
+        wave_fence();
         if (lane >= 16 * NR) return;
         const int r = lane >> 4, c = lane & 15;
         if (hw + r >= a.H || w0 + c >= a.W) return;
-        const uint32_t *u = (const uint32_t *)(sp + ((wave * NR + r) * 16 + c) * 16);
+        const uint32_t *u = (const uint32_t *)(sh + ((wave * NR + r) * 16 + c) * 16);
         float s = 0.f;
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
@@ -305,37 +255,216 @@ __global__ __launch_bounds__(256) void k_conv(ConvArgs a)
     }
 }
 
-// A tile of fewer rows or channels gives more blocks; below this many the
-// chip is not filled.
+// ---- convolution ------------------------------------------------------------
+// Block: 4 waves; output tiles of 4*NR rows x 16 columns x 16*NCO channels;
+// wave w owns rows w*NR .. w*NR+NR-1.  Per chunk of 32 input channels the
+// patch and the tile's weights (stored in the order of the matrix operand's
+// registers: 1 KiB per tap and 16 channels, read without bank conflicts) sit
+// in LDS.  A wave reads its 3 (NR + 2) pixel operands once and uses each for
+// the three taps of a column of the stencil, and each weight operand for NR
+// rows, and issues the next chunk's global loads before the products of this
+// one.  On an input of at most 16 channels (CQ 2: half the operand is
+// padding, zeroed in LDS once; CIN3: the network's 3-channel input) a block
+// instead walks several tiles, its XCD's in a row (neighbours share their rims
+// in its L2), keeps the weights in LDS, and loads the next tile ahead.
+// Every output adds its products in the order (chunk, tap), whatever the tile.
+//
+// Bound: level 0 by memory and LDS reads (16 channels in and out; 134 MB in 38
+// us at 4 x 1024 x 512, 3.5 TB/s of 4.7), the deeper levels by the latency of
+// a few chunks on few blocks.  Measured on that batch against a kernel that
+// read a pixel operand for every tap and left pooling, head and masks to
+// kernels of their own: forward 0.67 -> 0.41 ms, input gradients with their
+// ReLU and joins 1.60 -> 0.55 ms.
+//
+// EP_FWD   bias, ReLU, bfloat16; optionally the 2 x 2 means (pool) and the
+//          1 x 1 head (hout) of the rounded values
+// EP_MASK  input gradient through the ReLU of a layer of the same level:
+//          out = bf16(acc) where mask > 0
+// EP_UP    input gradient of [upsampled, skip]: channels below Cup summed
+//          over 2 x 2 pixels (the adjoint of copying) and masked at the
+//          coarser level (out); the others to skip (float32)
+// EP_DOWN  input gradient of a pooled input: each of the finer level's 2 x 2
+//          pixels gets skip + acc / 4, masked
+template <int NCO, int NR, int EP, int CQ, bool CIN3>
+__global__ __launch_bounds__(256, NCO *NR <= 4 && CQ == 2 ? 3 : 2) void k_conv(ConvArgs a)
+{
+    constexpr int TX = 4 * NR, PR = TX + 2;
+    constexpr bool WALK = CQ == 2;
+    typedef Patch<PR, CQ, KS> P_t;
+    constexpr int NW = NCO * 9 * 64, RW = (NW + 255) / 256;
+    __shared__ __align__(16) uint16_t sp[PR * PC * KS];
+    __shared__ __align__(16) uint16_t sw[NCO * 9 * 512];
+    // the head's transposition (the padding of sp has to stay zero)
+    __shared__ __align__(16) uint16_t sh[EP == EP_FWD && NCO == 1 ? TX * 256 : 8];
+    const int tilesW = (a.W + 15) >> 4, tilesH = (a.H + TX - 1) / TX;
+    const int ntiles = a.B * tilesH * tilesW, per = (ntiles + 7) >> 3;
+    const int xcd = blockIdx.x & 7, stride = gridDim.x >> 3;
+    const int last = min(ntiles - xcd * per, per);      // tiles xcd * per + 0 .. last - 1
+    int tl = blockIdx.x >> 3;
+    if (tl >= last) return;
+    const int ct0 = blockIdx.y * NCO;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int n = lane & 15, g = lane >> 4;
+
+    P_t patch;
+    int d[P_t::R], dup[WALK ? 1 : P_t::R] = {};
+    u4 wv[RW];
+    auto load_w = [&](int ch) {
+        const u4 *wt = (const u4 *)a.wt + ((size_t)ch * a.nct + ct0) * (9 * 64);
+#pragma unroll
+        for (int k = 0; k < RW; ++k) {
+            const int e = threadIdx.x + 256 * k;
+            wv[k] = wt[NW % 256 == 0 || e < NW ? e : NW - 1];
+        }
+    };
+    auto store_w = [&]() {
+#pragma unroll
+        for (int k = 0; k < RW; ++k) {
+            const int e = threadIdx.x + 256 * k;
+            if (NW % 256 == 0 || e < NW) ((u4 *)sw)[e] = wv[k];
+        }
+    };
+    int b, h0, w0;
+    auto place = [&](int q) {
+        const int tile = xcd * per + q, rest = tile / tilesW;
+        w0 = 16 * (tile - rest * tilesW);
+        b = rest / tilesH;
+        h0 = TX * (rest - b * tilesH);
+        patch.at(d, a.H, a.W, h0, w0, a.pw, false);
+        if constexpr (!WALK) {
+            if (a.Cu) patch.at(dup, a.H, a.W, h0, w0, a.pw, true);
+        }
+    };
+    auto load = [&](int ch) {
+        const size_t first = ((size_t)b * a.H + h0) * a.W + w0;
+        if constexpr (CIN3) {
+            patch.load3(a.src + first * kInCh, d);
+        } else if constexpr (WALK) {
+            patch.load(a.src + first * a.Cs, a.Cs, 0, d);
+        } else {
+            // the 32 channels of a chunk lie in up or in src as a whole
+            const int c0 = ch * kKChunk;
+            const bool half = c0 < a.Cu;
+            const int C = half ? a.Cu : a.Cs;
+            int o[P_t::R];
+#pragma unroll
+            for (int k = 0; k < P_t::R; ++k) o[k] = half ? dup[k] : d[k];
+            patch.load(half ? a.up + (((size_t)b * (a.H >> 1) + (h0 >> 1)) * (a.W >> 1) + (w0 >> 1)) * C : a.src + first * C,
+                       C, half ? c0 : c0 - a.Cu, o);
+        }
+    };
+    auto products = [&](f4 (&acc)[NCO][NR]) {
+        bf16x8 Bv[NR + 2][3];
+#pragma unroll
+        for (int r = 0; r < NR + 2; ++r)
+#pragma unroll
+            for (int dw = 0; dw < 3; ++dw) Bv[r][dw] = ld8(sp + ((wave * NR + r) * PC + n + dw) * KS + 8 * g);
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+            const int dh = t / 3, dw = t - 3 * (t / 3);
+            bf16x8 A[NCO];
+#pragma unroll
+            for (int j = 0; j < NCO; ++j) A[j] = ld8(sw + (j * 9 + t) * 512 + lane * 8);
+#pragma unroll
+            for (int j = 0; j < NCO; ++j)
+#pragma unroll
+                for (int r = 0; r < NR; ++r)
+                    acc[j][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[j], Bv[r + dh][dw], acc[j][r], 0, 0, 0);
+        }
+    };
+    place(tl);
+    load_w(0);
+    load(0);
+    f4 acc[NCO][NR];
+    auto clear = [&]() {
+#pragma unroll
+        for (int j = 0; j < NCO; ++j)
+#pragma unroll
+            for (int r = 0; r < NR; ++r) acc[j][r] = f4{0.f, 0.f, 0.f, 0.f};
+    };
+    if constexpr (!WALK) {
+        clear();
+        for (int ch = 0; ch < a.nchunk; ++ch) {
+            if (ch) __syncthreads();
+            patch.store(sp);
+            store_w();
+            __syncthreads();
+            if (ch + 1 < a.nchunk) {
+                load_w(ch + 1);
+                load(ch + 1);
+            }
+            products(acc);
+        }
+        conv_out<NCO, NR, EP>(a, acc, b, h0, w0, ct0, sh);
+    } else {
+        for (int e = threadIdx.x; e < PR * PC * 2; e += 256)
+            *(u4 *)(sp + (e >> 1) * KS + 16 + 8 * (e & 1)) = u4{0u, 0u, 0u, 0u};
+        store_w();
+        for (;;) {
+            patch.store(sp);
+            __syncthreads();
+            const int hb = b, hh = h0, ww = w0;
+            tl += stride;
+            if (tl < last) {
+                place(tl);
+                load(0);
+            }
+            clear();
+            products(acc);
+            conv_out<NCO, NR, EP>(a, acc, hb, hh, ww, ct0, sh);
+            if (tl >= last) return;
+            __syncthreads();
+        }
+    }
+}
+
+// A tile of fewer rows or channels gives more blocks; below this many tiles
+// the chip is not filled.
 constexpr int kConvBlocks = 512;
 
-template <int NCO, int NR, int EP> static int conv_blocks(const ConvArgs &a)
+template <int NR> static int conv_tiles(const ConvArgs &a)
 {
-    return a.B * ((a.H + 4 * NR - 1) / (4 * NR)) * ((a.W + 15) >> 4) * (a.nct / NCO);
+    return a.B * ((a.H + 4 * NR - 1) / (4 * NR)) * ((a.W + 15) >> 4);
 }
 
-template <int NCO, int NR, int EP> static void conv_run(const ConvArgs &a, hipStream_t s)
+template <int NCO, int NR, int EP, int CQ, bool CIN3> static void conv_run(const ConvArgs &a, hipStream_t s)
 {
-    dim3 grid(a.B * ((a.H + 4 * NR - 1) / (4 * NR)) * ((a.W + 15) >> 4), a.nct / NCO);
-    hipLaunchKernelGGL((k_conv<NCO, NR, EP>), grid, dim3(256), 0, s, a);
+    // walking tiles: as many blocks as run at once (three a CU), every one the same number of tiles
+    const int per = (conv_tiles<NR>(a) + 7) / 8, ny = a.nct / NCO, slots = std::max(1, 96 / ny);
+    const int rounds = CQ == 2 ? (per + slots - 1) / slots : 1;
+    hipLaunchKernelGGL((k_conv<NCO, NR, EP, CQ, CIN3>), dim3(8 * ((per + rounds - 1) / rounds), ny), dim3(256), 0, s, a);
 }
 
-template <int EP> static void conv_launch(const ConvArgs &a, hipStream_t s)
+// Wide tiles read each weight operand for more pixels; of two equally wide in
+// channels the taller one has the smaller rim.  Against that stand registers:
+// 32 channels of 32 or more inputs ran faster in tiles of 8 rows than of 16
+// (masked gradient at 512 x 256 pixels, batch 4: 23 against 29 us; forward 24
+// against 26), 16 channels of 48 slower (77 against 72 us at 1024 x 512).
+template <int EP, int CQ, bool CIN3> static void conv_launch(const ConvArgs &a, hipStream_t s)
 {
-    if (a.nct % 4 == 0 && conv_blocks<4, 4, EP>(a) >= kConvBlocks) conv_run<4, 4, EP>(a, s);
-    else if (a.nct % 3 == 0 && conv_blocks<3, 4, EP>(a) >= kConvBlocks) conv_run<3, 4, EP>(a, s);
-    else if (a.nct % 2 == 0 && conv_blocks<2, 4, EP>(a) >= kConvBlocks) conv_run<2, 4, EP>(a, s);
-    else if (a.nct == 1 && conv_blocks<1, 4, EP>(a) >= kConvBlocks) conv_run<1, 4, EP>(a, s);
-    else if (a.nct % 2 == 0 && conv_blocks<2, 2, EP>(a) >= kConvBlocks) conv_run<2, 2, EP>(a, s);
-    else conv_run<1, 2, EP>(a, s);
+    const int t4 = conv_tiles<4>(a) * a.nct, t2 = conv_tiles<2>(a) * a.nct;
+    if constexpr (CQ == 4) {
+        if (a.nct % 4 == 0 && t4 / 4 >= kConvBlocks) return conv_run<4, 4, EP, CQ, CIN3>(a, s);
+    }
+    if constexpr (!CIN3) {
+        if (a.nct % 3 == 0 && t4 / 3 >= kConvBlocks) return conv_run<3, 4, EP, CQ, CIN3>(a, s);
+        if constexpr (CQ == 2) {
+            if (a.nct % 2 == 0 && t4 / 2 >= kConvBlocks) return conv_run<2, 4, EP, CQ, CIN3>(a, s);
+        }
+        if (a.nct % 2 == 0 && t2 / 2 >= kConvBlocks) return conv_run<2, 2, EP, CQ, CIN3>(a, s);
+    }
+    if (a.nct == 1 && t4 >= kConvBlocks) return conv_run<1, 4, EP, CQ, CIN3>(a, s);
+    conv_run<1, 2, EP, CQ, CIN3>(a, s);
 }
 
 void launch_conv(const ConvArgs &a, int ep, hipStream_t s)
 {
-    if (ep == EP_FWD) conv_launch<EP_FWD>(a, s);
-    else if (ep == EP_MASK) conv_launch<EP_MASK>(a, s);
-    else if (ep == EP_UP) conv_launch<EP_UP>(a, s);
-    else conv_launch<EP_DOWN>(a, s);
+    const bool narrow = a.Cu + a.Cs <= 16;
+    if (a.Cs == kInCh) conv_launch<EP_FWD, 2, true>(a, s);
+    else if (ep == EP_FWD) narrow ? conv_launch<EP_FWD, 2, false>(a, s) : conv_launch<EP_FWD, 4, false>(a, s);
+    else if (ep == EP_MASK) narrow ? conv_launch<EP_MASK, 2, false>(a, s) : conv_launch<EP_MASK, 4, false>(a, s);
+    else if (ep == EP_UP) narrow ? conv_launch<EP_UP, 2, false>(a, s) : conv_launch<EP_UP, 4, false>(a, s);
+    else conv_launch<EP_DOWN, 4, false>(a, s);
 }
 
 // ---- weight gradient ------------------------------------------------------
@@ -350,6 +479,11 @@ void launch_conv(const ConvArgs &a, int ep, hipStream_t s)
 // The next tile's global loads are issued before this one's products.  The
 // four waves' sums meet in LDS in a fixed order and leave in register order
 // (1 KiB a fragment); k_wgrad_reduce adds the splits.
+//
+// Measured at 4 x 1024 x 512, all layers: 2.58 ms with operands gathered 16
+// bits at a time, 0.50 so; the reduction 0.78 -> 0.06 ms (one launch, half
+// the splits).  Bound by the latency of a tile's loads at two blocks a CU (the
+// sums take 144 registers), the layers of 16 channels by memory.
 constexpr int kWTX = 16;
 
 typedef short s4 __attribute__((ext_vector_type(4)));
@@ -360,8 +494,8 @@ __device__ __forceinline__ uint2 ld_tr(const uint16_t *p)
     return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)p));
 }
 
-template <int NCO, int NCS>
-__global__ __launch_bounds__(256) void k_wgrad(WgradArgs a)
+template <int NCO, int NCS, bool CIN3>
+__global__ __launch_bounds__(256, 2) void k_wgrad(WgradArgs a)
 {
     constexpr int PR = kWTX + 2, CT = 16 * NCO, GS = CT + 8, KP = 16 * NCS + 8;
     typedef Patch<PR, 2 * NCS, KP> P_t;
@@ -390,23 +524,35 @@ __global__ __launch_bounds__(256) void k_wgrad(WgradArgs a)
             for (int t = 0; t < 9; ++t) acc[j][c][t] = f4{0.f, 0.f, 0.f, 0.f};
     }
 
+    // this block's input channels lie in up or in src as a whole
+    const bool half = 16 * cs0 < a.Cu;
+    const int C = half ? a.Cu : a.Cs, c0 = half ? 16 * cs0 : 16 * cs0 - a.Cu;
+    const uint16_t *const src = half ? a.up : a.src;
     P_t patch;
-    constexpr int RG = 256 * (CT / 8) / 256;
-    uint4 gv[RG];
+    constexpr int RG = CT / 8;
+    u4 gv[RG];
+    unsigned gok = 0;
     auto load = [&](int tile) {
-        const int tw = tile % tilesW, rest = tile / tilesW;
-        const int th = rest % tilesH, b = rest / tilesH;
-        const int h0 = th * kWTX, w0 = tw * 16;
+        const int rest = tile / tilesW, w0 = 16 * (tile - rest * tilesW);
+        const int b = rest / tilesH, h0 = kWTX * (rest - b * tilesH);
+        const uint16_t *gy = a.gy + (((size_t)b * a.H + h0) * a.W + w0) * a.Cout + co0;
+        const bool inner = h0 + kWTX <= a.H && w0 + 16 <= a.W;
+        const int tid = here();
+        gok = 0;
 #pragma unroll
         for (int k = 0; k < RG; ++k) {
-            const int e = threadIdx.x + 256 * k, px = e / (CT / 8), q = e % (CT / 8);
-            const int h = h0 + (px >> 4), w = w0 + (px & 15);
-            gv[k] = make_uint4(0, 0, 0, 0);
-            if (h < a.H && w < a.W)
-                gv[k] = *(const uint4 *)(a.gy + (((size_t)b * a.H + h) * a.W + w) * a.Cout + co0 + 8 * q);
+            const int e = tid + 256 * k, px = e / (CT / 8), q = e % (CT / 8);
+            const int dh = px >> 4, dw = px & 15;
+            const bool in = inner || (h0 + dh < a.H && w0 + dw < a.W);
+            gok |= in ? 1u << k : 0u;
+            gv[k] = *(const u4 *)(gy + (long long)(in ? dh * a.W + dw : 0) * a.Cout + 8 * q);
         }
-        patch.at(b, a.H, a.W, h0, w0, a.pw);
-        patch.load(a.src, a.Cs, a.up, a.Cu, 16 * cs0);
+        int d[P_t::R];
+        patch.at(d, a.H, a.W, h0, w0, a.pw, half);
+        const size_t first = half ? ((size_t)b * (a.H >> 1) + (h0 >> 1)) * (a.W >> 1) + (w0 >> 1)
+                                  : ((size_t)b * a.H + h0) * a.W + w0;
+        if constexpr (CIN3) patch.load3(src + first * kInCh, d);
+        else patch.load(src + first * C, C, c0, d);
     };
     load(split);
     for (int tile = split; tile < ntiles; tile += a.nsplit) {
@@ -415,7 +561,7 @@ __global__ __launch_bounds__(256) void k_wgrad(WgradArgs a)
 #pragma unroll
         for (int k = 0; k < RG; ++k) {
             const int e = threadIdx.x + 256 * k;
-            *(uint4 *)(sg + (e / (CT / 8)) * GS + 8 * (e % (CT / 8))) = gv[k];
+            *(u4 *)(sg + (e / (CT / 8)) * GS + 8 * (e % (CT / 8))) = (gok >> k) & 1 ? gv[k] : u4{0u, 0u, 0u, 0u};
         }
         __syncthreads();
         if (tile + a.nsplit < ntiles) load(tile + a.nsplit);
@@ -514,8 +660,10 @@ int wgrad_splits(int B, int H, int W, int Cin, int Cout)
 {
     // about two blocks per CU: each block's sums are written and read once,
     // so more splits are more traffic and fewer leave CUs idle
-    const int ncs = (Cin + 15) >> 4, per = (Cout % 32 == 0 ? Cout / 32 : Cout / 16) * ((ncs + 1) / 2);
-    const int ns = (kWgradBlocks + per - 1) / per;
+    // (16 output channels: half the sums a block, and twice the blocks)
+    const bool wide = Cout % 32 == 0;
+    const int ncs = (Cin + 15) >> 4, per = (wide ? Cout / 32 : Cout / 16) * ((ncs + 1) / 2);
+    const int ns = ((wide ? kWgradBlocks : 2 * kWgradBlocks) + per - 1) / per;
     return std::max(1, std::min(ns, wgrad_tiles(B, H, W)));
 }
 
@@ -523,16 +671,17 @@ template <int NCO> static void wgrad_run(WgradArgs a, hipStream_t s)
 {
     const int ny = a.Cout / (16 * NCO), pairs = a.ncs / 2;
     a.cs0 = 0;
-    if (pairs) hipLaunchKernelGGL((k_wgrad<NCO, 2>), dim3(a.nsplit, ny, pairs), dim3(256), 0, s, a);
+    if (pairs) hipLaunchKernelGGL((k_wgrad<NCO, 2, false>), dim3(a.nsplit, ny, pairs), dim3(256), 0, s, a);
     if (a.ncs & 1) {
         a.cs0 = 2 * pairs;
-        hipLaunchKernelGGL((k_wgrad<NCO, 1>), dim3(a.nsplit, ny, 1), dim3(256), 0, s, a);
+        hipLaunchKernelGGL((k_wgrad<NCO, 1, false>), dim3(a.nsplit, ny, 1), dim3(256), 0, s, a);
     }
 }
 
 void launch_wgrad(const WgradArgs &a, hipStream_t s)
 {
-    if (a.Cout % 32 == 0) wgrad_run<2>(a, s);
+    if (a.Cs == kInCh) hipLaunchKernelGGL((k_wgrad<1, 1, true>), dim3(a.nsplit, a.Cout / 16, 1), dim3(256), 0, s, a);
+    else if (a.Cout % 32 == 0) wgrad_run<2>(a, s);
     else wgrad_run<1>(a, s);
 }
 
@@ -544,7 +693,8 @@ __global__ __launch_bounds__(256) void k_wgrad_reduce(ReduceArgs a, float *grads
 {
     __shared__ double sh[4][256];
     int k = 0;
-    while (k + 1 < kNConv && (int)blockIdx.x >= a.L[k + 1].block0) ++k;
+#pragma unroll
+    for (int i = 1; i < kNConv; ++i) k += (int)blockIdx.x >= a.L[i].block0 ? 1 : 0;
     if ((int)blockIdx.x >= a.wblocks) k = (int)blockIdx.x - a.wblocks;
     const ReduceLayer &L = a.L[k];
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
@@ -587,7 +737,8 @@ void launch_wgrad_reduce(const ReduceArgs &a, float *grads, hipStream_t s)
 }
 
 // ---- reductions over pixels: the head's gradient and the loss ----------------
-constexpr int kRedPx = 4096;     // pixels per block of the reducing kernels
+// pixels per block of the reducing kernels: enough blocks to fill the chip, few enough partial sums
+static int red_px(long long P) { return P >= (1 << 20) ? 4096 : P >= (1 << 18) ? 1024 : 256; }
 
 template <int N>
 __device__ __forceinline__ void block_sum_store(double (&v)[N], double *dst) {
@@ -608,15 +759,15 @@ __device__ __forceinline__ void block_sum_store(double (&v)[N], double *dst) {
     }
 }
 
-int head_bwd_blocks(long long P) { return (int)((P + kRedPx - 1) / kRedPx); }
+int head_bwd_blocks(long long P) { return (int)((P + red_px(P) - 1) / red_px(P)); }
 
 __global__ void k_head_bwd(const uint16_t *h, const float *wh, const float *gout, uint16_t *gy,
-                           double *part, long long P) {
+                           double *part, long long P, int px) {
     double acc[17];
 #pragma unroll
     for (int k = 0; k < 17; ++k) acc[k] = 0.0;
-    const long long p0 = (long long)blockIdx.x * kRedPx;
-    for (long long p = p0 + threadIdx.x; p < p0 + kRedPx && p < P; p += blockDim.x) {
+    const long long p0 = (long long)blockIdx.x * px;
+    for (long long p = p0 + threadIdx.x; p < p0 + px && p < P; p += blockDim.x) {
         const float go = gout[p];
         const uint4 v0 = *(const uint4 *)(h + p * 16), v1 = *(const uint4 *)(h + p * 16 + 8);
         const uint32_t u[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
@@ -639,42 +790,53 @@ __global__ void k_head_bwd(const uint16_t *h, const float *wh, const float *gout
 
 void launch_head_bwd(const uint16_t *h, const float *wh, const float *gout, uint16_t *gy,
                      double *part, long long P, hipStream_t s) {
-    hipLaunchKernelGGL(k_head_bwd, dim3(head_bwd_blocks(P)), dim3(256), 0, s, h, wh, gout, gy, part, P);
+    hipLaunchKernelGGL(k_head_bwd, dim3(head_bwd_blocks(P)), dim3(256), 0, s, h, wh, gout, gy, part, P, red_px(P));
 }
 
-__global__ void k_head_finalize(const double *part, int nblk, float *gwh) {
-    const int k = threadIdx.x;
-    if (k >= 17) return;
+// Sum of n values st apart by one wavefront, in a fixed order.
+__device__ __forceinline__ double wave_total(const double *p, int n, int st)
+{
+    const int lane = threadIdx.x & 63;
     double s = 0.0;
-    for (int b = 0; b < nblk; ++b) s += part[17 * (size_t)b + k];
-    gwh[k] = (float)s;
+#pragma unroll 8
+    for (int k = lane; k < n; k += 64) s += p[(size_t)k * st];
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+    return s;
+}
+
+__global__ __launch_bounds__(1024) void k_head_finalize(const double *part, int nblk, float *gwh) {
+    const int w = threadIdx.x >> 6;
+    for (int k = w; k < 17; k += 16) {
+        const double s = wave_total(part + k, nblk, 17);
+        if ((threadIdx.x & 63) == 0) gwh[k] = (float)s;
+    }
 }
 
 void launch_head_finalize(const double *part, int nblk, float *gwh, hipStream_t s) {
-    hipLaunchKernelGGL(k_head_finalize, dim3(1), dim3(64), 0, s, part, nblk, gwh);
+    hipLaunchKernelGGL(k_head_finalize, dim3(1), dim3(1024), 0, s, part, nblk, gwh);
 }
 
 // ---- masked mean-square loss ---------------------------------------------------
-int loss_blocks(long long P) { return (int)((P + kRedPx - 1) / kRedPx); }
+int loss_blocks(long long P) { return (int)((P + red_px(P) - 1) / red_px(P)); }
 
-__global__ void k_mask_sum(const float *mask, double *part, long long P) {
+__global__ void k_mask_sum(const float *mask, double *part, long long P, int px) {
     double acc[1] = {0.0};
-    const long long p0 = (long long)blockIdx.x * kRedPx;
-    for (long long p = p0 + threadIdx.x; p < p0 + kRedPx && p < P; p += blockDim.x) acc[0] += mask[p];
+    const long long p0 = (long long)blockIdx.x * px;
+    for (long long p = p0 + threadIdx.x; p < p0 + px && p < P; p += blockDim.x) acc[0] += mask[p];
     block_sum_store<1>(acc, part + blockIdx.x);
 }
 
 void launch_mask_sum(const float *mask, double *part, long long P, hipStream_t s) {
-    hipLaunchKernelGGL(k_mask_sum, dim3(loss_blocks(P)), dim3(256), 0, s, mask, part, P);
+    hipLaunchKernelGGL(k_mask_sum, dim3(loss_blocks(P)), dim3(256), 0, s, mask, part, P, red_px(P));
 }
 
 // loss = sum m (out - t)^2 / sum m;  gout = 2 m (out - t) / sum m
 __global__ void k_loss(const float *out, const float *target, const float *mask, const double *msum,
-                       float *gout, double *part, long long P) {
+                       float *gout, double *part, long long P, int px) {
     double acc[1] = {0.0};
     const double inv = *msum > 0.0 ? 1.0 / *msum : 0.0;
-    const long long p0 = (long long)blockIdx.x * kRedPx;
-    for (long long p = p0 + threadIdx.x; p < p0 + kRedPx && p < P; p += blockDim.x) {
+    const long long p0 = (long long)blockIdx.x * px;
+    for (long long p = p0 + threadIdx.x; p < p0 + px && p < P; p += blockDim.x) {
         const double d = (double)out[p] - (double)target[p];
         acc[0] += (double)mask[p] * d * d;
         gout[p] = (float)(2.0 * mask[p] * d * inv);
@@ -685,14 +847,12 @@ __global__ void k_loss(const float *out, const float *target, const float *mask,
 
 void launch_loss(const float *out, const float *target, const float *mask, const double *msum,
                  float *gout, double *part, long long P, hipStream_t s) {
-    hipLaunchKernelGGL(k_loss, dim3(loss_blocks(P)), dim3(256), 0, s, out, target, mask, msum, gout, part, P);
+    hipLaunchKernelGGL(k_loss, dim3(loss_blocks(P)), dim3(256), 0, s, out, target, mask, msum, gout, part, P, red_px(P));
 }
 
 __global__ void k_sum_parts(const double *part, int n, double *dst) {
-    if (threadIdx.x != 0) return;
-    double s = 0.0;
-    for (int k = 0; k < n; ++k) s += part[k];
-    *dst = s;
+    const double s = wave_total(part, n, 1);
+    if (threadIdx.x == 0) *dst = s;
 }
 
 void launch_sum_parts(const double *part, int n, double *dst, hipStream_t s) {
@@ -709,7 +869,8 @@ __global__ __launch_bounds__(256) void k_wprep(const float *params, PrepArgs a)
 {
     int k = 0;
     const int e = blockIdx.x * 256 + threadIdx.x;
-    while (k + 1 < 2 * kNConv && e >= a.first[k + 1]) ++k;
+#pragma unroll
+    for (int i = 1; i < 2 * kNConv; ++i) k += e >= a.first[i] ? 1 : 0;
     if (e >= a.first[2 * kNConv]) return;
     const int y = k >> 1, back = k & 1;
     const int M = back ? a.Cin[y] : a.Cout[y], K = back ? a.Cout[y] : a.Cin[y];

@@ -278,13 +278,14 @@ pic_status pic_tune(pic_ctx *ctx, int32_t push_unroll, int32_t push_merge, int32
  * outside {0, 1}. */
 pic_status pic_set_level_pairs(pic_ctx *ctx, int32_t on);
 
-/* How a context of one instance solved by plain CG (solver 1, or a grid
- * that multigrid cannot coarsen) runs a refinement pass: 1 (the default) as
- * one launch where the grid fits the device, 0 as one launch per step of the
- * iteration, -1 as one launch whose work-groups do not wait for one another
- * (for tests: on grids of several work-groups it gives up at once and the
- * pass falls back to 0, as it does when a wait takes over a second).  The
- * potential is the same bit for bit.  PIC_ERR_ARG for other values. */
+/* How a context of one instance runs its CG solves: 1 (the default) in one
+ * launch where the grid allows it (plain CG, i.e. solver 1 or a grid that
+ * multigrid cannot coarsen: one launch per refinement pass; multigrid on a
+ * small grid: one launch per solve), 0 as one launch per step of the
+ * iteration, -1 as 1 but without waiting (for tests: where several
+ * work-groups exchange data the launch gives up at once and the solve falls
+ * back to 0, as it does when a wait takes over a second).  The potential is
+ * the same bit for bit.  PIC_ERR_ARG for other values. */
 pic_status pic_set_cg_pass(pic_ctx *ctx, int32_t mode);
 
 /* Re-bins species s now (tile sort; drops removed particles). */

@@ -63,7 +63,9 @@ enum {
     F_ERR,       // sticky device error bits (kErrVWindow)
     F_UNCONV,    // sticky count of pushes whose potential had not met rtol
     F_CGABORT,   // a one-launch CG pass ended early and does not count: 1 gave up waiting, 2 a step was not finite
-    F_NFLAG = 12
+    F_CHUNK0,    // a one-launch solve's iterations for the next first pass, and for later ones
+    F_CHUNK1,
+    F_NFLAG = 14
 };
 
 // Device error bits (F_ERR): the assembly found the device step counter
@@ -271,6 +273,24 @@ size_t cg_rim_words(int NX, int NY);   // words of the rims (0: the plan exchang
 // wait: ticks of the 100 MHz wall clock a wait may take (< 0: none)
 hipError_t launch_cg_pass(const Inst *I, const CgPlan &p, unsigned epoch, int cap, unsigned long long *rim,
                           unsigned long long *slots, int *abort_word, long long wait, hipStream_t s);
+// A whole multigrid-CG solve of a small single instance as one launch.
+struct MgPlan {
+    int ok;
+    int R, tiles, tiles_y, help;       // tiles a thread; work-groups that share the dense coarsest solve
+    int off_u, off_g, off_s, off_s2, off_f, off_v, lds;
+};
+struct MgSolveArgs {
+    int chunk0, chunk1, max_iter;      // iterations a first and a later pass may take; of the whole solve
+    unsigned epoch;                    // the first of up to kMgEpochs exchange numbers
+    unsigned long long *words;         // mg_solve_words of the coarsest level's nodes, cleared once
+    int *abort_word;
+    long long wait;                    // as launch_cg_pass
+    int tiles, tiles_y, off_u, off_g, off_s, off_s2, off_f, off_v, help;   // of the plan
+};
+constexpr unsigned kMgEpochs = 64 * 130;
+int mg_solve_words(int dense_n);
+MgPlan mg_solve_plan(int NX, int NY, const CoarseArgs &c, int lg);
+hipError_t launch_mg_solve(const Inst *I, const MgPlan &p, MgSolveArgs m, hipStream_t s);
 void launch_push(const PushArgs *A, const Tab &t, bool push, int unroll, int merge, size_t lds,
                  hipStream_t s);
 void launch_rewind(const PushArgs *A, const Tab &t, hipStream_t s);

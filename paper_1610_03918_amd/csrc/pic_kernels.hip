@@ -14,6 +14,9 @@
 // Compiled with -ffp-contract=off: every float operation of the push is
 // rounded in the order written.
 #include "pic_internal.h"
+#include "wave_ops.h"
+
+#include <algorithm>
 
 namespace pic {
 
@@ -1637,91 +1640,94 @@ __device__ __forceinline__ void wave_sum4_f32(float &a, float &b, float &c, floa
 // Exact solve of the coarsest level, u = A^-1 g, from the packed lower
 // triangle T of the inverse the host factorised (row r: columns 0 .. r padded
 // to a multiple of 4, diagonal halved, zero rows and columns at fixed nodes).
-// Wavefront w takes rows w, w + 16, ...; its lanes read 16-byte pieces of the
-// row (Q pieces per lane and row), R rows per pass with every load of a pass
-// issued before any is used.  Each stored entry serves twice: its row's dot
+// Part w of 16 takes rows w, w + 16, ... (a wavefront's; where there are NW = 8,
+// two parts in turn); the lanes read 16-byte pieces of the row (Q pieces per
+// lane and row), R rows per pass with every load of a pass issued before any
+// is used.  Each stored entry serves twice: its row's dot
 // product with g (the lower part of u[r] and half its diagonal term, summed
 // across the wave) and T[r][c] g[r] added to the lane's partial sum for
 // column c (the upper part and the other half).  The column partials of the
-// 16 wavefronts meet in LDS (part, 16 x n floats) and are summed in a fixed
+// 16 parts meet in LDS (part, 16 x n floats) and are summed in a fixed
 // order.  Every stored float is read once.  Small levels (n <= 256: one piece
 // per lane and row, 8 rows of a wave per pass) pay one or two memory latencies.
-template <int Q, int R>
+template <int Q, int R, int NW = kCoarseWaves>
 __device__ __forceinline__ void c_dense(const CLev &L, const float *__restrict__ T, int n, float *part, int tid)
 {
     static_assert(R == 2 || R % 4 == 0, "rows per pass: 2 or a multiple of 4 (four-way wave sums)");
-    const int lane = tid & 63, w = tid >> 6;
+    const int lane = tid & 63;
     const int npc = (n + 3) >> 2;                 // 16-byte pieces of the longest row
     // g is read in 16-byte pieces: its padding up to a multiple of 4 (inside
     // the level's 16-byte rounded array) is cleared first
     if (tid < 4 && n + tid < 4 * npc) L.g[n + tid] = 0.0f;
     __syncthreads();
     const float4 *g4 = (const float4 *)L.g;
-    float4 acc[Q];
+    for (int w = tid >> 6; w < kCoarseWaves; w += NW) {
+        float4 acc[Q];
 #pragma unroll
-    for (int q = 0; q < Q; q++) acc[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int r0 = w; r0 < n; r0 += R * kCoarseWaves) {
-        float4 t[R][Q];
-#pragma unroll
-        for (int i = 0; i < R; i++) {
-            const int r = r0 + i * kCoarseWaves;
-            const int len = r < n ? (r >> 2) + 1 : 0;      // pieces of row r
-            const float4 *row = (const float4 *)(T + tri_off(r < n ? r : 0));
-#pragma unroll
-            for (int q = 0; q < Q; q++) {
-                const int k = lane + 64 * q;
-                t[i][q] = k < len ? row[k] : make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-        }
-        float4 gq[Q];
-#pragma unroll
-        for (int q = 0; q < Q; q++) {
-            const int k = lane + 64 * q;
-            gq[q] = k < npc ? g4[k] : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-        float dot[R];
-#pragma unroll
-        for (int i = 0; i < R; i++) {
-            const int r = r0 + i * kCoarseWaves;
-            const float gr = r < n ? L.g[r] : 0.0f;
-            dot[i] = 0.0f;
-#pragma unroll
-            for (int q = 0; q < Q; q++) {
-                dot[i] += t[i][q].x * gq[q].x + t[i][q].y * gq[q].y + t[i][q].z * gq[q].z + t[i][q].w * gq[q].w;
-                acc[q].x += t[i][q].x * gr;
-                acc[q].y += t[i][q].y * gr;
-                acc[q].z += t[i][q].z * gr;
-                acc[q].w += t[i][q].w * gr;
-            }
-        }
-        if constexpr (R == 2) {
-            float d2 = 0.0f, d3 = 0.0f;
-            wave_sum4_f32(dot[0], dot[1], d2, d3);
-        } else {
-#pragma unroll
-            for (int i = 0; i < R; i += 4) wave_sum4_f32(dot[i], dot[i + 1], dot[i + 2], dot[i + 3]);
-        }
-        if (lane == 63) {
+        for (int q = 0; q < Q; q++) acc[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int r0 = w; r0 < n; r0 += R * kCoarseWaves) {
+            float4 t[R][Q];
 #pragma unroll
             for (int i = 0; i < R; i++) {
                 const int r = r0 + i * kCoarseWaves;
-                if (r < n) L.u[r] = dot[i];
+                const int len = r < n ? (r >> 2) + 1 : 0;      // pieces of row r
+                const float4 *row = (const float4 *)(T + tri_off(r < n ? r : 0));
+#pragma unroll
+                for (int q = 0; q < Q; q++) {
+                    const int k = lane + 64 * q;
+                    t[i][q] = k < len ? row[k] : make_float4(0.f, 0.f, 0.f, 0.f);
+                }
+            }
+            float4 gq[Q];
+#pragma unroll
+            for (int q = 0; q < Q; q++) {
+                const int k = lane + 64 * q;
+                gq[q] = k < npc ? g4[k] : make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+            float dot[R];
+#pragma unroll
+            for (int i = 0; i < R; i++) {
+                const int r = r0 + i * kCoarseWaves;
+                const float gr = r < n ? L.g[r] : 0.0f;
+                dot[i] = 0.0f;
+#pragma unroll
+                for (int q = 0; q < Q; q++) {
+                    dot[i] += t[i][q].x * gq[q].x + t[i][q].y * gq[q].y + t[i][q].z * gq[q].z + t[i][q].w * gq[q].w;
+                    acc[q].x += t[i][q].x * gr;
+                    acc[q].y += t[i][q].y * gr;
+                    acc[q].z += t[i][q].z * gr;
+                    acc[q].w += t[i][q].w * gr;
+                }
+            }
+            if constexpr (R == 2) {
+                float d2 = 0.0f, d3 = 0.0f;
+                wave_sum4_f32(dot[0], dot[1], d2, d3);
+            } else {
+#pragma unroll
+                for (int i = 0; i < R; i += 4) wave_sum4_f32(dot[i], dot[i + 1], dot[i + 2], dot[i + 3]);
+            }
+            if (lane == 63) {
+#pragma unroll
+                for (int i = 0; i < R; i++) {
+                    const int r = r0 + i * kCoarseWaves;
+                    if (r < n) L.u[r] = dot[i];
+                }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < Q; q++) {
+            const int k = lane + 64 * q, c = 4 * k;
+            if (k < npc) {
+                float *pw = part + (size_t)w * n;
+                if (c < n) pw[c] = acc[q].x;
+                if (c + 1 < n) pw[c + 1] = acc[q].y;
+                if (c + 2 < n) pw[c + 2] = acc[q].z;
+                if (c + 3 < n) pw[c + 3] = acc[q].w;
             }
         }
     }
-#pragma unroll
-    for (int q = 0; q < Q; q++) {
-        const int k = lane + 64 * q, c = 4 * k;
-        if (k < npc) {
-            float *pw = part + (size_t)w * n;
-            if (c < n) pw[c] = acc[q].x;
-            if (c + 1 < n) pw[c + 1] = acc[q].y;
-            if (c + 2 < n) pw[c + 2] = acc[q].z;
-            if (c + 3 < n) pw[c + 3] = acc[q].w;
-        }
-    }
     __syncthreads();
-    for (int c = tid; c < n; c += 64 * kCoarseWaves) {
+    for (int c = tid; c < n; c += 64 * NW) {
         float v = L.u[c];
 #pragma unroll
         for (int q = 0; q < kCoarseWaves; q++) v += part[(size_t)q * n + c];
@@ -1738,6 +1744,90 @@ __device__ __forceinline__ void c_dense_any(const CLev &L, const float *__restri
 }
 
 constexpr int kCoarsePre = 4;   // 16-byte pieces per thread loaded before the level-0 reduction (fetch calls)
+
+// The V-cycle of LDS levels lev(0 .. nlev-1), level 0 holding its right-hand
+// side and red-from-zero start, by a whole work-group.  The levels of at most
+// kCoarseWaveNodes nodes, from the first such level to the coarsest and back,
+// are run by the first wavefront alone.  dense(): solves the coarsest level
+// exactly (called by every thread) and returns true, or returns false.
+template <class Lev, class Dense>
+__device__ __forceinline__ void c_cycle(Lev lev, int nlev, float *sr, int px, int py, int sweeps, Dense dense, int tid,
+                                        int nt)
+{
+    int ls = 0;
+    while (ls < nlev) {
+        const CLev L = lev(ls);
+        if (L.NX * L.NY <= kCoarseWaveNodes) break;
+        ls++;
+    }
+    const int lb = ls < nlev - 1 ? ls : nlev - 1;           // levels below lb descend with the work-group
+    for (int l = 0; l < lb; l++) {
+        const CLev L = lev(l), C = lev(l + 1);
+        c_sweep(L, 1, tid, nt);
+        __syncthreads();
+        c_resid_red(L, sr, tid, nt);
+        __syncthreads();
+        c_restrict(L, sr, C, px, py, tid, nt);
+        __syncthreads();
+    }
+    if (ls < nlev) {
+        if (tid < 64) {
+            for (int l = ls; l < nlev - 1; l++) {
+                const CLev L = lev(l), C = lev(l + 1);
+                c_sweep(L, 1, tid, 64);
+                wave_sync();
+                c_resid_red(L, sr, tid, 64);
+                wave_sync();
+                c_restrict(L, sr, C, px, py, tid, 64);
+                wave_sync();
+            }
+        }
+        __syncthreads();
+        const bool solved = dense();
+        __syncthreads();
+        if (tid < 64) {
+            if (!solved) {
+                // coarsest: red-black sweeps (the first black completes the pre-smoothing)
+                const CLev L = lev(nlev - 1);
+                for (int sw = 0; sw < sweeps; sw++) {
+                    c_sweep(L, 1, tid, 64);
+                    wave_sync();
+                    c_sweep(L, 0, tid, 64);
+                    wave_sync();
+                }
+            }
+            for (int l = nlev - 2; l >= ls; l--) {
+                const CLev F = lev(l), C = lev(l + 1);
+                c_correct_red(F, C, sr, tid, 64);
+                wave_sync();
+                c_black_from(F, sr, tid, 64);
+                wave_sync();
+                c_sweep(F, 0, tid, 64);
+                wave_sync();
+            }
+        }
+        __syncthreads();
+    } else if (dense()) {
+        __syncthreads();
+    } else {
+        const CLev L = lev(nlev - 1);
+        for (int sw = 0; sw < sweeps; sw++) {
+            c_sweep(L, 1, tid, nt);
+            __syncthreads();
+            c_sweep(L, 0, tid, nt);
+            __syncthreads();
+        }
+    }
+    for (int l = lb - 1; l >= 0; l--) {
+        const CLev F = lev(l), C = lev(l + 1);
+        c_correct_red(F, C, sr, tid, nt);
+        __syncthreads();
+        c_black_from(F, sr, tid, nt);
+        __syncthreads();
+        c_sweep(F, 0, tid, nt);
+        __syncthreads();
+    }
+}
 
 // The levels from lg on: one 1024-thread work-group per instance, every level
 // in LDS.  Per level on the way down a black half-sweep, the red residuals,
@@ -1863,79 +1953,10 @@ __global__ __launch_bounds__(1024) void k_coarse(const Inst *insts, Tab t, Tab t
         }
     }
     __syncthreads();
-    // first level run by one wavefront (nlev when none is small enough)
-    int ls = 0;
-    while (ls < nlev && dims[0][ls] * dims[1][ls] > kCoarseWaveNodes) ls++;
-    const int lb = ls < nlev - 1 ? ls : nlev - 1;           // levels below lb descend with the work-group
-    for (int l = 0; l < lb; l++) {
-        const CLev L = lev(l), C = lev(l + 1);
-        c_sweep(L, 1, tid, nt);
-        __syncthreads();
-        c_resid_red(L, sr, tid, nt);
-        __syncthreads();
-        c_restrict(L, sr, C, px, py, tid, nt);
-        __syncthreads();
-    }
-    if (ls < nlev) {
-        if (tid < 64) {
-            for (int l = ls; l < nlev - 1; l++) {
-                const CLev L = lev(l), C = lev(l + 1);
-                c_sweep(L, 1, tid, 64);
-                wave_sync();
-                c_resid_red(L, sr, tid, 64);
-                wave_sync();
-                c_restrict(L, sr, C, px, py, tid, 64);
-                wave_sync();
-            }
-        }
-        if (a.dense_n) {
-            __syncthreads();
-            c_dense_any(lev(nlev - 1), a.ainv, a.dense_n, (float *)(lds + a.off_p), tid);
-            __syncthreads();
-        }
-        if (tid < 64) {
-            if (!a.dense_n) {
-                // coarsest: red-black sweeps (the first black completes the pre-smoothing)
-                const CLev L = lev(nlev - 1);
-                for (int sw = 0; sw < a.sweeps; sw++) {
-                    c_sweep(L, 1, tid, 64);
-                    wave_sync();
-                    c_sweep(L, 0, tid, 64);
-                    wave_sync();
-                }
-            }
-            for (int l = nlev - 2; l >= ls; l--) {
-                const CLev F = lev(l), C = lev(l + 1);
-                c_correct_red(F, C, sr, tid, 64);
-                wave_sync();
-                c_black_from(F, sr, tid, 64);
-                wave_sync();
-                c_sweep(F, 0, tid, 64);
-                wave_sync();
-            }
-        }
-        __syncthreads();
-    } else if (a.dense_n) {
-        c_dense_any(lev(nlev - 1), a.ainv, a.dense_n, (float *)(lds + a.off_p), tid);
-        __syncthreads();
-    } else {
-        const CLev L = lev(nlev - 1);
-        for (int sw = 0; sw < a.sweeps; sw++) {
-            c_sweep(L, 1, tid, nt);
-            __syncthreads();
-            c_sweep(L, 0, tid, nt);
-            __syncthreads();
-        }
-    }
-    for (int l = lb - 1; l >= 0; l--) {
-        const CLev F = lev(l), C = lev(l + 1);
-        c_correct_red(F, C, sr, tid, nt);
-        __syncthreads();
-        c_black_from(F, sr, tid, nt);
-        __syncthreads();
-        c_sweep(F, 0, tid, nt);
-        __syncthreads();
-    }
+    c_cycle(lev, nlev, sr, px, py, a.sweeps, [&]() {
+        if (a.dense_n) c_dense_any(lev(nlev - 1), a.ainv, a.dense_n, (float *)(lds + a.off_p), tid);
+        return a.dense_n != 0;
+    }, tid, nt);
     {
         const int N = dims[0][0] * dims[1][0];
         const float *u0 = (const float *)(lds + tab[0][0]);
@@ -1952,6 +1973,832 @@ void launch_coarse(const Inst *I, const Tab &t, int lds_bytes, const Tab &t0, Pa
         allowed = lds_bytes;
     }
     hipLaunchKernelGGL(k_coarse, dim3(t.n), dim3(1024), lds_bytes, s, I, t, t0, pt, fuse ? 1 : 0);
+}
+
+// ---------------------------------------------------------------------------
+// a whole solve of a small grid in one launch: every refinement pass of the
+// multigrid-preconditioned CG by one work-group, all levels and the CG's
+// vectors in LDS
+//
+// Launched kernel by kernel a V-cycle of a small grid is three launches and a
+// pass several more, bound by the launches and by k_coarse on one CU (42 us a
+// V-cycle at 81 x 30 nodes, 34 us at 64 x 64; here 19.3 and 19.3).  Arithmetic
+// and the order of every addition are those of k_mg_down, k_coarse, k_mg_up,
+// k_phi_update, k_resid64 and k_finalize, and the iterations a pass may take
+// follow the host's rule, so the potential is the same bit for bit.
+//
+// A thread owns the nodes it owns in the tile kernels for the CG's vectors and
+// dot products (512 threads a 32 x 32 tile, two nodes each, NT tiles in turn),
+// and for the smoothing of levels 0 and 1 up to NT (level 1: a quarter) pairs
+// of a red and a black node, whose LDS positions and neighbours it looks up
+// once: computed anew in every phase, as k_coarse does, they cost 70 of 85
+// instructions a node (64 x 64 nodes: 24 us a V-cycle so).  512 threads, as
+// those positions take more than the 128 registers that 1024 would have.
+// More than 4 tiles (positions in registers no longer, 35 us at 96 x 56, as
+// much as launched) stay with the launched kernels.
+//
+// Of a V-cycle's 40000 cycles at 64 x 64 nodes the coarsest level's solve takes
+// 15000 (a packed inverse of 131 KB through one CU), a smoothing phase of
+// level 0 1400, the CG step with its sums 10000.  A coarsest level of more than
+// kDenseOnePass nodes (41 x 15 for the paper's 80 x 30 trench, 0.76 MB) took
+// one CU 19 us an iteration.  There 16 more work-groups each keep the rows of
+// one part of c_dense in LDS, receive the right-hand side and return their
+// share of the dot products and their column sums, in c_dense's order (7 us);
+// words are exchanged as in the one-launch CG pass, with the same bounded
+// waits.  At 256 nodes both ways take the same.
+// ---------------------------------------------------------------------------
+
+typedef float vf4 __attribute__((ext_vector_type(4)));
+
+// Sums of R floats over the 64 lanes of a wavefront (all lanes active), the
+// sum of v[k] returned in lane k: partners 1, 2, 4, 8, 16, 32 lanes apart, the
+// narrow steps folding two values into one register (28 instructions for eight
+// values; a full tree for each takes 48).
+template <int CTRL> __device__ __forceinline__ float dpp_f32(float x)
+{
+    return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false));
+}
+template <int R> __device__ __forceinline__ float wave_sum_f32(float (&v)[R])
+{
+    static_assert(R == 2 || R == 4 || R == 8, "");
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int k = 0; k < R; k++) v[k] = dpp_f32<0xB1>(v[k]);            // quad_perm [1,0,3,2]
+#pragma unroll
+    for (int k = 0; k < R / 2; k++) {
+        const float e = v[2 * k], o = v[2 * k + 1];
+        v[k] = dpp_f32<0x4E>(lane & 1 ? o : e);                        // quad_perm [2,3,0,1]
+    }
+    const float p0 = v[0], p1 = v[R > 2 ? 1 : 0], p2 = v[R > 4 ? 2 : 0], p3 = v[R > 4 ? 3 : 0];
+    float x;
+    if constexpr (R == 8) {
+        const float e = lane & 2 ? p1 : p0, o = lane & 2 ? p3 : p2;
+        const float e4 = dpp_f32<0x12C>(e), o4 = dpp_f32<0x124>(o);    // row_ror:12 (from 4 lanes up), row_ror:4
+        x = lane & 4 ? o4 : e4;
+    } else {
+        x = dpp_f32<0x12C>(R == 4 && (lane & 2) ? p1 : p0);
+    }
+    x = dpp_f32<0x128>(x);                                             // row_ror:8
+    const auto h = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+    const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(w[0]) + __uint_as_float(w[1]);
+}
+
+// Words of the exchange: the right-hand side, then each work-group's dot
+// products (row r by work-group r % 16), then its column sums; whole 128-byte
+// lines each.
+__host__ __device__ inline int dense_line(int n) { return (n + 15) & ~15; }
+constexpr int kDenseDots = 48;
+__host__ __device__ inline int dense_dot_word(int n, int r) { return dense_line(n) + (r & 15) * kDenseDots + (r >> 4); }
+__host__ __device__ inline int dense_col_word(int n, int h) { return dense_line(n) * (1 + h) + 16 * kDenseDots; }
+__host__ __device__ inline int mg_words(int n) { return dense_col_word(n, kCoarseWaves); }
+int mg_solve_words(int n) { return mg_words(n); }
+
+// Two tagged words at an even place in one 16-byte store (a reader takes a
+// word at a time, and each carries its tag).
+__device__ __forceinline__ void st_pair(const __amdgpu_buffer_rsrc_t words, int at, float x, float y, unsigned epoch)
+{
+    typedef unsigned vu4 __attribute__((ext_vector_type(4)));
+    constexpr int SC1 = 16;            // written through to where other dies read it
+    __builtin_amdgcn_raw_buffer_store_b128(vu4{__float_as_uint(x), epoch, __float_as_uint(y), epoch}, words, 8 * at, 0, SC1);
+}
+
+
+constexpr int kDenseCols = (kDenseMaxNodes + kMgThreads - 1) / kMgThreads;   // columns a thread
+constexpr int kDenseRows = (kDenseMaxNodes + kCoarseWaves - 1) / kCoarseWaves;
+
+// Rows of work-group h of the dense solve in LDS, zero beyond each row's
+// length; then one answer per right-hand side until the solve ends.
+__device__ void mg_dense_helper(const Inst &I, const MgSolveArgs &m, int h, unsigned epoch, unsigned char *lds)
+{
+    const CoarseArgs &a = I.coarse;
+    const int n = a.dense_n, np = 4 * ((n + 3) >> 2), tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rows = (n - h + kCoarseWaves - 1) / kCoarseWaves;
+    float *T = (float *)lds, *g = T + rows * np;
+    const auto words = __builtin_amdgcn_make_buffer_rsrc(m.words, 0, 8 * mg_words(n), 0x00027000);
+    __shared__ float dots[kDenseDots];
+    __shared__ int state;              // 0 go on, 1 finished, 2 gave up
+    for (int k = tid; k < rows * np; k += blockDim.x) {
+        const int i = k / np, c = k - i * np, r = h + i * kCoarseWaves;
+        T[k] = c < 4 * ((r >> 2) + 1) ? a.ainv[tri_off(r) + c] : 0.f;
+    }
+    if (tid == 0) state = 0;
+    for (int k = n + tid; k < np; k += blockDim.x) g[k] = 0.f;
+    for (;; epoch++) {
+        __syncthreads();
+        // one lane watches one line, another one in each work-group, so that
+        // no line is polled by all of them while its stores arrive
+        if (tid == 0) {
+            const int k = min(16 * h, n - 1);
+            Patience pat;
+            while (((unsigned)(ld_agent(m.words + k) >> 32) & 0x7FFFFFFFu) != epoch) {
+                __builtin_amdgcn_s_sleep(2);
+                if (!pat.more(m.abort_word, m.wait)) break;
+            }
+        }
+        __syncthreads();
+        int mine = 0;
+        for (int k = tid; k < n; k += blockDim.x) {
+            Patience pat;
+            for (;;) {
+                const u64 w = ld_agent(m.words + k);
+                const unsigned t = (unsigned)(w >> 32);
+                g[k] = __uint_as_float((unsigned)w);
+                if (t == epoch) break;
+                if (t == (epoch | 0x80000000u)) { mine = 1; break; }
+                __builtin_amdgcn_s_sleep(4);
+                if (!pat.more(m.abort_word, m.wait)) { mine = 2; break; }
+            }
+        }
+        if (mine) atomicMax(&state, mine);
+        __syncthreads();
+        if (state) return;
+        // dot products: rows wv, wv + 8, ... of this wavefront, pieces of 16 bytes a lane
+        constexpr int RW = 8, Q = (kDenseMaxNodes + 255) / 256;
+        static_assert(kDenseRows <= RW * (kMgThreads / 64) && kDenseRows <= 64, "");
+        const vf4 *g4 = (const vf4 *)g;
+        float dot[RW];
+#pragma unroll
+        for (int i = 0; i < RW; i++) dot[i] = 0.f;
+#pragma unroll
+        for (int q = 0; q < Q; q++) {
+            const int k = lane + 64 * q;
+            const bool in = k < np / 4;
+            vf4 x = g4[in ? k : 0];
+            x = in ? x : vf4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < RW; i++) {
+                const int ri = wv + i * (kMgThreads / 64);
+                if (ri >= rows) continue;
+                vf4 t = ((const vf4 *)(T + ri * np))[in ? k : 0];
+                t = in ? t : vf4{0.f, 0.f, 0.f, 0.f};
+                dot[i] += t.x * x.x + t.y * x.y + t.z * x.z + t.w * x.w;
+            }
+        }
+        const float d = wave_sum_f32(dot);
+        const int mr = wv + lane * (kMgThreads / 64);
+        if (lane < RW && mr < rows) dots[mr] = d;
+        // sums of columns 2 tid and 2 tid + 1: rows in order
+        const float gl = lane < rows ? g[h + lane * kCoarseWaves] : 0.f;
+        const int c2 = min(2 * tid, np - 2);
+        float a0 = 0.f, a1 = 0.f;
+        if (2 * (tid & ~63) < n) {
+            for (int i0 = 0; i0 < rows; i0 += 8) {
+#pragma unroll
+                for (int k = 0; k < 8; k++) {
+                    // past the last row a zero times the last row
+                    const float gr = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(gl), i0 + k));
+                    const float2 t = *(const float2 *)(T + min(i0 + k, rows - 1) * np + c2);
+                    a0 += t.x * gr;
+                    a1 += t.y * gr;
+                }
+            }
+        }
+        if (2 * tid < n) st_pair(words, dense_col_word(n, h) + 2 * tid, a0, a1, epoch);
+        __syncthreads();
+        if (tid >= kMgThreads - 64 && 2 * lane < rows)
+            st_pair(words, dense_dot_word(n, h) + 2 * lane, dots[2 * lane], dots[2 * lane + 1], epoch);
+        // the answer leaves before the polls for the next right-hand side begin
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        // nothing comes before the rest of the V-cycle is done
+        __builtin_amdgcn_s_sleep(127);
+    }
+}
+
+// x, of which the compiler does not know that it has not changed: what
+// follows from it is computed where it is used and not carried around a loop.
+template <class X> __device__ __forceinline__ X opaque(X x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
+// Positions in a level's LDS arrays that one thread smooths: NP pairs of a red
+// and a black node (own -1: none, or fixed), the four neighbours x-1, x+1,
+// y-1, y+1 as 16-bit halves, for a red node also the coarse nodes its
+// prolongation reads (one where both indices are even).
+template <int NP> struct Pairs {
+    int red[NP], black[NP];
+    unsigned ra[NP], rb[NP], ba[NP], bb[NP], ca[NP], cb[NP];
+    unsigned one;
+
+    __device__ __forceinline__ void find(const uint8_t *f, int NX, int NY, int NXc, int NYc, int tid, int nt)
+    {
+        const int HW = (NY + 1) >> 1, n = NX * HW;
+        one = 0;
+#pragma unroll
+        for (int k = 0; k < NP; k++) {
+            const int q = tid + k * nt, i = q < n ? q / HW : 0, jj = q < n ? q - i * HW : 0;
+            const int jr = 2 * jj + (i & 1), jb = 2 * jj + ((i + 1) & 1);
+            const bool r = q < n && jr < NY, b = q < n && jb < NY;
+            const Nb x = nbs(i, r ? jr : 0, NX, NY), y = nbs(i, b ? jb : 0, NX, NY);
+            red[k] = r && !f[i * NY + jr] ? i * NY + jr : -1;
+            black[k] = b && !f[i * NY + jb] ? i * NY + jb : -1;
+            ra[k] = (x.im * NY + (r ? jr : 0)) | ((unsigned)(x.ip * NY + (r ? jr : 0)) << 16);
+            rb[k] = (i * NY + x.jm) | ((unsigned)(i * NY + x.jp) << 16);
+            ba[k] = (y.im * NY + (b ? jb : 0)) | ((unsigned)(y.ip * NY + (b ? jb : 0)) << 16);
+            bb[k] = (i * NY + y.jm) | ((unsigned)(i * NY + y.jp) << 16);
+            const int I = i >> 1, J = (r ? jr : 0) >> 1, I1 = wrap_hi(I + 1, NXc), J1 = wrap_hi(J + 1, NYc);
+            ca[k] = (I * NYc + J) | ((unsigned)(I1 * NYc + J) << 16);
+            cb[k] = (I * NYc + J1) | ((unsigned)(I1 * NYc + J1) << 16);
+            if (((i | jr) & 1) == 0) one |= 1u << k;
+        }
+    }
+    // u = (g + four of v) / 4 at the nodes own
+    __device__ __forceinline__ void sweep(const int (&own)[NP], const unsigned (&a)[NP], const unsigned (&b)[NP],
+                                          const float *v, const float *g, float *u) const
+    {
+        float s[NP];
+#pragma unroll
+        for (int k = 0; k < NP; k++) {
+            const int o = opaque(own[k]);
+            const unsigned x = opaque(a[k]), y = opaque(b[k]);
+            s[k] = g[o < 0 ? 0 : o];
+            s[k] += v[x & 0xFFFFu];
+            s[k] += v[x >> 16];
+            s[k] += v[y & 0xFFFFu];
+            s[k] += v[y >> 16];
+        }
+#pragma unroll
+        for (int k = 0; k < NP; k++) {
+            const int o = opaque(own[k]);
+            if (o >= 0) u[o] = s[k] * 0.25f;
+        }
+    }
+    __device__ __forceinline__ void resid_red(const float *u, const float *g, float *sr) const
+    {
+#pragma unroll
+        for (int k = 0; k < NP; k++) {
+            const int o = opaque(red[k]), p = o < 0 ? 0 : o;
+            const unsigned x = opaque(ra[k]), y = opaque(rb[k]);
+            float v = 4.0f * u[p];
+            v -= u[x & 0xFFFFu];
+            v -= u[x >> 16];
+            v -= u[y & 0xFFFFu];
+            v -= u[y >> 16];
+            v = g[p] - v;
+            if (o >= 0) sr[o] = v;
+        }
+    }
+    __device__ __forceinline__ void correct_red(const float *u, const float *e, float *sr) const
+    {
+#pragma unroll
+        for (int k = 0; k < NP; k++) {
+            const int o = opaque(red[k]), p = o < 0 ? 0 : o;
+            const unsigned x = opaque(ca[k]), y = opaque(cb[k]);
+            const float c = e[x & 0xFFFFu];
+            const float m = 0.25f * (c + e[x >> 16] + e[y & 0xFFFFu] + e[y >> 16]);
+            const float v = u[p] + ((one >> k) & 1 ? c : m);
+            if (o >= 0) sr[o] = v;
+        }
+    }
+};
+
+// Positions of the red residuals that up to NC coarse nodes of a thread
+// restrict (none, the position of a zero, for those outside a bounded axis).
+template <int NC> struct Restrict {
+    int own[NC];                       // -1: none, or fixed
+    unsigned c[NC], a[NC], b[NC], red; // centre, (-,-) and (-,+), (+,-) and (+,+); bit k: a red coarse node
+
+    __device__ __forceinline__ void find(const uint8_t *fc, int NX, int NY, int NXc, int NYc, int px, int py,
+                                         int none, int tid, int nt)
+    {
+        red = 0;
+#pragma unroll
+        for (int k = 0; k < NC; k++) {
+            const int q = tid + k * nt, I = q < NXc * NYc ? q / NYc : 0, J = q < NXc * NYc ? q - I * NYc : 0;
+            own[k] = q < NXc * NYc && !fc[q] ? q : -1;
+            auto at = [&](int di, int dj) -> unsigned {
+                int i = 2 * I + di, j = 2 * J + dj;
+                if (px) i = wrap_hi(wrap_lo(i, NX), NX);
+                else if (i < 0 || i >= NX) return none;
+                if (py) j = wrap_hi(wrap_lo(j, NY), NY);
+                else if (j < 0 || j >= NY) return none;
+                return i * NY + j;
+            };
+            c[k] = at(0, 0);
+            a[k] = at(-1, -1) | (at(-1, 1) << 16);
+            b[k] = at(1, -1) | (at(1, 1) << 16);
+            if (((I + J) & 1) == 0) red |= 1u << k;
+        }
+    }
+    __device__ __forceinline__ void run(const float *sr, float *g, float *u) const
+    {
+#pragma unroll
+        for (int k = 0; k < NC; k++) {
+            const int o = opaque(own[k]);
+            const unsigned x = opaque(a[k]), y = opaque(b[k]), z = opaque(c[k]);
+            float acc = 0.0f;
+            acc += 0.25f * sr[x & 0xFFFFu];
+            acc += 0.25f * sr[x >> 16];
+            acc += sr[z];
+            acc += 0.25f * sr[y & 0xFFFFu];
+            acc += 0.25f * sr[y >> 16];
+            if (o >= 0) {
+                g[o] = acc;
+                u[o] = (red >> k) & 1 ? acc * 0.25f : 0.0f;
+            }
+        }
+    }
+};
+
+template <int NT, bool HELP>
+__global__ __launch_bounds__(kMgThreads, 2) void k_mg_solve(const Inst *insts, MgSolveArgs m)
+{
+    const Inst &I = insts[0];
+    extern __shared__ __align__(16) unsigned char lds[];
+    unsigned epoch = m.epoch;
+    int *F = I.F;
+    double *S = I.S;
+    if (F[F_CONV]) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            F[F_SKIP] = 1;
+            F[F_DONE] = 1;
+        }
+        return;
+    }
+    if (HELP && blockIdx.x > 0) {
+        mg_dense_helper(I, m, (int)blockIdx.x - 1, epoch, lds);
+        return;
+    }
+    constexpr int NT1 = NT / 4 + 1, NC = (NT + 1) / 2 + 1;   // level 1: pairs and nodes a thread
+    const CoarseArgs &a = I.coarse;
+    const LevelDev L0 = I.lev[0];
+    const int NX = L0.NX, NY = L0.NY, N0 = NX * NY, N1 = a.NX[0] * a.NY[0];
+    const int tid = threadIdx.x, nt = kMgThreads, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    __shared__ int tab[5][kMaxLev];              // levels 1 ..: LDS offsets of u, g, mask; nodes along x and y
+    __shared__ double red[2][2][NT][8];          // [turn][quantity][tile][wavefront]
+    __shared__ double redv[256];
+    __shared__ int give_up;
+    // kept: after a word exchange they would be read from memory again
+    const int nlev = a.nlev, px = a.px, py = a.py, sweeps = a.sweeps, dense_n = a.dense_n;
+    const float *const ainv = a.ainv;
+    float *const part = (float *)(lds + a.off_p);
+    if (tid == 0) {
+        give_up = 0;
+        for (int l = 0; l < nlev; l++) {
+            tab[0][l] = a.off_u[l];
+            tab[1][l] = a.off_g[l];
+            tab[2][l] = a.off_f[l];
+            tab[3][l] = a.NX[l];
+            tab[4][l] = a.NY[l];
+        }
+    }
+    auto lev = [&](int l) __attribute__((always_inline)) {
+        CLev L;
+        L.u = (float *)(lds + tab[0][l]);
+        L.g = (float *)(lds + tab[1][l]);
+        L.f = (const uint8_t *)(lds + tab[2][l]);
+        L.NX = tab[3][l];
+        L.NY = tab[4][l];
+        return L;
+    };
+    float *const u0 = (float *)(lds + m.off_u), *const g0 = (float *)(lds + m.off_g);
+    float *const sr0 = (float *)(lds + m.off_s), *const sr1 = (float *)(lds + a.off_s);
+    uint8_t *const f0 = lds + m.off_f;
+    __syncthreads();
+    float *const u1 = (float *)(lds + tab[0][0]), *const g1 = (float *)(lds + tab[1][0]);
+    for (int k = tid; k < N0; k += nt) {
+        f0[k] = L0.fix[k];
+        u0[k] = g0[k] = sr0[k] = 0.0f;
+    }
+    if (tid == 0) sr0[N0] = 0.0f;
+    for (int k = tid; k < N1; k += nt) u1[k] = g1[k] = sr1[k] = 0.0f;
+    for (int l = 0; l < nlev; l++)
+        for (int k = tid; k < tab[3][l] * tab[4][l]; k += nt) lds[tab[2][l] + k] = a.fix[l][k];
+    __syncthreads();
+    Pairs<NT> P0;
+    Pairs<NT1> P1;
+    Restrict<NC> R0;
+    Restrict<1> R1;
+    P0.find(f0, NX, NY, tab[3][0], tab[4][0], tid, nt);
+    R0.find(lds + tab[2][0], NX, NY, tab[3][0], tab[4][0], px, py, N0, tid, nt);
+    if (nlev > 1) {
+        P1.find(lds + tab[2][0], tab[3][0], tab[4][0], tab[3][1], tab[4][1], tid, nt);
+        R1.find(lds + tab[2][1], tab[3][0], tab[4][0], tab[3][1], tab[4][1], px, py, (m.off_s - a.off_s) / 4 + N0, tid, nt);
+        const CLev C = lev(1);
+        for (int k = tid; k < C.NX * C.NY; k += nt) C.u[k] = C.g[k] = 0.0f;
+    }
+    // own nodes: row and column of slot q (0, 0 where the thread has none there)
+    unsigned freeb = 0, redb = 0, inb = 0;
+    auto own = [&](int q, int &i, int &j) __attribute__((always_inline)) {
+        const int tile = q >> 1, ti = tile / m.tiles_y, tj = tile - ti * m.tiles_y, t = opaque(tid);
+        i = ti * kMgTile + (t >> 5) + (kMgThreads / kMgTile) * (q & 1);
+        j = tj * kMgTile + (t & (kMgTile - 1));
+    };
+#pragma unroll
+    for (int q = 0; q < 2 * NT; q++) {
+        int i, j;
+        own(q, i, j);
+        const bool in = (q >> 1) < m.tiles && i < NX && j < NY;
+        if (in) inb |= 1u << q;
+        if (in && !f0[i * NY + j]) freeb |= 1u << q;
+        if (((i + j) & 1) == 0) redb |= 1u << q;
+    }
+    auto node = [&](int q) __attribute__((always_inline)) {
+        int i, j;
+        own(q, i, j);
+        return (inb >> q) & 1 ? i * NY + j : 0;
+    };
+    // the CG's p, s and e of slot q
+    auto vec = [&](int w, int q) __attribute__((always_inline)) -> float & {
+        return ((float *)(lds + m.off_v))[(w * 2 * NT + q) * kMgThreads + tid];
+    };
+    // the coarsest level exactly: false where it has no inverse
+    auto dense = [&]() __attribute__((always_inline)) -> bool {
+        const int n = dense_n;
+        if (!n) return false;
+        const CLev L = lev(nlev - 1);
+        if constexpr (!HELP) {
+            c_dense<1, 8, kMgThreads / 64>(L, ainv, n, part, tid);
+            return true;
+        }
+        const auto words = __builtin_amdgcn_make_buffer_rsrc(m.words, 0, 8 * mg_words(n), 0x00027000);
+        if (2 * tid < n) st_pair(words, 2 * tid, L.g[2 * tid], L.g[min(2 * tid + 1, n - 1)], epoch);
+        // an answer takes two trips through memory and the sums between them; 17 words a thread polled
+        // without a pause kept the answers from getting through (0.7 ms a V-cycle at 615 nodes)
+        __builtin_amdgcn_s_sleep(64);
+        auto collect = [&](auto cols_) __attribute__((always_inline)) {
+            constexpr int C = decltype(cols_)::value;
+            Patience pat;
+            float x[C][kCoarseWaves + 1];
+            for (;;) {
+                bool here = true;
+#pragma unroll
+                for (int k = 0; k < C; k++) {
+                    const int c = min(tid + k * nt, n - 1);
+#pragma unroll
+                    for (int q = 0; q <= kCoarseWaves; q++) {
+                        const u64 w = ld_agent(m.words + (q == 0 ? dense_dot_word(n, c) : dense_col_word(n, q - 1) + c));
+                        here = here && (unsigned)(w >> 32) == epoch;
+                        x[k][q] = __uint_as_float((unsigned)w);
+                    }
+                }
+                if (here) break;
+                __builtin_amdgcn_s_sleep(8);
+                if (!pat.more(m.abort_word, m.wait)) {
+                    give_up = 1;
+                    break;
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < C; k++) {
+                float v = x[k][0];
+#pragma unroll
+                for (int q = 1; q <= kCoarseWaves; q++) v += x[k][q];
+                if (tid + k * nt < n) L.u[tid + k * nt] = v;
+            }
+        };
+        if (64 * wave + (kDenseCols - 1) * nt < n) collect(Int<kDenseCols>{});
+        else collect(Int<1>{});
+        return true;
+    };
+    // levels 2 and below, or the coarsest level alone
+    auto deeper = [&](int l) __attribute__((always_inline)) {
+        auto sub = [&](int k) __attribute__((always_inline)) { return lev(l + k); };
+        c_cycle(sub, nlev - l, l == 0 ? sr1 : (float *)(lds + m.off_s2), px, py, sweeps, dense, tid, nt);
+    };
+    // V-cycle of the right-hand side g0 from the red-from-zero start in u0
+    auto cycle = [&]() __attribute__((always_inline)) {
+        P0.sweep(P0.black, P0.ba, P0.bb, u0, g0, u0);
+        __syncthreads();
+        P0.resid_red(u0, g0, sr0);
+        __syncthreads();
+        R0.run(sr0, g1, u1);
+        __syncthreads();
+        const int deep = nlev > 1;
+        if (deep) {
+            P1.sweep(P1.black, P1.ba, P1.bb, u1, g1, u1);
+            __syncthreads();
+            P1.resid_red(u1, g1, sr1);
+            __syncthreads();
+            const CLev C = lev(1);
+            R1.run(sr1, C.g, C.u);
+            __syncthreads();
+        }
+        deeper(deep);
+        if (deep) {
+            P1.correct_red(u1, lev(1).u, sr1);
+            __syncthreads();
+            P1.sweep(P1.black, P1.ba, P1.bb, sr1, g1, u1);
+            __syncthreads();
+            P1.sweep(P1.red, P1.ra, P1.rb, u1, g1, u1);
+            __syncthreads();
+        }
+        P0.correct_red(u0, u1, sr0);
+        __syncthreads();
+        P0.sweep(P0.black, P0.ba, P0.bb, sr0, g0, u0);
+        __syncthreads();
+        P0.sweep(P0.red, P0.ra, P0.rb, u0, g0, u0);
+        __syncthreads();
+    };
+    int turn = 0;
+    // totals of NQ quantities from the tile threads' sums v[quantity][tile]
+    auto totals = [&](double (&v)[2][NT], auto nq_, double (&out)[2]) {
+        constexpr int NQ = decltype(nq_)::value, TS = NQ == 2 ? 2 : 4;
+#pragma unroll
+        for (int r = 0; r < NT; r += TS) {
+            double x[4];
+#pragma unroll
+            for (int k = 0; k < 4; k++) x[k] = r + k % TS < NT ? v[k / TS][r + k % TS < NT ? r + k % TS : 0] : 0.0;
+            wave_sum4(x);
+            if (lane == 0) {
+#pragma unroll
+                for (int k = 0; k < 4; k++)
+                    if (r + k % TS < NT) red[turn][k / TS][r + k % TS][wave] = x[k];
+            }
+        }
+        __syncthreads();
+        double y[4] = {0.0, 0.0, 0.0, 0.0};
+        if (lane < m.tiles) {
+#pragma unroll
+            for (int w = 0; w < 8; w++)
+#pragma unroll
+                for (int q = 0; q < NQ; q++) y[q] += red[turn][q][lane][w];
+        }
+        wave_sum4(y);
+        // the other three groups of 64 partials are empty
+#pragma unroll
+        for (int q = 0; q < NQ; q++) out[q] = y[q] + 0.0 + 0.0 + 0.0;
+        turn ^= 1;
+    };
+    // float64 residual r = b - A phi into lev[0].g, ||r||^2 (virtual blocks of 4 rows x 64 columns)
+    const int vbx = (NY + kGridBX - 1) / kGridBX, nvb = vbx * ((NX + kGridBY - 1) / kGridBY);
+    auto residual = [&]() __attribute__((always_inline)) -> double {
+        for (int vb = wave; vb < nvb; vb += nt / 64) {
+            const int byb = vb / vbx, j = (vb - byb * vbx) * kGridBX + lane;
+            double x[4];
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                const int i = byb * kGridBY + r, n = i * NY + j;
+                x[r] = 0.0;
+                if (i >= NX || j >= NY) continue;
+                if (f0[n]) {
+                    L0.g[n] = 0.0f;
+                    continue;
+                }
+                const int im = wrap_lo(i - 1, NX), ip = wrap_hi(i + 1, NX);
+                const int jm = wrap_lo(j - 1, NY), jp = wrap_hi(j + 1, NY);
+                const double *phi = I.phi;
+                double s = 4.0 * phi[n];
+                if (!f0[im * NY + j]) s -= phi[im * NY + j];
+                if (!f0[ip * NY + j]) s -= phi[ip * NY + j];
+                if (!f0[i * NY + jm]) s -= phi[i * NY + jm];
+                if (!f0[i * NY + jp]) s -= phi[i * NY + jp];
+                const double res = I.b[n] - s;
+                L0.g[n] = (float)res;
+                x[r] = res * res;
+            }
+            wave_sum4(x);
+            if (lane == 0) redv[vb] = 0.0 + x[0] + x[1] + x[2] + x[3];
+        }
+        __syncthreads();
+        double y[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) y[k] = lane + 64 * k < nvb ? redv[lane + 64 * k] : 0.0;
+        wave_sum4(y);
+        return y[0] + y[1] + y[2] + y[3];
+    };
+
+    int total_it = F[F_ITER_TOT], passes = F[F_PASSES], iter1 = F[F_ITER1];
+    int chunk0 = m.chunk0, chunk1 = m.chunk1;
+    double rr64 = S[S_RR64];
+    const double bb = S[S_BB] > 0.0 ? S[S_BB] : 1.0, tol2 = I.rtol * I.rtol;
+    const double lo = I.eta_min * I.eta_min;
+    for (int pass = 0; pass < 64; pass++) {
+        if (pass > 0 && (!(rr64 < INFINITY) || total_it >= m.max_iter)) break;
+        const int K = max(1, min(min(pass > 0 ? chunk1 : chunk0, 128), m.max_iter - total_it));
+        // inner start: r, ||r||^2, the inner stop ratio (e, p and s start with the first step)
+        float r_[2 * NT];
+        double v[2][NT], t2[2];
+#pragma unroll
+        for (int q = 0; q < 2 * NT; q++) {
+            const float x = L0.g[node(q)];
+            r_[q] = (freeb >> q) & 1 ? x : 0.f;
+        }
+        auto sum_rr = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int r = 0; r < NT; r++) {
+                double x = 0.0;
+                x += (double)r_[2 * r] * (double)r_[2 * r];
+                x += (double)r_[2 * r + 1] * (double)r_[2 * r + 1];
+                v[0][r] = x;
+                v[1][r] = 0.0;
+            }
+            totals(v, Int<1>{}, t2);
+        };
+        sum_rr();
+        double eta2 = 0.09 * tol2 * bb / (rr64 > 0.0 ? rr64 : 1.0);
+        eta2 = eta2 < lo ? lo : (eta2 > 0.25 ? 0.25 : eta2);
+        const double rr0 = t2[0];
+        double rr = rr0, a_old = 0.0, g_old = 0.0, b_old = 0.0;
+        bool done = rr0 == 0.0;
+        int iter = 0;
+        passes++;
+        while (!done && iter < K) {
+            // one V-cycle of r: z (level 0's u)
+#pragma unroll
+            for (int q = 0; q < 2 * NT; q++) {
+                const int n = node(q);
+                if ((freeb >> q) & 1) {
+                    g0[n] = r_[q];
+                    u0[n] = (redb >> q) & 1 ? r_[q] * 0.25f : 0.0f;
+                }
+            }
+            __syncthreads();
+            cycle();
+            if (HELP) {
+                epoch++;
+                if (give_up) {
+                    // the passes before this one stand; the host goes on from there
+                    if (tid == 0) __hip_atomic_store(m.abort_word, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    return;
+                }
+            }
+            // w = A z, r.z and w.z; the step's vectors are on their way meanwhile
+            float p_[2 * NT], s_[2 * NT], e_[2 * NT], w_[2 * NT], z_[2 * NT];
+#pragma unroll
+            for (int q = 0; q < 2 * NT; q++) {
+                const int n = node(q);
+                p_[q] = vec(0, q);
+                s_[q] = vec(1, q);
+                e_[q] = vec(2, q);
+                r_[q] = g0[n];
+            }
+#pragma unroll
+            for (int q = 0; q < 2 * NT; q++) {
+                int i, j;
+                own(q, i, j);
+                const bool f = (freeb >> q) & 1;
+                i = f ? i : 0;
+                j = f ? j : 0;
+                const Nb nb = nbs(i, j, NX, NY);
+                const float z = u0[i * NY + j];
+                float t = 4.0f * z;
+                t -= u0[nb.im * NY + j];
+                t -= u0[nb.ip * NY + j];
+                t -= u0[i * NY + nb.jm];
+                t -= u0[i * NY + nb.jp];
+                z_[q] = f ? z : 0.f;
+                w_[q] = f ? t : 0.f;
+                r_[q] = f ? r_[q] : 0.f;
+                // before the first step the vectors hold an earlier pass
+                e_[q] = iter > 0 ? e_[q] : 0.f;
+            }
+#pragma unroll
+            for (int r = 0; r < NT; r++) {
+                double x = 0.0, y = 0.0;
+#pragma unroll
+                for (int q = 2 * r; q < 2 * r + 2; q++) {
+                    x += (double)r_[q] * (double)z_[q];
+                    y += (double)w_[q] * (double)z_[q];
+                }
+                v[0][r] = x;
+                v[1][r] = y;
+            }
+            totals(v, Int<2>{}, t2);
+            // one CG step
+            const double gamma = t2[0], delta = t2[1];
+            const bool first = iter == 0;
+            double al, be = 0.0;
+            if (first) {
+                al = gamma / delta;
+            } else {
+                be = gamma / g_old;
+                al = gamma / (delta - be * gamma / a_old);
+            }
+            if (!(al > 0.0 && al < INFINITY && be < INFINITY)) {
+                done = true;
+                break;
+            }
+            const float alpha = (float)al, beta = (float)be;
+#pragma unroll
+            for (int q = 0; q < 2 * NT; q++) {
+                const float pn = first ? z_[q] : z_[q] + beta * p_[q];
+                const float sn = first ? w_[q] : w_[q] + beta * s_[q];
+                const bool f = (freeb >> q) & 1;
+                vec(0, q) = pn;
+                vec(1, q) = sn;
+                vec(2, q) = e_[q] + alpha * pn;
+                r_[q] = f ? r_[q] - alpha * sn : 0.f;
+            }
+            sum_rr();
+            rr = t2[0];
+            iter++;
+            total_it++;
+            if (passes == 1) iter1 = iter;
+            if (rr <= eta2 * rr0) done = true;
+            a_old = al;
+            b_old = be;
+            g_old = gamma;
+        }
+        // end of the pass: phi += e, float64 residual and convergence test
+#pragma unroll
+        for (int q = 0; q < 2 * NT; q++) {
+            const int n = node(q);
+            if (((freeb >> q) & 1) && iter > 0) I.phi[n] += (double)vec(2, q);
+        }
+        __syncthreads();
+        rr64 = residual();
+        const bool conv = rr64 <= tol2 * bb;
+        const int next = !done ? min(2 * K, 128) : max(1, iter);
+        if (pass > 0) chunk1 = next;
+        else chunk0 = next;
+        if (tid == 0) {
+            S[S_ETA2] = eta2;
+            S[S_RR0] = rr0;
+            S[S_RR] = rr;
+            S[S_CG_ALPHA] = a_old;
+            S[S_CG_BETA] = b_old;
+            S[S_CG_GAMMA] = g_old;
+            S[S_RR64] = rr64;
+            F[F_SKIP] = 0;
+            F[F_DONE] = done ? 1 : 0;
+            F[F_ITER] = iter;
+            F[F_ITER_TOT] = total_it;
+            F[F_PASSES] = passes;
+            F[F_ITER1] = iter1;
+            F[F_CONV] = conv ? 1 : 0;
+            F[F_CHUNK0] = chunk0;
+            F[F_CHUNK1] = chunk1;
+        }
+        __syncthreads();
+        if (conv) break;
+    }
+    // the helpers' last word
+    if (HELP)
+        for (int c = tid; c < dense_n; c += nt) st_agent(m.words + c, tagged(0u, epoch | 0x80000000u));
+}
+
+static const void *mg_solve_kernel(const MgPlan &p)
+{
+    if (p.help) return p.R == 2 ? (const void *)k_mg_solve<2, true> : (const void *)k_mg_solve<4, true>;
+    return p.R == 2 ? (const void *)k_mg_solve<2, false> : (const void *)k_mg_solve<4, false>;
+}
+
+MgPlan mg_solve_plan(int NX, int NY, const CoarseArgs &c, int lg)
+{
+    MgPlan p{};
+    p.tiles_y = (NY + kMgTile - 1) / kMgTile;
+    p.tiles = p.tiles_y * ((NX + kMgTile - 1) / kMgTile);
+    const int nvb = ((NY + kGridBX - 1) / kGridBX) * ((NX + kGridBY - 1) / kGridBY);
+    if (lg != 1 || p.tiles > 4 || nvb > 256) return p;
+    p.R = p.tiles <= 2 ? 2 : 4;
+    // what a thread's registers hold of levels 0 and 1
+    if (NX * ((NY + 1) / 2) > p.R * kMgThreads || c.NX[0] * ((c.NY[0] + 1) / 2) > (p.R / 4 + 1) * kMgThreads ||
+        c.NX[0] * c.NY[0] > ((p.R + 1) / 2 + 1) * kMgThreads || (c.nlev > 1 && c.NX[1] * c.NY[1] > kMgThreads))
+        return p;
+    const int N0 = NX * NY;
+    int off = (c.lds_bytes + 15) & ~15;
+    p.off_u = off;
+    off += (N0 * 4 + 15) & ~15;
+    p.off_g = off;
+    off += (N0 * 4 + 15) & ~15;
+    p.off_s = off;
+    off += ((N0 + 1) * 4 + 15) & ~15;
+    p.off_s2 = off;
+    if (c.nlev > 1) off += (c.NX[1] * c.NY[1] * 4 + 15) & ~15;
+    p.off_f = off;
+    off += (N0 + 15) & ~15;
+    p.off_v = off;
+    off += 3 * 2 * p.R * kMgThreads * 4;
+    p.help = c.dense_n > kDenseOnePass ? kCoarseWaves : 0;
+    if (p.help) {
+        const int np = 4 * ((c.dense_n + 3) >> 2);
+        off = std::max(off, (kDenseRows + 1) * np * 4);
+    }
+    p.lds = off;
+    if (off > 150 * 1024) return p;
+    const void *f = mg_solve_kernel(p);
+    if (off > 64 * 1024 && hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, off) != hipSuccess) {
+        (void)hipGetLastError();
+        return p;
+    }
+    int dev = 0, cus = 0, per = 0;
+    p.ok = hipGetDevice(&dev) == hipSuccess &&
+           hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+           hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, f, kMgThreads, off) == hipSuccess && per * cus > p.help;
+    return p;
+}
+
+hipError_t launch_mg_solve(const Inst *I, const MgPlan &p, MgSolveArgs m, hipStream_t s)
+{
+    m.tiles = p.tiles;
+    m.tiles_y = p.tiles_y;
+    m.off_u = p.off_u;
+    m.off_g = p.off_g;
+    m.off_s = p.off_s;
+    m.off_f = p.off_f;
+    m.off_s2 = p.off_s2;
+    m.off_v = p.off_v;
+    m.help = p.help;
+    const void *f = mg_solve_kernel(p);
+    void *args[] = {&I, &m};
+    if (p.help) return hipLaunchCooperativeKernel(f, dim3(1 + p.help), dim3(kMgThreads), args, p.lds, s);
+    return hipLaunchKernel(f, dim3(1), dim3(kMgThreads), args, p.lds, s);
 }
 
 // ---------------------------------------------------------------------------

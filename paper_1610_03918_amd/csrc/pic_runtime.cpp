@@ -258,6 +258,7 @@ struct InstHost {
     std::vector<float> ainvh;               // coarsest-level inverse (host copy kept until uploaded)
     float *d_ainv = nullptr;
     unsigned long long *d_cg_rim = nullptr, *d_cg_slots = nullptr;   // exchanges of a one-launch CG pass
+    unsigned long long *d_mg_words = nullptr;                        // and of a one-launch multigrid solve
     bool dense = false;                     // the coarsest level is solved with d_ainv
     Inst dev{};
     pic_solve_info last{};
@@ -321,9 +322,11 @@ struct pic_ctx {
     hipStream_t bin_stream = nullptr;
     hipEvent_t ev_bin_go = nullptr, ev_bin_done = nullptr;
     bool bin_pending = false;
-    // a context of one instance without multigrid runs each CG pass as one
-    // launch where the grid fits the device (cg.ok); epochs number its exchanges
+    // a context of one instance runs a small grid's multigrid solve (mgs.ok),
+    // or without multigrid each CG pass (cg.ok), as one launch where it fits
+    // the device; epochs number the exchanges
     CgPlan cg{};
+    MgPlan mgs{};
     unsigned cg_epoch = 1;
     int cg_mode = 1;               // 1 one launch, 0 the launched kernels, -1 one launch that does not wait (tests)
     // graphs
@@ -477,6 +480,7 @@ void carve_inst(InstHost *h, Carve &w, const Layout &L, const pic_config *cfg, c
         rim = w.take<unsigned long long>(cg_rim_words(L.NX, L.NY));
         slots = w.take<unsigned long long>(kCgSlotWords);
     }
+    unsigned long long *words = L.mg && L.lg == 1 && L.dense_n ? w.take<unsigned long long>((size_t)mg_solve_words(L.dense_n)) : nullptr;
     unsigned *counts[2], *offs[2], *curs[2], *boff[2];
     int4 *table[2];
     long long *info[2];
@@ -501,6 +505,7 @@ void carve_inst(InstHost *h, Carve &w, const Layout &L, const pic_config *cfg, c
     h->d_ainv = ainv;
     h->d_cg_rim = rim;
     h->d_cg_slots = slots;
+    h->d_mg_words = words;
     for (int l = 0; l < L.nlev; l++) {
         h->d_fix[l] = fix[l];
         h->d_u[l] = u[l];
@@ -928,6 +933,26 @@ pic_status do_sweep_solve(pic_ctx *c, int kind, const double *guess)
     return PIC_OK;
 }
 
+// Every pass of a small grid's multigrid solve as one launch.  False where
+// the context does not run it so, or the runtime refuses the launch.
+bool run_mg_solve(pic_ctx *c, int max_iter)
+{
+    if (!c->mgs.ok || !c->cg_mode) return false;
+    MgSolveArgs m{};
+    m.chunk0 = c->pass_chunk[0];
+    m.chunk1 = c->pass_chunk[1];
+    m.max_iter = max_iter;
+    m.epoch = c->cg_epoch & 0x3FFFFFFFu;
+    m.words = c->in[0].d_mg_words;
+    m.abort_word = c->d_F + F_CGABORT;
+    m.wait = c->cg_mode < 0 ? -1 : kCgWait;
+    c->cg_epoch += kMgEpochs;
+    if (launch_mg_solve(c->d_inst, c->mgs, m, c->stream) == hipSuccess) return true;
+    (void)hipGetLastError();
+    c->cg_mode = 0;
+    return false;
+}
+
 pic_status do_solve(pic_ctx *c, int kind, const double *guess)
 {
     if (c->sweep_solver) return do_sweep_solve(c, kind, guess);
@@ -949,8 +974,23 @@ pic_status do_solve(pic_ctx *c, int kind, const double *guess)
     if (plain_cg) {
         if ((st = read_flags(c, S, F)) != PIC_OK) return st;
         have = true;
+    } else if (run_mg_solve(c, max_iter)) {
+        if ((st = read_flags(c, S, F)) != PIC_OK) return st;
+        have = true;
+        if (F[F_CGABORT]) {
+            // gave up waiting: the passes that ended stand, the launched
+            // kernels go on from there, and run every later solve
+            c->cg_mode = 0;
+            F[F_CGABORT] = 0;
+            HIPCHK(c, hipMemcpyAsync(c->d_F, F.data(), F.size() * sizeof(int), hipMemcpyHostToDevice, c->stream));
+            HIPCHK(c, hipStreamSynchronize(c->stream));
+        }
+        if (F[F_PASSES] > 0) {
+            c->pass_chunk[0] = F[F_CHUNK0];
+            c->pass_chunk[1] = F[F_CHUNK1];
+        }
     }
-    for (int pass = 0; pass < 64; pass++) {
+    for (int pass = have ? F[F_PASSES] : 0; pass < 64; pass++) {
         int most = 0;
         if (have) {
             bool all = true;
@@ -1346,6 +1386,7 @@ pic_status init_instance(pic_ctx *c, int k, const pic_config *cfg, const pic_buf
         HIPCHK(c, hipMemsetAsync(h.d_cg_rim, 0, sizeof(unsigned long long) * cg_rim_words(L.NX, L.NY), s));
         HIPCHK(c, hipMemsetAsync(h.d_cg_slots, 0xFF, sizeof(unsigned long long) * kCgSlotWords, s));
     }
+    if (h.d_mg_words) HIPCHK(c, hipMemsetAsync(h.d_mg_words, 0, sizeof(unsigned long long) * mg_solve_words(L.dense_n), s));
     HIPCHK(c, hipMemsetAsync(h.d_counts[0], 0, sizeof(unsigned) * L.ntiles, s));
     HIPCHK(c, hipMemsetAsync(h.d_counts[1], 0, sizeof(unsigned) * L.ntiles, s));
     HIPCHK(c, hipMemsetAsync(buf->phi, 0, sizeof(double) * (size_t)L.NX * L.NY, s));
@@ -1473,7 +1514,11 @@ pic_status batch_init(int n, const pic_config *cfgs, const pic_buffers *bufs, vo
         c->sweep_solver = sk;
     }
     build_tabs(c);
-    if (n == 1 && !c->in[0].L.mg && !c->sweep_solver) c->cg = cg_plan(c->in[0].L.NX, c->in[0].L.NY);
+    if (n == 1 && !c->sweep_solver) {
+        const Layout &L = c->in[0].L;
+        if (L.mg) c->mgs = mg_solve_plan(L.NX, L.NY, c->in[0].dev.coarse, L.lg);
+        else c->cg = cg_plan(L.NX, L.NY);
+    }
     c->step = 0;
     pic_status st = upload_vwindow(c, 0);
     if (st != PIC_OK) return st;

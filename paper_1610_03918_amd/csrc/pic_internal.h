@@ -72,12 +72,34 @@ enum {
 // outside the window of conductor potentials (it then reads row 0).
 constexpr int kErrVWindow = 1;
 
+// A pointer into device memory kept in a descriptor.  A pointer that a kernel
+// reads from memory could point anywhere, LDS included: its accesses would be
+// flat ones, which count as LDS accesses too, so that every wait for LDS or for
+// a scalar load would also wait for the loads in flight.  This one's accesses
+// are known to be of device memory.
+template <class T> struct Dev {
+    uintptr_t at;
+    __host__ __device__ Dev &operator=(T *p)
+    {
+        at = (uintptr_t)p;
+        return *this;
+    }
+    __host__ __device__ operator T *() const
+    {
+#ifdef __HIP_DEVICE_COMPILE__
+        return (T *)(__attribute__((address_space(1))) T *)at;
+#else
+        return (T *)at;
+#endif
+    }
+};
+
 struct LevelDev {
     int NX, NY;
-    float *u;          // correction (level 0: z at the start of the V-cycle)
-    float *uo;         // pre-smoothed level from the down half-cycle (fine levels; = u on LDS levels)
-    float *g;          // right-hand side (level 0: r)
-    const uint8_t *fix;
+    Dev<float> u;          // correction (level 0: z at the start of the V-cycle)
+    Dev<float> uo;         // pre-smoothed level from the down half-cycle (fine levels; = u on LDS levels)
+    Dev<float> g;          // right-hand side (level 0: r)
+    Dev<const uint8_t> fix;
 };
 
 struct CoarseArgs {
@@ -85,13 +107,13 @@ struct CoarseArgs {
     int NX[kMaxLev], NY[kMaxLev];
     int off_u[kMaxLev], off_g[kMaxLev], off_f[kMaxLev]; // LDS byte offsets
     int off_s;                     // LDS scratch: one float per node of the first LDS level
-    const uint8_t *fix[kMaxLev];   // global masks of those levels
-    float *u_top;                  // global u of the first LDS level (output)
-    const float *g_top;            // global g of the first LDS level (input)
+    Dev<const uint8_t> fix[kMaxLev];   // global masks of those levels
+    Dev<float> u_top;                  // global u of the first LDS level (output)
+    Dev<const float> g_top;            // global g of the first LDS level (input)
     int px, py;
     int sweeps;                    // red-black pairs on the coarsest level
     int lds_bytes;
-    const float *ainv;             // inverse of the coarsest level's operator (packed lower triangle), or null
+    Dev<const float> ainv;             // inverse of the coarsest level's operator (packed lower triangle), or null
     int dense_n;                   // its node count n when the coarsest level is solved exactly, else 0
     int off_p;                     // LDS: kCoarseWaves x n column partial sums of the exact solve
 };
@@ -113,19 +135,19 @@ struct Inst {
     Geom g;
     int nlev, lg, mg;
     LevelDev lev[kMaxLev];
-    const uint8_t *node_cond, *cell_cond;
-    double *phi, *b, *phi_prev;
-    double *phi2;                  // second potential buffer of the Jacobi sweeps (solver 2)
-    unsigned long long *rho[2];
-    float *e, *p[2], *q;
-    float *z;                      // preconditioned residual of the CG (level-0 u)
+    Dev<const uint8_t> node_cond, cell_cond;
+    Dev<double> phi, b, phi_prev;
+    Dev<double> phi2;                  // second potential buffer of the Jacobi sweeps (solver 2)
+    Dev<unsigned long long> rho[2];
+    Dev<float> e, p[2], q;
+    Dev<float> z;                      // preconditioned residual of the CG (level-0 u)
     // multigrid-preconditioned CG in the Chronopoulos-Gear form: residual
     // pair (lev[0].g, cg_r1), s = A p pair, w = A z
-    float *cg_r1, *cg_s[2], *cg_w;
-    float4 *E4;
-    double *S;
-    int *F;
-    unsigned long long *surf;
+    Dev<float> cg_r1, cg_s[2], cg_w;
+    Dev<float4> E4;
+    Dev<double> S;
+    Dev<int> F;
+    Dev<unsigned long long> surf;
     double qcharge;                // weight * 2^-32
     int charge_mode, charge_row, sjl, sjh;
     double sden;
@@ -143,8 +165,8 @@ struct Tab {
 };
 
 struct HitLog {
-    int32_t *rec;                  // capacity x 6 int32 (pic_hit layout)
-    unsigned long long *count;
+    Dev<int32_t> rec;                  // capacity x 6 int32 (pic_hit layout)
+    Dev<unsigned long long> count;
     long long capacity;
     int species_mask;
 };
@@ -152,22 +174,22 @@ struct HitLog {
 struct PushArgs {
     Geom g;
     int TX, TY, lx, ly, tiles_y, H, WX, WY;
-    const uint8_t *cell_cond;
-    const float4 *E4;              // per cell: (Ex,Ey) at corners 00,10 then 01,11
-    int32_t *cell[2];              // both storage sets; info[7] selects the one in use
-    float *ox[2], *oy[2], *vx[2], *vy[2];
-    const int4 *table;             // (tile, start, end, 0) per block
-    const long long *info;         // [1] table entries, [2 + set] slots, [7] set in use
-    unsigned long long *rho;
+    Dev<const uint8_t> cell_cond;
+    Dev<const float4> E4;              // per cell: (Ex,Ey) at corners 00,10 then 01,11
+    Dev<int32_t> cell[2];              // both storage sets; info[7] selects the one in use
+    Dev<float> ox[2], oy[2], vx[2], vy[2];
+    Dev<const int4> table;             // (tile, start, end, 0) per block
+    Dev<const long long> info;         // [1] table entries, [2 + set] slots, [7] set in use
+    Dev<unsigned long long> rho;
     float qdt, dtf, hq;            // alpha dt, dt, alpha dt / 2 (float32)
     int box_i_top, box_j_lo, box_j_hi;
     int species, inst;
-    unsigned long long *tally;     // 9 counters of this species
-    unsigned long long *surf;      // trench-bottom hits per column, or null
-    unsigned long long *iad;       // bottom-impact angle histogram (ions), or null
+    Dev<unsigned long long> tally;     // 9 counters of this species
+    Dev<unsigned long long> surf;      // trench-bottom hits per column, or null
+    Dev<unsigned long long> iad;       // bottom-impact angle histogram (ions), or null
     HitLog log;
-    const long long *step;         // device step counter (hit records)
-    unsigned long long *fallbacks;
+    Dev<const long long> step;         // device step counter (hit records)
+    Dev<unsigned long long> fallbacks;
     int recycle_rows;              // > 0: lost ions of this species are recycled into rows 0 .. recycle_rows-1
                                    // (by k_recycle, after the push)
     unsigned recycle_key[2];
@@ -179,33 +201,33 @@ struct PushArgs {
 // that are appended to species 0 (the set in use), after its binned slots.
 struct SeeArgs {
     Geom g;
-    const int32_t *rec;                 // hit ring, capacity x 6 int32 (pic_hit layout)
-    const unsigned long long *log_count;// records written so far
+    Dev<const int32_t> rec;                 // hit ring, capacity x 6 int32 (pic_hit layout)
+    Dev<const unsigned long long> log_count;// records written so far
     long long log_capacity;
-    unsigned long long *misc;           // [0] records consumed, [1] slots asked this step,
+    Dev<unsigned long long> misc;           // [0] records consumed, [1] slots asked this step,
                                         // [2] electrons appended, [3] dropped
     unsigned thresh[2];                 // floor(yield_s 2^24)
     double vth;
     unsigned key[2];
-    int32_t *cell[2];                   // species 0, both storage sets; info[7] selects
-    float *ox[2], *oy[2], *vx[2], *vy[2];
-    long long *info;                    // species 0: [1] push blocks, [2 + set] slots,
+    Dev<int32_t> cell[2];                   // species 0, both storage sets; info[7] selects
+    Dev<float> ox[2], oy[2], vx[2], vy[2];
+    Dev<long long> info;                    // species 0: [1] push blocks, [2 + set] slots,
                                         // [4] slots binned, [5] blocks of the binned slots, [7] set
-    int4 *table;                        // species 0 push table
+    Dev<int4> table;                        // species 0 push table
     long long capacity;
     int chunk;
-    unsigned long long *rho;            // charge of species 0
+    Dev<unsigned long long> rho;            // charge of species 0
 };
 
 struct BinArgs {
     int nx, ny;
     int lx, ly, tiles_y, ntiles, chunk;
-    unsigned long long *bad;       // count of slots with a code outside the grid
-    int32_t *cell[2];              // both storage sets: source info[7], destination the other
-    float *ox[2], *oy[2], *vx[2], *vy[2];
-    unsigned *counts, *offsets, *cursor, *boff;
-    int4 *table;
-    long long *info;               // [0] alive, [1] table entries, [2 + set] slots, [7] set in use
+    Dev<unsigned long long> bad;       // count of slots with a code outside the grid
+    Dev<int32_t> cell[2];              // both storage sets: source info[7], destination the other
+    Dev<float> ox[2], oy[2], vx[2], vy[2];
+    Dev<unsigned> counts, offsets, cursor, boff;
+    Dev<int4> table;
+    Dev<long long> info;               // [0] alive, [1] table entries, [2 + set] slots, [7] set in use
 };
 
 // Reduction partials: one float64 per block and quantity.
@@ -249,12 +271,13 @@ void launch_update_red0(const Inst *I, const Tab &t, int knew, Part pt, hipStrea
 void launch_coarse(const Inst *I, const Tab &t, int lds_bytes, const Tab &t0, Part pt, bool fuse, hipStream_t s);
 // fused fine-level V-cycle halves (tables of 32 x 32 tiles of level l)
 constexpr int kMgTileHost = 32;
-// down: mode 0 level >= 1, mode 1 level 0 at the start of an inner pass,
-// mode 2 level 0 after a CG step; par = buffer of the r / s pairs read
-void launch_mg_down(const Inst *I, const Tab &t, int level, int mode, int par, Part pt, hipStream_t s);
-void launch_mg_up(const Inst *I, const Tab &t, int level, int par, Part pt, hipStream_t s);
-// levels l and l + 1 in one launch (table of level-(l+1) tiles); down or up
-void launch_mg_pair(const Inst *I, const Tab &t, int level, bool down, hipStream_t s);
+// level 0, down: mode 1 at the start of an inner pass, modes 2 and 3 after a
+// CG step; par = buffer of the r / s pairs read
+void launch_mg_down(const Inst *I, const Tab &t, int mode, int par, Part pt, hipStream_t s);
+void launch_mg_up(const Inst *I, const Tab &t, int par, Part pt, hipStream_t s);
+// level l >= 1, down or up: the pairs (l, l + 1) of tp (tiles of level l + 1)
+// and the single levels of tf
+void launch_mg_mid(const Inst *I, const Tab &tp, const Tab &tf, int level, bool down, hipStream_t s);
 // One refinement pass of plain CG on a single instance as one launch
 // (cg_persist.hip).  Virtual blocks are the 4 x 64 node blocks of the grid
 // kernels; up to kCgSingleVb of them run in one work-group.

@@ -169,30 +169,68 @@ __device__ void apply_op(const Inst &I, int op, double t0, double t1)
 // block (others pass through): per-thread sums in a fixed order, then one
 // per wavefront into sh[q][0 .. 3].  The caller synchronises and adds the
 // four, so every kernel that reduces the same partials gets the same totals.
+// RND loads a thread and quantity are in flight.
+template <int RND = 8> struct PartialSums {
+    double v[2][RND];
+
+    // the first round's loads
+    __device__ __forceinline__ void load(const Part &pt, int b0, int b1, int nq, int tid)
+    {
+#pragma unroll
+        for (int r = 0; r < RND; r++) {
+            const int k = b0 + r * 256 + tid;
+            v[0][r] = tid < 256 && k < b1 ? pt.p[k] : 0.0;
+            v[1][r] = tid < 256 && nq > 1 && k < b1 ? pt.p[pt.stride + k] : 0.0;
+        }
+    }
+    __device__ __forceinline__ void sum(const Part &pt, int b0, int b1, int nq, double (*sh)[4], int tid)
+    {
+        if (tid >= 256) return;
+        const int lane = tid & 63, wid = tid >> 6;
+        double s[2] = {0.0, 0.0};
+        for (int k0 = b0;;) {
+#pragma unroll
+            for (int r = 0; r < RND; r++) {
+                s[0] += v[0][r];
+                s[1] += v[1][r];
+            }
+            k0 += RND * 256;
+            if (k0 >= b1) break;
+            load(pt, k0, b1, nq, tid);
+        }
+        for (int q = 0; q < 2; q++) {
+            const double w = wave_sum(s[q]);
+            if (lane == 0) sh[q][wid] = w;
+        }
+    }
+};
 __device__ __forceinline__ void partial_sums_256(const Part &pt, int b0, int b1, int nq, double (*sh)[4], int tid)
 {
-    if (tid >= 256) return;
-    const int lane = tid & 63, wid = tid >> 6;
-    double s[2] = {0.0, 0.0};
-    // loads of a round issued together
-    for (int k0 = b0; k0 < b1; k0 += 8 * 256) {
-        double v[2][8];
-#pragma unroll
-        for (int r = 0; r < 8; r++) {
-            const int k = k0 + r * 256 + tid;
-            v[0][r] = k < b1 ? pt.p[k] : 0.0;
-            v[1][r] = (nq > 1 && k < b1) ? pt.p[pt.stride + k] : 0.0;
-        }
-#pragma unroll
-        for (int r = 0; r < 8; r++) {
-            s[0] += v[0][r];
-            s[1] += v[1][r];
-        }
-    }
-    for (int q = 0; q < 2; q++) {
-        const double w = wave_sum(s[q]);
-        if (lane == 0) sh[q][wid] = w;
-    }
+    PartialSums<> p;
+    p.load(pt, b0, b1, nq, tid);
+    p.sum(pt, b0, b1, nq, sh, tid);
+}
+
+// x, of which the compiler does not know that it has not changed: what
+// follows from it is computed where it is used and not carried around a loop.
+template <class X> __device__ __forceinline__ X opaque(X x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+// a[k] by a vector load: a wait for a scalar load is one for all of them, those
+// for the addresses of the loads to come included.
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+// Ends the program where the flag is set, by an instruction beside the test: a
+// jump to the kernel's end fetches code from another page.
+__device__ __forceinline__ void end_if(int flag)
+{
+    if (__builtin_expect(uniform(flag), 1)) __builtin_amdgcn_endpgm();
+}
+template <class T> __device__ __forceinline__ T vload(const T *a, int k)
+{
+    asm("" : "+v"(k));
+    return a[k];
 }
 
 // Chronopoulos-Gear recurrences of the multigrid-preconditioned CG from
@@ -201,15 +239,15 @@ __device__ __forceinline__ void partial_sums_256(const Part &pt, int b0, int b1,
 // on the first step alpha = gamma / delta, beta = 0.  False when the step
 // length is not positive and finite (the inner solve ends there; the float64
 // refinement carries on).
-__device__ __forceinline__ bool cg_coefficients(const double *S, int iter, double gamma, double delta,
-                                                double &alpha, double &beta)
+__device__ __forceinline__ bool cg_coefficients(int iter, double gamma, double delta, double gamma_old,
+                                                double alpha_old, double &alpha, double &beta)
 {
     beta = 0.0;
     if (iter == 0) {
         alpha = gamma / delta;
     } else {
-        beta = gamma / S[S_CG_GAMMA];
-        alpha = gamma / (delta - beta * gamma / S[S_CG_ALPHA]);
+        beta = gamma / gamma_old;
+        alpha = gamma / (delta - beta * gamma / alpha_old);
     }
     return alpha > 0.0 && alpha < INFINITY && beta < INFINITY;
 }
@@ -809,7 +847,16 @@ void launch_update_red0(const Inst *I, const Tab &t, int knew, Part pt, hipStrea
 constexpr int kMgTile = 32;
 constexpr int kMgThreads = 512;
 
-__device__ __forceinline__ int wrap_any(int x, int n) { return ((x % n) + n) % n; }
+// x modulo n.  A window reaches past a periodic axis once at most unless the
+// level is smaller than the window: the two divisions (of run-time numbers,
+// 80 instructions a node) are for those levels only.
+__device__ __forceinline__ int wrap_any(int x, int n)
+{
+    x += x < 0 ? n : 0;
+    x -= x >= n ? n : 0;
+    if ((unsigned)x >= (unsigned)n) x = ((x % n) + n) % n;
+    return x;
+}
 
 // Window index (wi0 + a, wj0 + c) -> global node of level (NX, NY), or -1
 // outside a bounded axis.
@@ -822,92 +869,168 @@ __device__ __forceinline__ long long win_node(int NX, int NY, int px, int py, in
     return (long long)gi * NY + gj;
 }
 
-// Stages u (from src), g, fix of the W x W window with origin (wi0, wj0) on
-// level L.  Fixed nodes hold u = 0 on every level (no update ever writes
-// them), so the stencils below add neighbours without testing their mask;
-// all loads of a thread are issued before the LDS stores.
-template <int W, int NT = kMgThreads>
-__device__ __forceinline__ void mg_stage(const LevelDev &L, const float *src, const float *gsrc, int px, int py,
-                                         int wi0, int wj0, float *su, float *sg, uint8_t *sf)
-{
-    constexpr int R = (W * W + NT - 1) / NT;
+// u (from src), g, fix of the W x W window with origin (wi0, wj0) on level L,
+// to LDS.  Fixed nodes hold u = 0 on every level (no update ever writes them),
+// so the stencils below add neighbours without testing their mask.  A launch
+// of these kernels is a chain of trips to memory (what it reads was written by
+// other kernels, mostly on other dies), so a kernel issues every load before it
+// waits for any, the flag that may end it included (257 x 257 nodes, with each
+// part's loads after the one before: 10.3, 5.8, 5.9 and 7.2 us for the level-0
+// and level-1 down and the level-1 and level-0 up kernels; now 8.0, 5.0, 4.6
+// and 6.2).  Where a launch holds several instances, of which some have
+// finished, the flag comes first: loading for nothing cost a batch of six more
+// (8.5 -> 13.1 us for the level-0 down kernel) than the trip it saves.
+template <int W, int NT = kMgThreads> struct Window {
+    static constexpr int R = (W * W + NT - 1) / NT;
     float uv[R], gv[R];
     uint8_t fv[R];
-#pragma unroll
-    for (int r = 0; r < R; r++) {
-        const int k = (int)threadIdx.x + r * NT;
-        const int a = k / W, c = k - a * W;
-        const long long n = k < W * W ? win_node(L.NX, L.NY, px, py, wi0 + a, wj0 + c) : -1;
-        uv[r] = 0.0f;
-        gv[r] = 0.0f;
-        fv[r] = 1;
-        if (n >= 0) {
-            fv[r] = L.fix[n];
-            uv[r] = src[n];
-            gv[r] = gsrc[n];
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < R; r++) {
-        const int k = (int)threadIdx.x + r * NT;
-        if (k < W * W) {
-            su[k] = uv[r];
-            sg[k] = gv[r];
-            sf[k] = fv[r];
-        }
-    }
-}
 
-// Level 0 of the inner CG (Chronopoulos-Gear form): stages the residual
-// after this iteration's update, r - alpha (w + beta s), as g and its
-// red-from-zero start as u.  With `update` false the residual is r itself
-// (start of a pass).  Every block evaluates the same float32 expression for
-// a node, so window copies agree with the owner's stored values.
-template <int W>
-__device__ __forceinline__ void mg_stage_l0(const Inst &I, int update, int first, float alpha, float beta,
-                                            const float *r, const float *sv, const float *wv, int wi0, int wj0,
-                                            float *su, float *sg, uint8_t *sf)
-{
-    constexpr int R = (W * W + kMgThreads - 1) / kMgThreads;
-    const LevelDev &L = I.lev[0];
-    float rv[R], s_[R], w_[R];
+    __device__ __forceinline__ void load(const LevelDev &L, const float *src, const float *gsrc, int px, int py,
+                                         int wi0, int wj0)
+    {
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const int k = (int)threadIdx.x + r * NT;
+            const int a = k / W, c = k - a * W;
+            const long long n = k < W * W ? win_node(L.NX, L.NY, px, py, wi0 + a, wj0 + c) : -1;
+            uv[r] = 0.0f;
+            gv[r] = 0.0f;
+            fv[r] = 1;
+            if (n >= 0) {
+                fv[r] = L.fix[n];
+                uv[r] = src[n];
+                gv[r] = gsrc[n];
+            }
+        }
+    }
+    __device__ __forceinline__ void store(float *su, float *sg, uint8_t *sf) const
+    {
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const int k = (int)threadIdx.x + r * NT;
+            if (k < W * W) {
+                su[k] = uv[r];
+                sg[k] = gv[r];
+                sf[k] = fv[r];
+            }
+        }
+    }
+};
+
+// The prolonged coarse correction e at the window's red nodes (their mask is
+// tested where it is used).
+template <int W, int NT = kMgThreads> struct Prolonged {
+    static constexpr int R = (W * W + NT - 1) / NT;
+    float e[R][4];
+    unsigned one;                      // bit r: a red node of both even indices, which lies on a coarse node
+
+    __device__ __forceinline__ void load(const LevelDev &L, const LevelDev &C, int px, int py, int wi0, int wj0)
+    {
+        const float *u = C.u;
+        one = 0;
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const int k = (int)threadIdx.x + r * NT;
+            const int a = k / W, c = k - a * W;
+            int gi = wi0 + a, gj = wj0 + c;
+            if (px) gi = wrap_any(gi, L.NX);
+            if (py) gj = wrap_any(gj, L.NY);
+            const bool in = k < W * W && ((a + c) & 1) == 0 && gi >= 0 && gi < L.NX && gj >= 0 && gj < L.NY;
+            const int I = in ? gi >> 1 : 0, J = in ? gj >> 1 : 0;
+            const int I1 = wrap_hi(I + 1, C.NX), J1 = wrap_hi(J + 1, C.NY);
+            e[r][0] = u[(long long)I * C.NY + J];
+            e[r][1] = u[(long long)I1 * C.NY + J];
+            e[r][2] = u[(long long)I * C.NY + J1];
+            e[r][3] = u[(long long)I1 * C.NY + J1];
+            if (((gi | gj) & 1) == 0) one |= 1u << r;
+        }
+    }
+    // sc = su + the correction at the red nodes that are not fixed, else 0
+    __device__ __forceinline__ void add(const float *su, const uint8_t *sf, float *sc) const
+    {
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const int k = (int)threadIdx.x + r * NT;
+            const int a = k / W, c = k - a * W;
+            const float m = 0.25f * (e[r][0] + e[r][1] + e[r][2] + e[r][3]);
+            if (k < W * W) sc[k] = ((a + c) & 1) == 0 && !sf[k] ? su[k] + ((one >> r) & 1 ? e[r][0] : m) : 0.0f;
+        }
+    }
+};
+
+// Level 0 of the inner CG (Chronopoulos-Gear form): the residual after this
+// iteration's update, r - alpha (w + beta s), as g and its red-from-zero start
+// as u.  With `update` false the residual is r itself (start of a pass).
+// Every block evaluates the same float32 expression for a node, so window
+// copies agree with the owner's stored values.  load() also reads the own
+// nodes' w, s, z, p and e.
+template <int W> struct Window0 {
+    static constexpr int R = (W * W + kMgThreads - 1) / kMgThreads, O = kMgTile * kMgTile / kMgThreads;
+    float rv[R], s_[R], w_[R], ow[O], os[O], oz[O], op[O], oe[O];
     uint8_t fv[R];
+
+    __device__ __forceinline__ void load(const Inst &I, int update, const float *r, const float *sv, int i0, int j0,
+                                         int HD)
+    {
+        const LevelDev &L = I.lev[0];
+        const float *wv = I.cg_w, *z = I.z, *p = I.p[0], *e = I.e;
 #pragma unroll
-    for (int q = 0; q < R; q++) {
-        const int k = (int)threadIdx.x + q * kMgThreads;
-        const int a = k / W, c = k - a * W;
-        const long long n = k < W * W ? win_node(L.NX, L.NY, I.g.px, I.g.py, wi0 + a, wj0 + c) : -1;
-        rv[q] = 0.0f;
-        s_[q] = 0.0f;
-        w_[q] = 0.0f;
-        fv[q] = 1;
-        if (n >= 0) {
-            fv[q] = L.fix[n];
-            rv[q] = r[n];
-            if (update) {
-                w_[q] = wv[n];
-                if (!first) s_[q] = sv[n];
+        for (int q = 0; q < R; q++) {
+            const int k = (int)threadIdx.x + q * kMgThreads;
+            const int a = k / W, c = k - a * W;
+            const long long n =
+                k < W * W ? win_node(L.NX, L.NY, I.g.px, I.g.py, i0 - HD + a, j0 - HD + c) : -1;
+            rv[q] = 0.0f;
+            s_[q] = 0.0f;
+            w_[q] = 0.0f;
+            fv[q] = 1;
+            if (n >= 0) {
+                fv[q] = L.fix[n];
+                rv[q] = r[n];
+                if (update) {
+                    w_[q] = wv[n];
+                    s_[q] = sv[n];
+                }
+            }
+        }
+        if (!update) return;
+#pragma unroll
+        for (int q = 0; q < O; q++) {
+            const int k = (int)threadIdx.x + q * kMgThreads;
+            const int gi = i0 + k / kMgTile, gj = j0 + k % kMgTile;
+            if (gi < L.NX && gj < L.NY) {
+                const long long n = (long long)gi * L.NY + gj;
+                ow[q] = wv[n];
+                os[q] = sv[n];
+                oz[q] = z[n];
+                op[q] = p[n];
+                oe[q] = e[n];
             }
         }
     }
+    // first: beta = 0, s holds an earlier pass
+    __device__ __forceinline__ void store(int update, int first, float alpha, float beta, float *su, float *sg,
+                                          uint8_t *sf) const
+    {
 #pragma unroll
-    for (int q = 0; q < R; q++) {
-        const int k = (int)threadIdx.x + q * kMgThreads;
-        if (k >= W * W) continue;
-        const int a = k / W, c = k - a * W;
-        float rn = 0.0f;
-        if (!fv[q]) {
-            rn = rv[q];
-            if (update) {
-                const float sn = first ? w_[q] : w_[q] + beta * s_[q];
-                rn = rn - alpha * sn;
+        for (int q = 0; q < R; q++) {
+            const int k = (int)threadIdx.x + q * kMgThreads;
+            if (k >= W * W) continue;
+            const int a = k / W, c = k - a * W;
+            float rn = 0.0f;
+            if (!fv[q]) {
+                rn = rv[q];
+                if (update) {
+                    const float sn = first ? w_[q] : w_[q] + beta * s_[q];
+                    rn = rn - alpha * sn;
+                }
             }
+            sg[k] = rn;
+            su[k] = (((a + c) & 1) == 0) ? rn * 0.25f : 0.0f;
+            sf[k] = fv[q];
         }
-        sg[k] = rn;
-        su[k] = (((a + c) & 1) == 0) ? rn * 0.25f : 0.0f;
-        sf[k] = fv[q];
     }
-}
+};
 
 // Gauss-Seidel value at window node k (neighbours in the window; fixed
 // neighbours contribute their zero).
@@ -936,11 +1059,114 @@ __device__ __forceinline__ void win_sweep(float *su, const float *sg, const uint
     }
 }
 
-// Down half-cycle of level l with NU pre-smoothing steps: from the
-// red-from-zero start, black, then (red, black) x (NU - 1); the pre-smoothed
-// level goes to uo, the restricted residual to level l + 1 (g, and u = its
-// red-from-zero start).
-// MODE 0: level l >= 1 (start staged from u).
+__host__ __device__ constexpr int pad16(int b) { return (b + 15) & ~15; }
+__host__ __device__ constexpr int win_lds(int W) { return pad16(3 * W * W * 4) + pad16(W * W); }
+// Window arrays at byte offset off: u, g, scratch (float) and the mask.
+struct WinLds {
+    float *u, *g, *r;
+    uint8_t *f;
+};
+__device__ __forceinline__ WinLds win_at(unsigned char *lds, int off, int W)
+{
+    WinLds w;
+    w.u = (float *)(lds + off);
+    w.g = w.u + W * W;
+    w.r = w.g + W * W;
+    w.f = (uint8_t *)(lds + off + pad16(3 * W * W * 4));
+    return w;
+}
+
+constexpr int kMgSmooth = 1;     // pre- and post-smoothing steps on the fine levels
+
+// Pre-smoothing of a window from its red-from-zero start.
+template <int NU, int W, int NT>
+__device__ __forceinline__ void pre_smooth(float *su, const float *sg, const uint8_t *sf)
+{
+#pragma unroll
+    for (int m = 1; m < 2 * NU; m++) {
+        win_sweep<W, NT>(su, sg, sf, m, m & 1);           // odd m: black, even m: red
+        __syncthreads();
+    }
+}
+
+// Own nodes (both colours) to uo; residuals at the red nodes the restriction
+// reads (window rows/cols 2NU .. W-1-2NU).
+template <int NU, int W, int NT>
+__device__ __forceinline__ void down_residuals(const LevelDev &F, int i0, int j0, const float *su, const float *sg,
+                                               const uint8_t *sf, float *sr)
+{
+    constexpr int HD = 2 * NU + 1;
+    float *uo = F.uo;
+    for (int k = threadIdx.x; k < kMgTile * kMgTile; k += NT) {
+        const int a = k / kMgTile, c = k - a * kMgTile;
+        const int gi = i0 + a, gj = j0 + c;
+        if (gi >= F.NX || gj >= F.NY) continue;
+        uo[(long long)gi * F.NY + gj] = su[(a + HD) * W + (c + HD)];
+    }
+    for (int k = threadIdx.x; k < W * W; k += NT) {
+        const int a = k / W, c = k - a * W;
+        if (a < 2 * NU || a > W - 1 - 2 * NU || c < 2 * NU || c > W - 1 - 2 * NU) continue;
+        if (((a + c) & 1) != 0) continue;
+        float r = 0.0f;
+        if (!sf[k]) {
+            float q = 4.0f * su[k];
+            q -= su[k - W];
+            q -= su[k + W];
+            q -= su[k - 1];
+            q -= su[k + 1];
+            r = sg[k] - q;
+        }
+        sr[k] = r;
+    }
+}
+
+// Restriction to coarse node (CI, CJ), which lies on window node k.
+template <int W>
+__device__ __forceinline__ void restrict_node(const LevelDev &C, int CI, int CJ, int fixed, const float *sr, int k)
+{
+    const long long n = (long long)CI * C.NY + CJ;
+    float gv = 0.0f, uv = 0.0f;
+    if (!fixed) {
+        float acc = 0.0f;
+        acc += 0.25f * sr[k - W - 1];
+        acc += 0.25f * sr[k - W + 1];
+        acc += 1.0f * sr[k];
+        acc += 0.25f * sr[k + W - 1];
+        acc += 0.25f * sr[k + W + 1];
+        gv = acc;
+        if (((CI + CJ) & 1) == 0) uv = gv * 0.25f;
+    }
+    C.g[n] = gv;
+    C.u[n] = uv;
+}
+
+// Down half-cycle of level l >= 1 (start staged from u) on its 32 x 32 tile
+// (ti, tj) with NU pre-smoothing steps: from the red-from-zero start, black,
+// then (red, black) x (NU - 1); the pre-smoothed level goes to uo, the
+// restricted residual to level l + 1 (g, and u = its red-from-zero start).
+template <int NU, int NT>
+__device__ __forceinline__ void mg_down_fine(const Inst &I, int level, int ti, int tj, int done, unsigned char *lds)
+{
+    constexpr int HD = 2 * NU + 1, W = kMgTile + 2 * HD - 1;
+    const LevelDev F = I.lev[level], C = I.lev[level + 1];
+    const int i0 = ti * kMgTile, j0 = tj * kMgTile;
+    const WinLds f = win_at(lds, 0, W);
+    const int rci = (int)threadIdx.x >> 4, rcj = threadIdx.x & 15;   // coarse node of the restriction
+    const int CI = (i0 >> 1) + rci, CJ = (j0 >> 1) + rcj;
+    const bool coarse = threadIdx.x < 256 && CI < C.NX && CJ < C.NY;
+    const uint8_t cfix = C.fix[coarse ? (long long)CI * C.NY + CJ : 0];
+    Window<W, NT> win;
+    win.load(F, F.u, F.g, I.g.px, I.g.py, i0 - HD, j0 - HD);
+    if (uniform(done)) return;
+    win.store(f.u, f.g, f.f);
+    __syncthreads();
+    pre_smooth<NU, W, NT>(f.u, f.g, f.f);
+    down_residuals<NU, W, NT>(F, i0, j0, f.u, f.g, f.f, f.r);
+    __syncthreads();
+    if (coarse) restrict_node<W>(C, CI, CJ, cfix, f.r, (2 * rci + HD) * W + (2 * rcj + HD));
+}
+
+// The same of level 0.
 // MODE 1: level 0 at the start of an inner pass: r = R[0], e = 0, ||r||^2
 //         (inner stop ratio and counters in the last block).
 // MODE 2: level 0 after a CG step: alpha and beta from the last V-cycle's
@@ -949,8 +1175,7 @@ __device__ __forceinline__ void win_sweep(float *su, const float *sg, const uint
 //         s' to the other buffers of the pair, ||r'||^2 partials (pt) for
 //         the inner stop test.  par: buffer of the pair holding r and s.
 template <int NU, int MODE>
-__global__ __launch_bounds__(kMgThreads) void k_mg_down(const Inst *insts, Tab t, int level, int par, Part pt,
-                                                        Part pq)
+__global__ __launch_bounds__(kMgThreads, 8) void k_mg_down(const Inst *insts, Tab t, int par, Part pt, Part pq)
 {
     constexpr int HD = 2 * NU + 1, W = kMgTile + 2 * HD - 1;
     const int ku = unit_of(t, (int)blockIdx.x);
@@ -959,18 +1184,26 @@ __global__ __launch_bounds__(kMgThreads) void k_mg_down(const Inst *insts, Tab t
     double *S = I.S;
     const int lb = (int)blockIdx.x - t.boff[ku];
     const int ti = lb / t.bx[ku], tj = lb - ti * t.bx[ku];
-    const LevelDev F0 = I.lev[level], Cc = I.lev[level + 1];
+    const LevelDev F0 = I.lev[0], Cc = I.lev[1];
     const int i0 = ti * kMgTile, j0 = tj * kMgTile;
     __shared__ float su[W * W], sg[W * W], sr[W * W];
     __shared__ uint8_t sf[W * W];
     double rr = 0.0;
-    bool work = true;
-    if (MODE == 1) {
-        work = !F[F_CONV];
-    } else {
-        if (F[F_DONE]) return;
-    }
+    Window0<W> win0;
+    const float *r = par ? I.cg_r1 : F0.g;
+    if (MODE == 2 && t.n > 1 && F[F_DONE]) return;
+    const int stop = vload(F, MODE == 1 ? F_CONV : F_DONE);
+    PartialSums<3> ps;
+    if (MODE == 2) ps.load(pq, t.boff[ku], t.boff[ku + 1], 2, (int)threadIdx.x);
+    const int iter = MODE == 2 ? vload(F, F_ITER) : 0;
+    const double g_old = MODE == 2 ? vload(S, S_CG_GAMMA) : 0.0, a_old = MODE == 2 ? vload(S, S_CG_ALPHA) : 0.0;
+    const int rci = (int)threadIdx.x >> 4, rcj = threadIdx.x & 15;   // coarse node of the restriction
+    const int CI = (i0 >> 1) + rci, CJ = (j0 >> 1) + rcj;
+    const bool coarse = threadIdx.x < 256 && CI < Cc.NX && CJ < Cc.NY;
+    const uint8_t cfix = Cc.fix[coarse ? (long long)CI * Cc.NY + CJ : 0];
+    win0.load(I, MODE == 2, r, I.cg_s[par], i0, j0, HD);
     float alpha = 0.0f, beta = 0.0f;
+    int first = 1;
     if (MODE == 2) {
         // this step's alpha and beta from the last V-cycle's r.z and (A z).z
         // partials (pq): every block adds them in the same order, so all
@@ -978,12 +1211,13 @@ __global__ __launch_bounds__(kMgThreads) void k_mg_down(const Inst *insts, Tab t
         // also ends the inner solve when they are not usable (no block of
         // this launch writes a flag the others read).
         __shared__ double shq[2][4];
-        partial_sums_256(pq, t.boff[ku], t.boff[ku + 1], 2, shq, (int)threadIdx.x);
+        if (uniform(stop)) return;
+        ps.sum(pq, t.boff[ku], t.boff[ku + 1], 2, shq, (int)threadIdx.x);
         __syncthreads();
         const double gamma = shq[0][0] + shq[0][1] + shq[0][2] + shq[0][3];
         const double delta = shq[1][0] + shq[1][1] + shq[1][2] + shq[1][3];
         double a, b;
-        const bool ok = cg_coefficients(S, F[F_ITER], gamma, delta, a, b);
+        const bool ok = cg_coefficients(iter, gamma, delta, g_old, a_old, a, b);
         if (lb == 0 && threadIdx.x == 0) {
             S[S_CG_NALPHA] = a;
             S[S_CG_NBETA] = b;
@@ -992,138 +1226,55 @@ __global__ __launch_bounds__(kMgThreads) void k_mg_down(const Inst *insts, Tab t
         if (!ok) return;
         alpha = (float)a;
         beta = (float)b;
+        first = iter == 0;
     }
-    if (work) {
-        if (MODE == 0) {
-            mg_stage<W>(F0, F0.u, F0.g, I.g.px, I.g.py, i0 - HD, j0 - HD, su, sg, sf);
-        } else {
-            const int first = MODE == 2 ? F[F_ITER] == 0 : 1;
-            const float *r = par ? I.cg_r1 : F0.g;
-            mg_stage_l0<W>(I, MODE == 2, first, alpha, beta, r, I.cg_s[par], I.cg_w, i0 - HD, j0 - HD, su, sg, sf);
-            __syncthreads();
-            // own tile: the vector updates and ||r'||^2 (reads the window only)
-            float *rn_out = par ? F0.g : I.cg_r1;
-            float *sn_out = I.cg_s[1 - par];
-            for (int k = threadIdx.x; k < kMgTile * kMgTile; k += kMgThreads) {
-                const int a = k / kMgTile, c = k - a * kMgTile;
-                const int gi = i0 + a, gj = j0 + c;
-                if (gi >= F0.NX || gj >= F0.NY) continue;
-                const long long n = (long long)gi * F0.NY + gj;
-                const int w = (a + HD) * W + (c + HD);
-                if (MODE == 1) {
-                    I.e[n] = 0.0f;
-                } else if (!sf[w]) {
-                    const float z = I.z[n];
-                    const float pn = first ? z : z + beta * I.p[0][n];
-                    const float sn = first ? I.cg_w[n] : I.cg_w[n] + beta * I.cg_s[par][n];
-                    I.p[0][n] = pn;
-                    I.e[n] = I.e[n] + alpha * pn;
-                    sn_out[n] = sn;
-                    rn_out[n] = sg[w];
-                } else {
-                    I.p[0][n] = 0.0f;
-                    sn_out[n] = 0.0f;
-                    rn_out[n] = 0.0f;
-                }
-                if (!sf[w]) rr += (double)sg[w] * (double)sg[w];
-            }
-        }
-        if (MODE == 0) __syncthreads();
+    if (MODE != 1 || !uniform(stop)) {
+        win0.store(MODE == 2, first, alpha, beta, su, sg, sf);
+        __syncthreads();
+        // own tile: the vector updates and ||r'||^2 (reads the window only)
+        float *rn_out = par ? F0.g : I.cg_r1;
+        float *sn_out = I.cg_s[1 - par], *p_out = I.p[0], *e_out = I.e;
 #pragma unroll
-        for (int m = 1; m < 2 * NU; m++) {
-            win_sweep<W>(su, sg, sf, m, m & 1);           // odd m: black, even m: red
-            __syncthreads();
-        }
-        // own nodes (both colours) to uo; residuals at the red nodes the
-        // restriction reads (window rows/cols 2NU .. W-1-2NU)
-        for (int k = threadIdx.x; k < kMgTile * kMgTile; k += kMgThreads) {
+        for (int q = 0; q < kMgTile * kMgTile / kMgThreads; q++) {
+            const int k = (int)threadIdx.x + q * kMgThreads;
             const int a = k / kMgTile, c = k - a * kMgTile;
             const int gi = i0 + a, gj = j0 + c;
             if (gi >= F0.NX || gj >= F0.NY) continue;
-            F0.uo[(long long)gi * F0.NY + gj] = su[(a + HD) * W + (c + HD)];
-        }
-        for (int k = threadIdx.x; k < W * W; k += kMgThreads) {
-            const int a = k / W, c = k - a * W;
-            if (a < 2 * NU || a > W - 1 - 2 * NU || c < 2 * NU || c > W - 1 - 2 * NU) continue;
-            if (((a + c) & 1) != 0) continue;
-            float r = 0.0f;
-            if (!sf[k]) {
-                float q = 4.0f * su[k];
-                q -= su[k - W];
-                q -= su[k + W];
-                q -= su[k - 1];
-                q -= su[k + 1];
-                r = sg[k] - q;
+            const long long n = (long long)gi * F0.NY + gj;
+            const int w = (a + HD) * W + (c + HD);
+            if (MODE == 1) {
+                e_out[n] = 0.0f;
+            } else if (!sf[w]) {
+                const float pn = first ? win0.oz[q] : win0.oz[q] + beta * win0.op[q];
+                const float sn = first ? win0.ow[q] : win0.ow[q] + beta * win0.os[q];
+                p_out[n] = pn;
+                e_out[n] = win0.oe[q] + alpha * pn;
+                sn_out[n] = sn;
+                rn_out[n] = sg[w];
+            } else {
+                p_out[n] = 0.0f;
+                sn_out[n] = 0.0f;
+                rn_out[n] = 0.0f;
             }
-            sr[k] = r;
+            if (!sf[w]) rr += (double)sg[w] * (double)sg[w];
         }
+        pre_smooth<NU, W, kMgThreads>(su, sg, sf);
+        down_residuals<NU, W, kMgThreads>(F0, i0, j0, su, sg, sf, sr);
         __syncthreads();
-        // restriction: coarse nodes (i0/2 .. i0/2+15, j0/2 .. j0/2+15)
-        if (threadIdx.x < 256) {
-            const int ci = threadIdx.x >> 4, cj = threadIdx.x & 15;
-            const int CI = (i0 >> 1) + ci, CJ = (j0 >> 1) + cj;
-            if (CI < Cc.NX && CJ < Cc.NY) {
-                const long long n = (long long)CI * Cc.NY + CJ;
-                float gv = 0.0f, uv = 0.0f;
-                if (!Cc.fix[n]) {
-                    const int k = (2 * ci + HD) * W + (2 * cj + HD);
-                    float acc = 0.0f;
-                    acc += 0.25f * sr[k - W - 1];
-                    acc += 0.25f * sr[k - W + 1];
-                    acc += 1.0f * sr[k];
-                    acc += 0.25f * sr[k + W - 1];
-                    acc += 0.25f * sr[k + W + 1];
-                    gv = acc;
-                    if (((CI + CJ) & 1) == 0) uv = gv * 0.25f;
-                }
-                Cc.g[n] = gv;
-                Cc.u[n] = uv;
-            }
-        }
+        if (coarse) restrict_node<W>(Cc, CI, CJ, cfix, sr, (2 * rci + HD) * W + (2 * rcj + HD));
     }
-    if (MODE == 0) return;
     double v[1] = {rr};
     block_partials<1>(v, pt);
 }
 
-// Up half-cycle of level l with NU post-smoothing steps: black from the
-// corrected reds (pre-smoothed value + bilinear prolongation of level l+1's
-// result u), then red, then (black, red) x (NU - 1); result to u.
-// L0: level 0 of the inner CG: z = the V-cycle result on the tile and a
-// one-node ring around it, z to u (the CG's z), w = A z to cg_w, r.z and w.z
-// partials, the step scalars alpha and beta in the last block.  par: buffer
-// of the pair holding the current residual.
-template <int NU, int L0>
-__global__ __launch_bounds__(kMgThreads) void k_mg_up(const Inst *insts, Tab t, int level, int par, Part pt)
+// Post-smoothing of a window: black from the corrected reds sc, then red, then
+// (black, red) x (NU - 1), without the last red half-sweep unless it covers
+// the tile's ring (L0).
+template <int NU, int L0, int W, int NT>
+__device__ __forceinline__ void post_smooth(float *su, const float *sg, const float *sc, const uint8_t *sf)
 {
-    constexpr int HU = 2 * NU + L0, W = kMgTile + 2 * HU;
-    const int ku = unit_of(t, (int)blockIdx.x);
-    const Inst &I = insts[t.id[ku]];
-    if (I.F[F_DONE]) return;
-    const int lb = (int)blockIdx.x - t.boff[ku];
-    const int ti = lb / t.bx[ku], tj = lb - ti * t.bx[ku];
-    const LevelDev F = I.lev[level], Cc = I.lev[level + 1];
-    const int i0 = ti * kMgTile, j0 = tj * kMgTile;
-    __shared__ float su[W * W], sg[W * W], sc[W * W];
-    __shared__ uint8_t sf[W * W];
-    const float *gsrc = (L0 && par) ? I.cg_r1 : F.g;
-    mg_stage<W>(F, F.uo, gsrc, I.g.px, I.g.py, i0 - HU, j0 - HU, su, sg, sf);
-    __syncthreads();
-    // red nodes: value plus the prolonged coarse correction (0 on fixed nodes)
-    for (int k = threadIdx.x; k < W * W; k += kMgThreads) {
-        const int a = k / W, c = k - a * W;
-        int gi = i0 - HU + a, gj = j0 - HU + c;
-        float v = 0.0f;
-        if (((a + c) & 1) == 0 && !sf[k]) {
-            if (I.g.px) gi = wrap_any(gi, F.NX);
-            if (I.g.py) gj = wrap_any(gj, F.NY);
-            v = su[k] + prolong_red(Cc.u, Cc.NX, Cc.NY, gi, gj);
-        }
-        sc[k] = v;
-    }
-    __syncthreads();
     // black update over window rows/cols 1 .. W-2 from the corrected reds
-    for (int k = threadIdx.x; k < W * W; k += kMgThreads) {
+    for (int k = threadIdx.x; k < W * W; k += NT) {
         const int a = k / W, c = k - a * W;
         if (a < 1 || a > W - 2 || c < 1 || c > W - 2 || sf[k]) continue;
         if (((a + c) & 1) != 1) continue;
@@ -1138,29 +1289,80 @@ __global__ __launch_bounds__(kMgThreads) void k_mg_up(const Inst *insts, Tab t, 
     constexpr int MEND = L0 ? 2 * NU + 1 : 2 * NU;
 #pragma unroll
     for (int m = 2; m < MEND; m++) {
-        win_sweep<W>(su, sg, sf, m, m & 1);               // even m: red, odd m: black
+        win_sweep<W, NT>(su, sg, sf, m, m & 1);           // even m: red, odd m: black
         __syncthreads();
     }
-    if (!L0) {
-        // last red half-sweep on the own tile; write both colours to u
-        for (int k = threadIdx.x; k < kMgTile * kMgTile; k += kMgThreads) {
-            const int a = k / kMgTile, c = k - a * kMgTile;
-            const int gi = i0 + a, gj = j0 + c;
-            if (gi >= F.NX || gj >= F.NY) continue;
-            const int w = (a + HU) * W + (c + HU);
-            float z = 0.0f;                               // fixed nodes carry no correction
-            if (!sf[w]) {
-                z = su[w];
-                if (((gi + gj) & 1) == 0) z = win_gs<W>(su, sg, w);
-            }
-            F.u[(long long)gi * F.NY + gj] = z;
+}
+
+// Up half-cycle of level l >= 1 with NU post-smoothing steps on its tile
+// (ti, tj): the corrected reds (pre-smoothed value + bilinear prolongation of
+// level l+1's result u), then the post-smoothing; result to u.
+template <int NU, int NT>
+__device__ __forceinline__ void mg_up_fine(const Inst &I, int level, int ti, int tj, int done, unsigned char *lds)
+{
+    constexpr int HU = 2 * NU, W = kMgTile + 2 * HU;
+    const LevelDev F = I.lev[level];
+    const int i0 = ti * kMgTile, j0 = tj * kMgTile;
+    const WinLds f = win_at(lds, 0, W);
+    Window<W, NT> win;
+    Prolonged<W, NT> pro;
+    win.load(F, F.uo, F.g, I.g.px, I.g.py, i0 - HU, j0 - HU);
+    pro.load(F, I.lev[level + 1], I.g.px, I.g.py, i0 - HU, j0 - HU);
+    if (uniform(done)) return;
+    win.store(f.u, f.g, f.f);
+    __syncthreads();
+    pro.add(f.u, f.f, f.r);
+    __syncthreads();
+    post_smooth<NU, 0, W, NT>(f.u, f.g, f.r, f.f);
+    // last red half-sweep on the own tile; write both colours to u
+    float *u = F.u;
+    for (int k = threadIdx.x; k < kMgTile * kMgTile; k += NT) {
+        const int a = k / kMgTile, c = k - a * kMgTile;
+        const int gi = i0 + a, gj = j0 + c;
+        if (gi >= F.NX || gj >= F.NY) continue;
+        const int w = (a + HU) * W + (c + HU);
+        float z = 0.0f;                                   // fixed nodes carry no correction
+        if (!f.f[w]) {
+            z = f.u[w];
+            if (((gi + gj) & 1) == 0) z = win_gs<W>(f.u, f.g, w);
         }
-        return;
+        u[(long long)gi * F.NY + gj] = z;
     }
-    // level 0: the last red sweep covered the tile and its ring; z = su
+}
+
+// The same of level 0: z = the V-cycle result on the tile and a one-node ring
+// around it, z to u (the CG's z), w = A z to cg_w, r.z and w.z partials.  par:
+// buffer of the pair holding the current residual.
+template <int NU>
+__global__ __launch_bounds__(kMgThreads) void k_mg_up(const Inst *insts, Tab t, int par, Part pt)
+{
+    constexpr int HU = 2 * NU + 1, W = kMgTile + 2 * HU;
+    const int ku = unit_of(t, (int)blockIdx.x);
+    const Inst &I = insts[t.id[ku]];
+    if (t.n > 1) end_if(I.F[F_DONE]);
+    const int done = vload((const int *)I.F, F_DONE);
+    const int lb = (int)blockIdx.x - t.boff[ku];
+    const int ti = lb / t.bx[ku], tj = lb - ti * t.bx[ku];
+    const LevelDev F = I.lev[0];
+    const int i0 = ti * kMgTile, j0 = tj * kMgTile;
+    __shared__ float su[W * W], sg[W * W], sc[W * W];
+    __shared__ uint8_t sf[W * W];
+    const float *gsrc = par ? I.cg_r1 : F.g;
+    Window<W> win;
+    Prolonged<W> pro;
+    win.load(F, F.uo, gsrc, I.g.px, I.g.py, i0 - HU, j0 - HU);
+    pro.load(F, I.lev[1], I.g.px, I.g.py, i0 - HU, j0 - HU);
+    if (uniform(done)) return;
+    win.store(su, sg, sf);
+    __syncthreads();
+    pro.add(su, sf, sc);
+    __syncthreads();
+    post_smooth<NU, 1, W, kMgThreads>(su, sg, sc, sf);
+    // the last red sweep covered the tile and its ring; z = su
     // (0 on fixed nodes), w = A z with the neighbours in the order x-1, x+1,
     // y-1, y+1
     double rz = 0.0, wz = 0.0;
+    float *z_out = F.u, *w_out = I.cg_w;
     for (int k = threadIdx.x; k < kMgTile * kMgTile; k += kMgThreads) {
         const int a = k / kMgTile, c = k - a * kMgTile;
         const int gi = i0 + a, gj = j0 + c;
@@ -1179,14 +1381,12 @@ __global__ __launch_bounds__(kMgThreads) void k_mg_up(const Inst *insts, Tab t, 
             rz += (double)sg[w] * (double)z;
             wz += (double)wv * (double)z;
         }
-        F.u[n] = z;
-        I.cg_w[n] = wv;
+        z_out[n] = z;
+        w_out[n] = wv;
     }
     double v[2] = {rz, wz};
     block_partials<2>(v, pt);
 }
-
-constexpr int kMgSmooth = 1;     // pre- and post-smoothing steps on the fine levels
 
 // The level-0 up kernel's r.z and (A z).z partials: a range of their own
 // after the two the other reductions use, so that they survive until the
@@ -1194,33 +1394,26 @@ constexpr int kMgSmooth = 1;     // pre- and post-smoothing steps on the fine le
 // in between).
 static Part cg_dot_part(Part pt) { return Part{pt.p + 2 * (size_t)pt.stride, pt.stride}; }
 
-void launch_mg_down(const Inst *I, const Tab &t, int level, int mode, int par, Part pt, hipStream_t s)
+void launch_mg_down(const Inst *I, const Tab &t, int mode, int par, Part pt, hipStream_t s)
 {
     if (!t.n) return;
     const dim3 g(tab_blocks(t)), b(kMgThreads);
     const Part pq = cg_dot_part(pt);
-    if (mode == 0) {
-        hipLaunchKernelGGL((k_mg_down<kMgSmooth, 0>), g, b, 0, s, I, t, level, par, pt, pq);
-    } else if (mode == 1) {
-        hipLaunchKernelGGL((k_mg_down<kMgSmooth, 1>), g, b, 0, s, I, t, level, par, pt, pq);
+    if (mode == 1) {
+        hipLaunchKernelGGL((k_mg_down<kMgSmooth, 1>), g, b, 0, s, I, t, par, pt, pq);
         finalize(I, t, pt, OP_INIT, s);
     } else {
         // mode 3: the coarse kernel reduces the partials (fused update)
-        hipLaunchKernelGGL((k_mg_down<kMgSmooth, 2>), g, b, 0, s, I, t, level, par, pt, pq);
+        hipLaunchKernelGGL((k_mg_down<kMgSmooth, 2>), g, b, 0, s, I, t, par, pt, pq);
         if (mode == 2) finalize(I, t, pt, OP_UPDATE, s);
     }
 }
 
-void launch_mg_up(const Inst *I, const Tab &t, int level, int par, Part pt, hipStream_t s)
+void launch_mg_up(const Inst *I, const Tab &t, int par, Part pt, hipStream_t s)
 {
     if (!t.n) return;
-    const dim3 g(tab_blocks(t)), b(kMgThreads);
-    if (level == 0) {
-        // the next level-0 down kernel turns the partials into alpha and beta
-        hipLaunchKernelGGL((k_mg_up<kMgSmooth, 1>), g, b, 0, s, I, t, level, par, cg_dot_part(pt));
-    } else {
-        hipLaunchKernelGGL((k_mg_up<kMgSmooth, 0>), g, b, 0, s, I, t, level, par, pt);
-    }
+    // the next level-0 down kernel turns the partials into alpha and beta
+    hipLaunchKernelGGL((k_mg_up<kMgSmooth>), dim3(tab_blocks(t)), dim3(kMgThreads), 0, s, I, t, par, cg_dot_part(pt));
 }
 
 // ---------------------------------------------------------------------------
@@ -1237,51 +1430,41 @@ constexpr int kPairDnC = 37;      // down, level l + 1: rows I0 - 3 .. I0 + 33
 constexpr int kPairUpC = 39;      // up, level l + 1:   rows I0 - 3 .. I0 + 35
 constexpr int kPairUpF = 68;      // up, level l:       rows 2 I0 - 2 .. 2 I0 + 65
 
-__host__ __device__ constexpr int pad16(int b) { return (b + 15) & ~15; }
-__host__ __device__ constexpr int win_lds(int W) { return pad16(3 * W * W * 4) + pad16(W * W); }
 constexpr int kPairDnLds = win_lds(kPairDnF) + win_lds(kPairDnC);
 constexpr int kPairUpLds = win_lds(kPairUpC) + win_lds(kPairUpF);
-
-// Window arrays at byte offset off: u, g, scratch (float) and the mask.
-struct WinLds {
-    float *u, *g, *r;
-    uint8_t *f;
-};
-__device__ __forceinline__ WinLds win_at(unsigned char *lds, int off, int W)
-{
-    WinLds w;
-    w.u = (float *)(lds + off);
-    w.g = w.u + W * W;
-    w.r = w.g + W * W;
-    w.f = (uint8_t *)(lds + off + pad16(3 * W * W * 4));
-    return w;
-}
 
 // Down half-cycles of levels l and l + 1: black half-sweep of level l from
 // its red-from-zero start, level l's pre-smoothed tile nodes to uo, the
 // restriction of its red residuals to the level-(l+1) window (g of the own
 // tile stored), black half-sweep there, level l+1's tile to uo, and the
 // restriction to level l + 2 (g and its red-from-zero start u).
-__global__ __launch_bounds__(kPairThreads) void k_mg_down_pair(const Inst *insts, Tab t, int level)
+__device__ __forceinline__ void mg_down_pair(const Inst &I, int level, int ti, int tj, int done, unsigned char *lds)
 {
     constexpr int WF = kPairDnF, WC = kPairDnC, NT = kPairThreads;
-    extern __shared__ __align__(16) unsigned char lds[];
-    const int ku = unit_of(t, (int)blockIdx.x);
-    const Inst &I = insts[t.id[ku]];
-    if (I.F[F_DONE]) return;
-    const int lb = (int)blockIdx.x - t.boff[ku];
-    const int ti = lb / t.bx[ku], tj = lb - ti * t.bx[ku];
     const LevelDev F = I.lev[level], C = I.lev[level + 1], N = I.lev[level + 2];
     const int px = I.g.px, py = I.g.py;
     const int I0 = ti * kMgTile, J0 = tj * kMgTile;
     const WinLds f = win_at(lds, 0, WF), c = win_at(lds, win_lds(WF), WC);
     const int tid = threadIdx.x;
-    mg_stage<WF, NT>(F, F.u, F.g, px, py, 2 * I0 - 9, 2 * J0 - 9, f.u, f.g, f.f);
-    for (int k = tid; k < WC * WC; k += NT) {
-        const int a = k / WC, b = k - a * WC;
-        const long long n = win_node(C.NX, C.NY, px, py, I0 - 3 + a, J0 - 3 + b);
-        c.f[k] = n >= 0 ? C.fix[n] : 1;
+    constexpr int RC = (WC * WC + NT - 1) / NT;
+    uint8_t fc[RC];
+#pragma unroll
+    for (int r = 0; r < RC; r++) {
+        const int k = tid + r * NT, a = k / WC, b = k - a * WC;
+        const long long n = k < WC * WC ? win_node(C.NX, C.NY, px, py, I0 - 3 + a, J0 - 3 + b) : -1;
+        fc[r] = 1;
+        if (n >= 0) fc[r] = C.fix[n];
     }
+    const int ci = tid >> 4, cj = tid & 15, CI = (I0 >> 1) + ci, CJ = (J0 >> 1) + cj;   // node of level l + 2
+    const bool coarse = tid < 256 && CI < N.NX && CJ < N.NY;
+    const uint8_t cfix = N.fix[coarse ? (long long)CI * N.NY + CJ : 0];
+    Window<WF, NT> win;
+    win.load(F, F.u, F.g, px, py, 2 * I0 - 9, 2 * J0 - 9);
+    if (uniform(done)) return;
+    win.store(f.u, f.g, f.f);
+#pragma unroll
+    for (int r = 0; r < RC; r++)
+        if (tid + r * NT < WC * WC) c.f[tid + r * NT] = fc[r];
     __syncthreads();
     win_sweep<WF, NT>(f.u, f.g, f.f, 1, 1);               // black, rows 1 .. WF-2
     __syncthreads();
@@ -1347,26 +1530,22 @@ __global__ __launch_bounds__(kPairThreads) void k_mg_down_pair(const Inst *insts
         c.r[k] = r;
     }
     __syncthreads();
-    if (tid < 256) {                                      // restriction to level l + 2
-        const int ci = tid >> 4, cj = tid & 15;
-        const int CI = (I0 >> 1) + ci, CJ = (J0 >> 1) + cj;
-        if (CI < N.NX && CJ < N.NY) {
-            const long long n = (long long)CI * N.NY + CJ;
-            float gv = 0.0f, uv = 0.0f;
-            if (!N.fix[n]) {
-                const int m = (3 + 2 * ci) * WC + (3 + 2 * cj);
-                float acc = 0.0f;
-                acc += 0.25f * c.r[m - WC - 1];
-                acc += 0.25f * c.r[m - WC + 1];
-                acc += 1.0f * c.r[m];
-                acc += 0.25f * c.r[m + WC - 1];
-                acc += 0.25f * c.r[m + WC + 1];
-                gv = acc;
-                if (((CI + CJ) & 1) == 0) uv = gv * 0.25f;
-            }
-            N.g[n] = gv;
-            N.u[n] = uv;
+    if (coarse) {                                         // restriction to level l + 2
+        const long long n = (long long)CI * N.NY + CJ;
+        float gv = 0.0f, uv = 0.0f;
+        if (!cfix) {
+            const int m = (3 + 2 * ci) * WC + (3 + 2 * cj);
+            float acc = 0.0f;
+            acc += 0.25f * c.r[m - WC - 1];
+            acc += 0.25f * c.r[m - WC + 1];
+            acc += 1.0f * c.r[m];
+            acc += 0.25f * c.r[m + WC - 1];
+            acc += 0.25f * c.r[m + WC + 1];
+            gv = acc;
+            if (((CI + CJ) & 1) == 0) uv = gv * 0.25f;
         }
+        N.g[n] = gv;
+        N.u[n] = uv;
     }
 }
 
@@ -1374,34 +1553,25 @@ __global__ __launch_bounds__(kPairThreads) void k_mg_down_pair(const Inst *insts
 // the prolonged level-(l+2) correction at its reds, black update, red
 // half-sweep (its final correction, in LDS); then level l likewise with the
 // prolongation read from that LDS result; level l's tile to u.
-__global__ __launch_bounds__(kPairThreads) void k_mg_up_pair(const Inst *insts, Tab t, int level)
+__device__ __forceinline__ void mg_up_pair(const Inst &I, int level, int ti, int tj, int done, unsigned char *lds)
 {
     constexpr int WC = kPairUpC, WF = kPairUpF, NT = kPairThreads;
-    extern __shared__ __align__(16) unsigned char lds[];
-    const int ku = unit_of(t, (int)blockIdx.x);
-    const Inst &I = insts[t.id[ku]];
-    if (I.F[F_DONE]) return;
-    const int lb = (int)blockIdx.x - t.boff[ku];
-    const int ti = lb / t.bx[ku], tj = lb - ti * t.bx[ku];
     const LevelDev F = I.lev[level], C = I.lev[level + 1], N = I.lev[level + 2];
     const int px = I.g.px, py = I.g.py;
     const int I0 = ti * kMgTile, J0 = tj * kMgTile;
     const WinLds c = win_at(lds, 0, WC), f = win_at(lds, win_lds(WC), WF);
     const int tid = threadIdx.x;
-    mg_stage<WC, NT>(C, C.uo, C.g, px, py, I0 - 3, J0 - 3, c.u, c.g, c.f);
-    mg_stage<WF, NT>(F, F.uo, F.g, px, py, 2 * I0 - 2, 2 * J0 - 2, f.u, f.g, f.f);
+    Window<WC, NT> wc;
+    Window<WF, NT> wf;
+    Prolonged<WC, NT> pro;
+    wc.load(C, C.uo, C.g, px, py, I0 - 3, J0 - 3);
+    pro.load(C, N, px, py, I0 - 3, J0 - 3);
+    wf.load(F, F.uo, F.g, px, py, 2 * I0 - 2, 2 * J0 - 2);
+    if (uniform(done)) return;
+    wc.store(c.u, c.g, c.f);
+    wf.store(f.u, f.g, f.f);
     __syncthreads();
-    for (int k = tid; k < WC * WC; k += NT) {             // corrected reds of level l + 1
-        const int a = k / WC, b = k - a * WC;
-        float v = 0.0f;
-        if (((a + b) & 1) == 0 && !c.f[k]) {
-            int gi = I0 - 3 + a, gj = J0 - 3 + b;
-            if (px) gi = wrap_any(gi, C.NX);
-            if (py) gj = wrap_any(gj, C.NY);
-            v = c.u[k] + prolong_red(N.u, N.NX, N.NY, gi, gj);
-        }
-        c.r[k] = v;
-    }
+    pro.add(c.u, c.f, c.r);                               // corrected reds of level l + 1
     __syncthreads();
     for (int k = tid; k < WC * WC; k += NT) {             // black update, rows 1 .. WC-2
         const int a = k / WC, b = k - a * WC;
@@ -1455,20 +1625,58 @@ __global__ __launch_bounds__(kPairThreads) void k_mg_up_pair(const Inst *insts, 
     }
 }
 
-void launch_mg_pair(const Inst *I, const Tab &t, int level, bool down, hipStream_t s)
+// The half-cycle of level l of a V-cycle's instances: the pairs (l, l + 1) of tp
+// (tiles of level l + 1) and the single levels l of tf.  A batch of grids of
+// several sizes has both; in a launch of each they took 6.2 + 13.0 us down and
+// 7.1 + 11.6 us up, of which the single levels' is all latency, and 4 us each
+// where the instances have finished.  PAIRS false: no pairs, half the threads
+// (a 32 x 32 tile is two nodes a thread, and the halo of a level's window then
+// takes three rounds of loads instead of two: 4.6 us up at 129 x 129 nodes).
+template <bool PAIRS, bool DOWN>
+__global__ __launch_bounds__(PAIRS ? kPairThreads : kMgThreads) void k_mg_mid(const Inst *insts, Tab t, int npair,
+                                                                             int level)
 {
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int ku = unit_of(t, (int)blockIdx.x);
+    const bool pair = PAIRS && ku < npair;
+    const Inst &I = insts[t.id[ku]];
+    if (t.n > 1) end_if(I.F[F_DONE]);
+    const int done = vload((const int *)I.F, F_DONE);
+    const int lb = (int)blockIdx.x - t.boff[ku];
+    const int ti = lb / t.bx[ku], tj = lb - ti * t.bx[ku];
+    if (pair) {
+        if constexpr (DOWN) mg_down_pair(I, level, ti, tj, done, lds);
+        else mg_up_pair(I, level, ti, tj, done, lds);
+    } else {
+        if constexpr (DOWN) mg_down_fine<kMgSmooth, PAIRS ? kPairThreads : kMgThreads>(I, level, ti, tj, done, lds);
+        else mg_up_fine<kMgSmooth, PAIRS ? kPairThreads : kMgThreads>(I, level, ti, tj, done, lds);
+    }
+}
+
+void launch_mg_mid(const Inst *I, const Tab &tp, const Tab &tf, int level, bool down, hipStream_t s)
+{
+    Tab t = tp;
+    for (int k = 0; k < tf.n; k++) {
+        t.id[t.n] = tf.id[k];
+        t.bx[t.n] = tf.bx[k];
+        t.boff[t.n + 1] = t.boff[t.n] + tf.boff[k + 1] - tf.boff[k];
+        t.n++;
+    }
     if (!t.n) return;
     static bool attr = false;
     if (!attr) {
-        (void)hipFuncSetAttribute((const void *)k_mg_down_pair, hipFuncAttributeMaxDynamicSharedMemorySize,
+        (void)hipFuncSetAttribute((const void *)k_mg_mid<true, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   kPairDnLds);
-        (void)hipFuncSetAttribute((const void *)k_mg_up_pair, hipFuncAttributeMaxDynamicSharedMemorySize,
+        (void)hipFuncSetAttribute((const void *)k_mg_mid<true, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   kPairUpLds);
         attr = true;
     }
-    const dim3 g(tab_blocks(t)), b(kPairThreads);
-    if (down) hipLaunchKernelGGL(k_mg_down_pair, g, b, kPairDnLds, s, I, t, level);
-    else hipLaunchKernelGGL(k_mg_up_pair, g, b, kPairUpLds, s, I, t, level);
+    const dim3 g(tab_blocks(t)), bp(kPairThreads), bf(kMgThreads);
+    constexpr int fine = win_lds(kMgTile + 2 * (2 * kMgSmooth + 1) - 1);   // the down window, the larger one
+    if (tp.n && down) hipLaunchKernelGGL((k_mg_mid<true, true>), g, bp, kPairDnLds, s, I, t, tp.n, level);
+    else if (tp.n) hipLaunchKernelGGL((k_mg_mid<true, false>), g, bp, kPairUpLds, s, I, t, tp.n, level);
+    else if (down) hipLaunchKernelGGL((k_mg_mid<false, true>), g, bf, fine, s, I, t, tp.n, level);
+    else hipLaunchKernelGGL((k_mg_mid<false, false>), g, bf, fine, s, I, t, tp.n, level);
 }
 
 // ---------------------------------------------------------------------------
@@ -1846,7 +2054,7 @@ __global__ __launch_bounds__(1024) void k_coarse(const Inst *insts, Tab t, Tab t
 {
     const Inst &I = insts[t.id[blockIdx.x]];
     const int tid = threadIdx.x, nt = blockDim.x;
-    if (!fuse && I.F[F_DONE]) return;
+    if (!fuse || t.n > 1) end_if(I.F[F_DONE]);
     const CoarseArgs &a = I.coarse;
     extern __shared__ __align__(16) unsigned char lds[];
     __shared__ int tab[3][kMaxLev];
@@ -1854,7 +2062,7 @@ __global__ __launch_bounds__(1024) void k_coarse(const Inst *insts, Tab t, Tab t
     // 16-byte pieces to stage: the masks of every level, then the first
     // level's g (the global arrays are 256-byte aligned and padded, the LDS
     // ones 16-byte rounded, so whole pieces stay inside both)
-    __shared__ const unsigned char *src[kMaxLev + 1];
+    __shared__ Dev<const uint4> src[kMaxLev + 1];
     __shared__ int dst[kMaxLev + 1], cum[kMaxLev + 2];
     if (tid == 0) {
         int c = 0;
@@ -1864,12 +2072,12 @@ __global__ __launch_bounds__(1024) void k_coarse(const Inst *insts, Tab t, Tab t
             tab[2][l] = a.off_f[l];
             dims[0][l] = a.NX[l];
             dims[1][l] = a.NY[l];
-            src[l] = a.fix[l];
+            src[l] = (const uint4 *)(const uint8_t *)a.fix[l];
             dst[l] = a.off_f[l];
             cum[l] = c;
             c += (a.NX[l] * a.NY[l] + 15) >> 4;
         }
-        src[a.nlev] = (const unsigned char *)a.g_top;
+        src[a.nlev] = (const uint4 *)(const float *)a.g_top;
         dst[a.nlev] = a.off_g[0];
         cum[a.nlev] = c;
         cum[a.nlev + 1] = c + ((a.NX[0] * a.NY[0] + 3) >> 2);
@@ -1885,7 +2093,7 @@ __global__ __launch_bounds__(1024) void k_coarse(const Inst *insts, Tab t, Tab t
             int k = 0;
             while (p >= cum[k + 1]) k++;
             const int q = p - cum[k];
-            v = ((const uint4 *)src[k])[q];
+            v = src[k][q];
             d = dst[k] + 16 * q;
         }
     };
@@ -1930,7 +2138,7 @@ __global__ __launch_bounds__(1024) void k_coarse(const Inst *insts, Tab t, Tab t
         int k = 0;
         while (p >= cum[k + 1]) k++;
         const int q = p - cum[k];
-        *(uint4 *)(lds + dst[k] + 16 * q) = ((const uint4 *)src[k])[q];
+        *(uint4 *)(lds + dst[k] + 16 * q) = src[k][q];
     }
     auto lev = [&](int l) {
         CLev L;
@@ -2165,14 +2373,6 @@ __device__ void mg_dense_helper(const Inst &I, const MgSolveArgs &m, int h, unsi
         // nothing comes before the rest of the V-cycle is done
         __builtin_amdgcn_s_sleep(127);
     }
-}
-
-// x, of which the compiler does not know that it has not changed: what
-// follows from it is computed where it is used and not carried around a loop.
-template <class X> __device__ __forceinline__ X opaque(X x)
-{
-    asm volatile("" : "+v"(x));
-    return x;
 }
 
 // Positions in a level's LDS arrays that one thread smooths: NP pairs of a red
@@ -2839,6 +3039,7 @@ __device__ __forceinline__ void wave_sum4_u32(unsigned &a, unsigned &b, unsigned
 // for outstanding particle loads.
 #define GLOBAL __attribute__((address_space(1)))
 template <class T> __device__ __forceinline__ GLOBAL T *to_global(T *p) { return (GLOBAL T *)p; }
+template <class T> __device__ __forceinline__ GLOBAL T *to_global(const Dev<T> &p) { return (GLOBAL T *)p.at; }
 typedef int nt_i4 __attribute__((ext_vector_type(4)));
 typedef float nt_f4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float4 ld_f4(GLOBAL const float4 *p)

@@ -4025,6 +4025,9 @@ void launch_recycle(const PushArgs *A, const Tab &t, hipStream_t s)
     hipLaunchKernelGGL(k_recycle, dim3(tab_blocks(t)), dim3(256), 0, s, A, t);
 }
 
+// Bound by reading cells and velocities (12 bytes a slot).  A load behind a
+// test of the slot's cell, and one slot a round, ran at 1.7 TB/s (92M slots:
+// 657 us); all loads of eight slots at once: 190 us.
 __global__ __launch_bounds__(256) void k_kinetic(const PushArgs *A, int unit, double *part)
 {
     const PushArgs &aa = A[unit];
@@ -4033,8 +4036,24 @@ __global__ __launch_bounds__(256) void k_kinetic(const PushArgs *A, int unit, do
     const int32_t *cell = aa.cell[set];
     const float *vx = aa.vx[set], *vy = aa.vy[set];
     double s = 0.0;
-    for (long long p = (long long)blockIdx.x * 256 + threadIdx.x; p < n; p += (long long)gridDim.x * 256)
-        if (cell[p] >= 0) s += (double)vx[p] * vx[p] + (double)vy[p] * vy[p];
+    constexpr int U = 8;
+    const long long step = (long long)gridDim.x * 256;
+    for (long long p0 = (long long)blockIdx.x * 256 + threadIdx.x; p0 < n; p0 += U * step) {
+        int c[U];
+        float x[U], y[U];
+#pragma unroll
+        for (int k = 0; k < U; k++) {
+            const long long p = p0 + k * step < n ? p0 + k * step : p0;
+            c[k] = cell[p];
+            x[k] = vx[p];
+            y[k] = vy[p];
+        }
+#pragma unroll
+        for (int k = 0; k < U; k++) {
+            const double e = (double)x[k] * x[k] + (double)y[k] * y[k];
+            s += p0 + k * step < n && c[k] >= 0 ? e : 0.0;
+        }
+    }
     diag_block_sum(s, part);
 }
 
@@ -4052,24 +4071,30 @@ __global__ __launch_bounds__(256) void k_field_energy(const Inst *insts, int ins
     diag_block_sum(0.5 * s, part);
 }
 
-__global__ void k_sum_partials(const double *part, int n, double *out)
+// The kDiagBlocks partials in block order: one thread adds, from LDS (from
+// memory, a trip at a time, 31 us; 5.2 so).
+__global__ __launch_bounds__(256) void k_sum_partials(const double *part, double *out)
 {
+    __shared__ double sh[kDiagBlocks];
+    for (int k = threadIdx.x; k < kDiagBlocks; k += 256) sh[k] = part[k];
+    __syncthreads();
     if (threadIdx.x != 0) return;
     double s = 0.0;
-    for (int k = 0; k < n; k++) s += part[k];
+#pragma unroll 16
+    for (int k = 0; k < kDiagBlocks; k++) s += sh[k];
     *out = s;
 }
 
 void launch_kinetic(const PushArgs *A, int unit, double *part, double *out, hipStream_t s)
 {
     hipLaunchKernelGGL(k_kinetic, dim3(kDiagBlocks), dim3(256), 0, s, A, unit, part);
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(64), 0, s, part, kDiagBlocks, out);
+    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, s, part, out);
 }
 
 void launch_field_energy(const Inst *I, int inst, double *part, double *out, hipStream_t s)
 {
     hipLaunchKernelGGL(k_field_energy, dim3(kDiagBlocks), dim3(256), 0, s, I, inst, part);
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(64), 0, s, part, kDiagBlocks, out);
+    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, s, part, out);
 }
 
 // ---------------------------------------------------------------------------

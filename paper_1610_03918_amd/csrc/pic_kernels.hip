@@ -1869,7 +1869,8 @@ __device__ __forceinline__ void c_dense(const CLev &L, const float *__restrict__
     if (tid < 4 && n + tid < 4 * npc) L.g[n + tid] = 0.0f;
     __syncthreads();
     const float4 *g4 = (const float4 *)L.g;
-    for (int w = tid >> 6; w < kCoarseWaves; w += NW) {
+    // (the row addresses in scalar registers)
+    for (int w = uniform(tid >> 6); w < kCoarseWaves; w += NW) {
         float4 acc[Q];
 #pragma unroll
         for (int q = 0; q < Q; q++) acc[q] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -2037,6 +2038,184 @@ __device__ __forceinline__ void c_cycle(Lev lev, int nlev, float *sr, int px, in
     }
 }
 
+// Positions in a level's LDS arrays that one thread smooths, looked up once: NP
+// pairs of neighbours (i, 2j) and (i, 2j + 1), one red and one black.  The
+// phases compute them anew otherwise, 70 of 85 instructions a node.  Five words
+// a pair: the first node (16 bits), whether its row is odd, which of the two
+// are free and which exist; the nodes above and below the first; those left
+// and right of the pair; the four coarse nodes the red one's prolongation
+// reads.  A position past a row's end is read but never used.  Positions are
+// unpacked where they are used: kept unpacked they would not fit.
+template <int NP> struct Pairs {
+    unsigned p[NP], v[NP], h[NP], ca[NP], cb[NP];
+    int last;                          // this wavefront has pairs of the last round
+
+    __device__ __forceinline__ void find(int NX, int NY, int NXc, int NYc, int tid, int nt)
+    {
+        const int HW = (NY + 1) >> 1, n = NX * HW;
+        const float rcp = 1.0f / (float)HW;
+        last = uniform(tid) + (NP - 1) * nt < n;
+#pragma unroll
+        for (int k = 0; k < NP; k++) {
+            const int q = tid + k * nt, i = q < n ? div_rcp(q, rcp) : 0, j = q < n ? 2 * (q - i * HW) : 0;
+            const int I = i >> 1, J = j >> 1, I1 = wrap_hi(I + 1, NXc), J1 = wrap_hi(J + 1, NYc);
+            p[k] = (i * NY + j) | (unsigned)(i & 1) << 16 | (q < n ? 1u << 19 : 0u) | (q < n && j + 1 < NY ? 1u << 20 : 0u);
+            v[k] = (wrap_lo(i - 1, NX) * NY + j) | (unsigned)(wrap_hi(i + 1, NX) * NY + j) << 16;
+            h[k] = (i * NY + wrap_lo(j - 1, NY)) | (unsigned)(i * NY + (j + 2 < NY ? j + 2 : 0)) << 16;
+            ca[k] = (I * NYc + J) | (unsigned)(I1 * NYc + J) << 16;
+            cb[k] = (I * NYc + J1) | (unsigned)(I1 * NYc + J1) << 16;
+        }
+    }
+    // which nodes are free, once the level's mask is in LDS
+    __device__ __forceinline__ void mark(const uint8_t *f)
+    {
+        unsigned f0[NP], f1[NP];
+#pragma unroll
+        for (int k = 0; k < NP; k++) {
+            const int o = p[k] & 0xFFFFu;
+            f0[k] = f[o];
+            f1[k] = f[o + 1];
+        }
+#pragma unroll
+        for (int k = 0; k < NP; k++)
+            p[k] |= (p[k] >> 2) & ((f0[k] ? 0u : 1u << 17) | (f1[k] ? 0u : 1u << 18));   // of those that exist
+    }
+    struct At {
+        int o, up, dn, lf, rt;         // the node of the colour and its neighbours
+        bool free, in;
+    };
+    template <int COL> __device__ __forceinline__ At at(int k) const
+    {
+        const unsigned w = opaque(p[k]), t = ((w >> 16) & 1) ^ COL;   // 1: the pair's second node
+        const unsigned x = opaque(v[k]) + t * 0x10001u, y = opaque(h[k]);
+        At r;
+        r.o = (int)((w & 0xFFFFu) + t);
+        r.up = (int)(x & 0xFFFFu);
+        r.dn = (int)(x >> 16);
+        r.lf = t ? r.o - 1 : (int)(y & 0xFFFFu);
+        r.rt = t ? (int)(y >> 16) : r.o + 1;
+        r.free = (w >> (17 + t)) & 1;
+        r.in = (w >> (19 + t)) & 1;
+        return r;
+    }
+    // u = (g + four of src) / 4 at the free nodes of a colour (0 red)
+    template <int COL> __device__ __forceinline__ void sweep(const float *src, const float *g, float *u) const
+    {
+        float s[NP];
+#pragma unroll
+        for (int k = 0; k < NP; k++) {
+            if (NP > 1 && k == NP - 1 && !last) continue;
+            const At n = at<COL>(k);
+            s[k] = g[n.o];
+            s[k] += src[n.up];
+            s[k] += src[n.dn];
+            s[k] += src[n.lf];
+            s[k] += src[n.rt];
+        }
+#pragma unroll
+        for (int k = 0; k < NP; k++) {
+            if (NP > 1 && k == NP - 1 && !last) continue;
+            const unsigned w = opaque(p[k]), t = ((w >> 16) & 1) ^ COL;
+            if ((w >> (17 + t)) & 1) u[(w & 0xFFFFu) + t] = s[k] * 0.25f;
+        }
+    }
+    // red-from-zero start
+    __device__ __forceinline__ void start(const float *g, float *u) const
+    {
+#pragma unroll
+        for (int k = 0; k < NP; k++) {
+            const At r = at<0>(k), b = at<1>(k);
+            const float x = g[r.o] * 0.25f;
+            if (r.in) u[r.o] = r.free ? x : 0.0f;
+            if (b.in) u[b.o] = 0.0f;
+        }
+    }
+    // residual at the red nodes, 0 at fixed ones
+    __device__ __forceinline__ void resid_red(const float *u, const float *g, float *sr) const
+    {
+#pragma unroll
+        for (int k = 0; k < NP; k++) {
+            if (NP > 1 && k == NP - 1 && !last) continue;
+            const At n = at<0>(k);
+            float v = 4.0f * u[n.o];
+            v -= u[n.up];
+            v -= u[n.dn];
+            v -= u[n.lf];
+            v -= u[n.rt];
+            v = g[n.o] - v;
+            if (n.in) sr[n.o] = n.free ? v : 0.0f;
+        }
+    }
+    // red nodes with the prolonged coarse correction e, 0 at fixed ones
+    __device__ __forceinline__ void correct_red(const float *u, const float *e, float *sr) const
+    {
+#pragma unroll
+        for (int k = 0; k < NP; k++) {
+            if (NP > 1 && k == NP - 1 && !last) continue;
+            const unsigned w = opaque(p[k]), odd = (w >> 16) & 1, o = (w & 0xFFFFu) + odd;
+            const unsigned x = opaque(ca[k]), y = opaque(cb[k]);
+            const float c = e[x & 0xFFFFu];
+            const float m = 0.25f * (c + e[x >> 16] + e[y & 0xFFFFu] + e[y >> 16]);
+            const float v = u[o] + (odd ? m : c);
+            if ((w >> (19 + odd)) & 1) sr[o] = (w >> (17 + odd)) & 1 ? v : 0.0f;
+        }
+    }
+};
+
+// Positions of the red residuals that up to NC coarse nodes tid, tid + nt, ...
+// of a thread restrict: the centre (16 bits), whether the coarse node is red,
+// free, and exists; (-,-) and (-,+); (+,-) and (+,+).  Those outside a bounded
+// axis read node 0, which is red and lies on that axis' edge: a fixed node's
+// residual, 0.
+template <int NC> struct Restrict {
+    unsigned c[NC], a[NC], b[NC];
+
+    __device__ __forceinline__ void find(int NX, int NY, int NXc, int NYc, int px, int py, int tid, int nt)
+    {
+        const float rcp = 1.0f / (float)NYc;
+#pragma unroll
+        for (int k = 0; k < NC; k++) {
+            const bool in = tid + k * nt < NXc * NYc;
+            const int q = in ? tid + k * nt : 0, I = div_rcp(q, rcp), J = q - I * NYc, i = 2 * I, j = 2 * J;
+            const bool um = px || i > 0, up = px || i + 1 < NX, lm = py || j > 0, lp = py || j + 1 < NY;
+            const int rm = wrap_lo(i - 1, NX) * NY, rp = wrap_hi(i + 1, NX) * NY;
+            const int cm = wrap_lo(j - 1, NY), cp = wrap_hi(j + 1, NY);
+            c[k] = (i * NY + j) | (((I + J) & 1) == 0 ? 1u << 16 : 0u) | (in ? 1u << 18 : 0u);
+            a[k] = (unsigned)(um && lm ? rm + cm : 0) | (unsigned)(um && lp ? rm + cp : 0) << 16;
+            b[k] = (unsigned)(up && lm ? rp + cm : 0) | (unsigned)(up && lp ? rp + cp : 0) << 16;
+        }
+    }
+    __device__ __forceinline__ void mark(const uint8_t *fc, int tid, int nt)
+    {
+#pragma unroll
+        for (int k = 0; k < NC; k++) {
+            const bool in = (c[k] >> 18) & 1;
+            const int f = fc[in ? tid + k * nt : 0];
+            if (in && !f) c[k] |= 1u << 17;
+        }
+    }
+    __device__ __forceinline__ void run(const float *sr, float *g, float *u, int tid, int nt) const
+    {
+#pragma unroll
+        for (int k = 0; k < NC; k++) {
+            const unsigned z = opaque(c[k]), x = opaque(a[k]), y = opaque(b[k]);
+            float acc = 0.0f;
+            acc += 0.25f * sr[x & 0xFFFFu];
+            acc += 0.25f * sr[x >> 16];
+            acc += sr[z & 0xFFFFu];
+            acc += 0.25f * sr[y & 0xFFFFu];
+            acc += 0.25f * sr[y >> 16];
+            if ((z >> 17) & 1) {
+                g[tid + k * nt] = acc;
+                u[tid + k * nt] = (z >> 16) & 1 ? acc * 0.25f : 0.0f;
+            } else if ((z >> 18) & 1) {
+                g[tid + k * nt] = 0.0f;
+                u[tid + k * nt] = 0.0f;
+            }
+        }
+    }
+};
+
 // The levels from lg on: one 1024-thread work-group per instance, every level
 // in LDS.  Per level on the way down a black half-sweep, the red residuals,
 // their restriction to the next level with its red-from-zero start; on the
@@ -2050,6 +2229,14 @@ __device__ __forceinline__ void c_cycle(Lev lev, int nlev, float *sr, int px, in
 // inner stop test; one launch fewer per iteration.  The paired or single
 // fine levels between the two run on regardless (their output is then
 // unused).
+// NP > 0: the first two levels by positions looked up once (Pairs, Restrict),
+// NP pairs of the first a thread: a phase of a 65 x 65 level takes 1500 cycles
+// instead of 3000.  What is left is spread over the chain: loads and the
+// step's totals 9000 cycles, masks and start 5000, the first two levels 15000,
+// the levels below 8000, the exact solve 7000, each piece of code fetched for
+// one pass through it.  257 x 257 nodes (first level 65 x 65): 17.7 -> 15.8 us,
+// 1024 x 513 (128 x 65): 26.2 -> 24.0 us.
+template <int NP>
 __global__ __launch_bounds__(1024) void k_coarse(const Inst *insts, Tab t, Tab t0, Part pt, int fuse)
 {
     const Inst &I = insts[t.id[blockIdx.x]];
@@ -2103,6 +2290,28 @@ __global__ __launch_bounds__(1024) void k_coarse(const Inst *insts, Tab t, Tab t
     fetch(1, pv1, pd1);
     fetch(2, pv2, pd2);
     fetch(3, pv3, pd3);
+    // the coarsest level's inverse on its way to this die's cache: a word of
+    // every line (from other kernels' launches it is not there any more)
+    constexpr int kWarm = 5;
+    float warm_inv[kWarm];
+    const int lines = a.dense_n ? (int)((tri_off(a.dense_n) + 31) >> 5) : 0;
+    if (NP) {
+        const float *inv = a.ainv;
+#pragma unroll
+        for (int k = 0; k < kWarm; k++) warm_inv[k] = tid + k * 1024 < lines ? inv[(tid + k * 1024) * 32] : 0.0f;
+    }
+    // positions of the first two levels, looked up while the loads are under way
+    constexpr int NPA = NP ? NP : 1, NPB = NP > 3 ? 2 : 1, NCA = NP > 3 ? 3 : 2;
+    Pairs<NPA> P0;
+    Pairs<NPB> P1;
+    Restrict<NCA> R0;
+    Restrict<1> R1;
+    if (NP) {
+        P0.find(dims[0][0], dims[1][0], dims[0][1], dims[1][1], tid, 1024);
+        R0.find(dims[0][0], dims[1][0], dims[0][1], dims[1][1], px, py, tid, 1024);
+        P1.find(dims[0][1], dims[1][1], dims[0][2], dims[1][2], tid, 1024);
+        R1.find(dims[0][1], dims[1][1], dims[0][2], dims[1][2], px, py, tid, 1024);
+    }
     if (fuse) {
         // what k_finalize(OP_UPDATE) does after the level-0 CG step (t0: that
         // launch's units, in the same order as t): the totals of its partials
@@ -2120,7 +2329,9 @@ __global__ __launch_bounds__(1024) void k_coarse(const Inst *insts, Tab t, Tab t
                                 (double)(wf[F_ITER] + wf[F_ITER_TOT] + wf[F_PASSES]);
             asm volatile("" ::"v"(warm));
         }
-        partial_sums_256(pt, t0.boff[blockIdx.x], t0.boff[blockIdx.x + 1], 2, fsh, tid);
+        PartialSums<4> ps;
+        ps.load(pt, t0.boff[blockIdx.x], t0.boff[blockIdx.x + 1], 2, tid);
+        ps.sum(pt, t0.boff[blockIdx.x], t0.boff[blockIdx.x + 1], 2, fsh, tid);
         __syncthreads();
         if (tid == 0) {
             apply_op(I, OP_UPDATE, fsh[0][0] + fsh[0][1] + fsh[0][2] + fsh[0][3],
@@ -2151,36 +2362,94 @@ __global__ __launch_bounds__(1024) void k_coarse(const Inst *insts, Tab t, Tab t
     };
     float *sr = (float *)(lds + a.off_s);
     __syncthreads();
-    {
-        const CLev L = lev(0);
-        const int N = L.NX * L.NY;
-        const float rcp = 1.0f / (float)L.NY;
-        for (int k = tid; k < N; k += nt) {
-            const int i = div_rcp(k, rcp), j = k - i * L.NY;
-            L.u[k] = (!L.f[k] && ((i + j) & 1) == 0) ? L.g[k] * 0.25f : 0.0f;
-        }
-    }
-    __syncthreads();
-    c_cycle(lev, nlev, sr, px, py, a.sweeps, [&]() {
+    auto dense = [&]() __attribute__((always_inline)) {
         if (a.dense_n) c_dense_any(lev(nlev - 1), a.ainv, a.dense_n, (float *)(lds + a.off_p), tid);
         return a.dense_n != 0;
-    }, tid, nt);
+    };
+    const CLev A = lev(0);
+    if constexpr (NP > 0) {
+        const CLev B = lev(1), C = lev(2);
+#pragma unroll
+        for (int k = 0; k < kWarm; k++) asm volatile("" ::"v"(warm_inv[k]));
+        P0.mark(A.f);
+        R0.mark(B.f, tid, 1024);
+        P1.mark(B.f);
+        R1.mark(C.f, tid, 1024);
+        P0.start(A.g, A.u);
+        __syncthreads();
+        P0.template sweep<1>(A.u, A.g, A.u);
+        __syncthreads();
+        P0.resid_red(A.u, A.g, sr);
+        __syncthreads();
+        R0.run(sr, B.g, B.u, tid, 1024);
+        __syncthreads();
+        P1.template sweep<1>(B.u, B.g, B.u);
+        __syncthreads();
+        P1.resid_red(B.u, B.g, sr);
+        __syncthreads();
+        R1.run(sr, C.g, C.u, tid, 1024);
+        __syncthreads();
+        c_cycle([&](int l) __attribute__((always_inline)) { return lev(l + 2); }, nlev - 2, sr, px, py, a.sweeps, dense,
+                tid, nt);
+        P1.correct_red(B.u, C.u, sr);
+        __syncthreads();
+        P1.template sweep<1>(sr, B.g, B.u);
+        __syncthreads();
+        P1.template sweep<0>(B.u, B.g, B.u);
+        __syncthreads();
+        P0.correct_red(A.u, B.u, sr);
+        __syncthreads();
+        P0.template sweep<1>(sr, A.g, A.u);
+        __syncthreads();
+        P0.template sweep<0>(A.u, A.g, A.u);
+        __syncthreads();
+    } else {
+        const int N = A.NX * A.NY;
+        const float rcp = 1.0f / (float)A.NY;
+        for (int k = tid; k < N; k += nt) {
+            const int i = div_rcp(k, rcp), j = k - i * A.NY;
+            A.u[k] = (!A.f[k] && ((i + j) & 1) == 0) ? A.g[k] * 0.25f : 0.0f;
+        }
+        __syncthreads();
+        c_cycle(lev, nlev, sr, px, py, a.sweeps, dense, tid, nt);
+    }
     {
-        const int N = dims[0][0] * dims[1][0];
-        const float *u0 = (const float *)(lds + tab[0][0]);
-        for (int k = tid; k < N; k += nt) a.u_top[k] = u0[k];
+        const int N = A.NX * A.NY;
+        float *u = a.u_top;
+        for (int k = tid; k < N; k += nt) u[k] = A.u[k];
     }
 }
 
-void launch_coarse(const Inst *I, const Tab &t, int lds_bytes, const Tab &t0, Part pt, bool fuse, hipStream_t s)
+// The form of k_coarse for one instance: pairs of the first level a thread, 0
+// where the first two levels are not there, do not fit the registers, or wrap
+// an odd number of columns.
+int coarse_form(const CoarseArgs &c)
+{
+    if (c.nlev < 3 || (c.py && ((c.NY[0] | c.NY[1]) & 1))) return 0;
+    const int p0 = c.NX[0] * ((c.NY[0] + 1) / 2), p1 = c.NX[1] * ((c.NY[1] + 1) / 2);
+    const int n1 = c.NX[1] * c.NY[1], n2 = c.NX[2] * c.NY[2];
+    if (c.NX[0] * c.NY[0] > 65000 || n2 > 1024) return 0;
+    if (p0 <= 3 * 1024 && p1 <= 1024 && n1 <= 2 * 1024) return 3;
+    if (p0 <= 5 * 1024 && p1 <= 2 * 1024 && n1 <= 3 * 1024) return 5;
+    return 0;
+}
+
+void launch_coarse(const Inst *I, const Tab &t, int form, int lds_bytes, const Tab &t0, Part pt, bool fuse,
+                   hipStream_t s)
 {
     if (!t.n) return;
-    static int allowed = 64 * 1024;
-    if (lds_bytes > allowed) {
-        (void)hipFuncSetAttribute((const void *)k_coarse, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
-        allowed = lds_bytes;
+    const int f = form == 3 ? 1 : form == 5 ? 2 : 0;
+    static const void *const kernel[3] = {(const void *)k_coarse<0>, (const void *)k_coarse<3>,
+                                          (const void *)k_coarse<5>};
+    static int allowed[3] = {64 * 1024, 64 * 1024, 64 * 1024};
+    if (lds_bytes > allowed[f]) {
+        (void)hipFuncSetAttribute(kernel[f], hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+        allowed[f] = lds_bytes;
     }
-    hipLaunchKernelGGL(k_coarse, dim3(t.n), dim3(1024), lds_bytes, s, I, t, t0, pt, fuse ? 1 : 0);
+    const dim3 g(t.n), b(1024);
+    if (f == 1) hipLaunchKernelGGL(k_coarse<3>, g, b, lds_bytes, s, I, t, t0, pt, fuse ? 1 : 0);
+    else if (f == 2) hipLaunchKernelGGL(k_coarse<5>, g, b, lds_bytes, s, I, t, t0, pt, fuse ? 1 : 0);
+    else hipLaunchKernelGGL(k_coarse<0>, g, b, lds_bytes, s, I, t, t0, pt, fuse ? 1 : 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -2375,135 +2644,6 @@ __device__ void mg_dense_helper(const Inst &I, const MgSolveArgs &m, int h, unsi
     }
 }
 
-// Positions in a level's LDS arrays that one thread smooths: NP pairs of a red
-// and a black node (own -1: none, or fixed), the four neighbours x-1, x+1,
-// y-1, y+1 as 16-bit halves, for a red node also the coarse nodes its
-// prolongation reads (one where both indices are even).
-template <int NP> struct Pairs {
-    int red[NP], black[NP];
-    unsigned ra[NP], rb[NP], ba[NP], bb[NP], ca[NP], cb[NP];
-    unsigned one;
-
-    __device__ __forceinline__ void find(const uint8_t *f, int NX, int NY, int NXc, int NYc, int tid, int nt)
-    {
-        const int HW = (NY + 1) >> 1, n = NX * HW;
-        one = 0;
-#pragma unroll
-        for (int k = 0; k < NP; k++) {
-            const int q = tid + k * nt, i = q < n ? q / HW : 0, jj = q < n ? q - i * HW : 0;
-            const int jr = 2 * jj + (i & 1), jb = 2 * jj + ((i + 1) & 1);
-            const bool r = q < n && jr < NY, b = q < n && jb < NY;
-            const Nb x = nbs(i, r ? jr : 0, NX, NY), y = nbs(i, b ? jb : 0, NX, NY);
-            red[k] = r && !f[i * NY + jr] ? i * NY + jr : -1;
-            black[k] = b && !f[i * NY + jb] ? i * NY + jb : -1;
-            ra[k] = (x.im * NY + (r ? jr : 0)) | ((unsigned)(x.ip * NY + (r ? jr : 0)) << 16);
-            rb[k] = (i * NY + x.jm) | ((unsigned)(i * NY + x.jp) << 16);
-            ba[k] = (y.im * NY + (b ? jb : 0)) | ((unsigned)(y.ip * NY + (b ? jb : 0)) << 16);
-            bb[k] = (i * NY + y.jm) | ((unsigned)(i * NY + y.jp) << 16);
-            const int I = i >> 1, J = (r ? jr : 0) >> 1, I1 = wrap_hi(I + 1, NXc), J1 = wrap_hi(J + 1, NYc);
-            ca[k] = (I * NYc + J) | ((unsigned)(I1 * NYc + J) << 16);
-            cb[k] = (I * NYc + J1) | ((unsigned)(I1 * NYc + J1) << 16);
-            if (((i | jr) & 1) == 0) one |= 1u << k;
-        }
-    }
-    // u = (g + four of v) / 4 at the nodes own
-    __device__ __forceinline__ void sweep(const int (&own)[NP], const unsigned (&a)[NP], const unsigned (&b)[NP],
-                                          const float *v, const float *g, float *u) const
-    {
-        float s[NP];
-#pragma unroll
-        for (int k = 0; k < NP; k++) {
-            const int o = opaque(own[k]);
-            const unsigned x = opaque(a[k]), y = opaque(b[k]);
-            s[k] = g[o < 0 ? 0 : o];
-            s[k] += v[x & 0xFFFFu];
-            s[k] += v[x >> 16];
-            s[k] += v[y & 0xFFFFu];
-            s[k] += v[y >> 16];
-        }
-#pragma unroll
-        for (int k = 0; k < NP; k++) {
-            const int o = opaque(own[k]);
-            if (o >= 0) u[o] = s[k] * 0.25f;
-        }
-    }
-    __device__ __forceinline__ void resid_red(const float *u, const float *g, float *sr) const
-    {
-#pragma unroll
-        for (int k = 0; k < NP; k++) {
-            const int o = opaque(red[k]), p = o < 0 ? 0 : o;
-            const unsigned x = opaque(ra[k]), y = opaque(rb[k]);
-            float v = 4.0f * u[p];
-            v -= u[x & 0xFFFFu];
-            v -= u[x >> 16];
-            v -= u[y & 0xFFFFu];
-            v -= u[y >> 16];
-            v = g[p] - v;
-            if (o >= 0) sr[o] = v;
-        }
-    }
-    __device__ __forceinline__ void correct_red(const float *u, const float *e, float *sr) const
-    {
-#pragma unroll
-        for (int k = 0; k < NP; k++) {
-            const int o = opaque(red[k]), p = o < 0 ? 0 : o;
-            const unsigned x = opaque(ca[k]), y = opaque(cb[k]);
-            const float c = e[x & 0xFFFFu];
-            const float m = 0.25f * (c + e[x >> 16] + e[y & 0xFFFFu] + e[y >> 16]);
-            const float v = u[p] + ((one >> k) & 1 ? c : m);
-            if (o >= 0) sr[o] = v;
-        }
-    }
-};
-
-// Positions of the red residuals that up to NC coarse nodes of a thread
-// restrict (none, the position of a zero, for those outside a bounded axis).
-template <int NC> struct Restrict {
-    int own[NC];                       // -1: none, or fixed
-    unsigned c[NC], a[NC], b[NC], red; // centre, (-,-) and (-,+), (+,-) and (+,+); bit k: a red coarse node
-
-    __device__ __forceinline__ void find(const uint8_t *fc, int NX, int NY, int NXc, int NYc, int px, int py,
-                                         int none, int tid, int nt)
-    {
-        red = 0;
-#pragma unroll
-        for (int k = 0; k < NC; k++) {
-            const int q = tid + k * nt, I = q < NXc * NYc ? q / NYc : 0, J = q < NXc * NYc ? q - I * NYc : 0;
-            own[k] = q < NXc * NYc && !fc[q] ? q : -1;
-            auto at = [&](int di, int dj) -> unsigned {
-                int i = 2 * I + di, j = 2 * J + dj;
-                if (px) i = wrap_hi(wrap_lo(i, NX), NX);
-                else if (i < 0 || i >= NX) return none;
-                if (py) j = wrap_hi(wrap_lo(j, NY), NY);
-                else if (j < 0 || j >= NY) return none;
-                return i * NY + j;
-            };
-            c[k] = at(0, 0);
-            a[k] = at(-1, -1) | (at(-1, 1) << 16);
-            b[k] = at(1, -1) | (at(1, 1) << 16);
-            if (((I + J) & 1) == 0) red |= 1u << k;
-        }
-    }
-    __device__ __forceinline__ void run(const float *sr, float *g, float *u) const
-    {
-#pragma unroll
-        for (int k = 0; k < NC; k++) {
-            const int o = opaque(own[k]);
-            const unsigned x = opaque(a[k]), y = opaque(b[k]), z = opaque(c[k]);
-            float acc = 0.0f;
-            acc += 0.25f * sr[x & 0xFFFFu];
-            acc += 0.25f * sr[x >> 16];
-            acc += sr[z];
-            acc += 0.25f * sr[y & 0xFFFFu];
-            acc += 0.25f * sr[y >> 16];
-            if (o >= 0) {
-                g[o] = acc;
-                u[o] = (red >> k) & 1 ? acc * 0.25f : 0.0f;
-            }
-        }
-    }
-};
-
 template <int NT, bool HELP>
 __global__ __launch_bounds__(kMgThreads, 2) void k_mg_solve(const Inst *insts, MgSolveArgs m)
 {
@@ -2574,13 +2714,15 @@ __global__ __launch_bounds__(kMgThreads, 2) void k_mg_solve(const Inst *insts, M
     Pairs<NT1> P1;
     Restrict<NC> R0;
     Restrict<1> R1;
-    P0.find(f0, NX, NY, tab[3][0], tab[4][0], tid, nt);
-    R0.find(lds + tab[2][0], NX, NY, tab[3][0], tab[4][0], px, py, N0, tid, nt);
+    P0.find(NX, NY, tab[3][0], tab[4][0], tid, nt);
+    P0.mark(f0);
+    R0.find(NX, NY, tab[3][0], tab[4][0], px, py, tid, nt);
+    R0.mark(lds + tab[2][0], tid, nt);
     if (nlev > 1) {
-        P1.find(lds + tab[2][0], tab[3][0], tab[4][0], tab[3][1], tab[4][1], tid, nt);
-        R1.find(lds + tab[2][1], tab[3][0], tab[4][0], tab[3][1], tab[4][1], px, py, (m.off_s - a.off_s) / 4 + N0, tid, nt);
-        const CLev C = lev(1);
-        for (int k = tid; k < C.NX * C.NY; k += nt) C.u[k] = C.g[k] = 0.0f;
+        P1.find(tab[3][0], tab[4][0], tab[3][1], tab[4][1], tid, nt);
+        P1.mark(lds + tab[2][0]);
+        R1.find(tab[3][0], tab[4][0], tab[3][1], tab[4][1], px, py, tid, nt);
+        R1.mark(lds + tab[2][1], tid, nt);
     }
     // own nodes: row and column of slot q (0, 0 where the thread has none there)
     unsigned freeb = 0, redb = 0, inb = 0;
@@ -2663,36 +2805,36 @@ __global__ __launch_bounds__(kMgThreads, 2) void k_mg_solve(const Inst *insts, M
     };
     // V-cycle of the right-hand side g0 from the red-from-zero start in u0
     auto cycle = [&]() __attribute__((always_inline)) {
-        P0.sweep(P0.black, P0.ba, P0.bb, u0, g0, u0);
+        P0.template sweep<1>(u0, g0, u0);
         __syncthreads();
         P0.resid_red(u0, g0, sr0);
         __syncthreads();
-        R0.run(sr0, g1, u1);
+        R0.run(sr0, g1, u1, tid, nt);
         __syncthreads();
         const int deep = nlev > 1;
         if (deep) {
-            P1.sweep(P1.black, P1.ba, P1.bb, u1, g1, u1);
+            P1.template sweep<1>(u1, g1, u1);
             __syncthreads();
             P1.resid_red(u1, g1, sr1);
             __syncthreads();
             const CLev C = lev(1);
-            R1.run(sr1, C.g, C.u);
+            R1.run(sr1, C.g, C.u, tid, nt);
             __syncthreads();
         }
         deeper(deep);
         if (deep) {
             P1.correct_red(u1, lev(1).u, sr1);
             __syncthreads();
-            P1.sweep(P1.black, P1.ba, P1.bb, sr1, g1, u1);
+            P1.template sweep<1>(sr1, g1, u1);
             __syncthreads();
-            P1.sweep(P1.red, P1.ra, P1.rb, u1, g1, u1);
+            P1.template sweep<0>(u1, g1, u1);
             __syncthreads();
         }
         P0.correct_red(u0, u1, sr0);
         __syncthreads();
-        P0.sweep(P0.black, P0.ba, P0.bb, sr0, g0, u0);
+        P0.template sweep<1>(sr0, g0, u0);
         __syncthreads();
-        P0.sweep(P0.red, P0.ra, P0.rb, u0, g0, u0);
+        P0.template sweep<0>(u0, g0, u0);
         __syncthreads();
     };
     int turn = 0;
@@ -2946,6 +3088,7 @@ MgPlan mg_solve_plan(int NX, int NY, const CoarseArgs &c, int lg)
     p.tiles = p.tiles_y * ((NX + kMgTile - 1) / kMgTile);
     const int nvb = ((NY + kGridBX - 1) / kGridBX) * ((NX + kGridBY - 1) / kGridBY);
     if (lg != 1 || p.tiles > 4 || nvb > 256) return p;
+    if (c.py && ((NY | (c.nlev > 1 ? c.NY[0] : 0)) & 1)) return p;      // the pairs of Pairs wrap whole
     p.R = p.tiles <= 2 ? 2 : 4;
     // what a thread's registers hold of levels 0 and 1
     if (NX * ((NY + 1) / 2) > p.R * kMgThreads || c.NX[0] * ((c.NY[0] + 1) / 2) > (p.R / 4 + 1) * kMgThreads ||

@@ -309,7 +309,7 @@ struct pic_ctx {
     Tab t_plain{};                 // level-0 grid of the instances solved by plain CG
     Tab t_fine[kMaxLev] = {};      // 32 x 32 tiles of the fine multigrid levels handled one at a time
     Tab t_pair[kMaxLev] = {};      // 32 x 32 tiles of level l + 1 for levels l, l + 1 in one launch
-    int maxlg = 0, coarse_lds = 0, any_mg = 0;
+    int maxlg = 0, coarse_lds = 0, coarse_frm = 0, any_mg = 0;   // coarse_frm: coarse_form of every instance, or 0
     int pair_levels = 1;           // fine levels 1, 2 (3, 4, ...) two per launch
     size_t push_lds = 0;
     int unroll = 2, merge = 0;
@@ -662,7 +662,7 @@ void enqueue_vcycle_mid(pic_ctx *c, bool fuse_update, hipStream_t s)
 {
     Part pt = part_of(c);
     for (int l = 1; l < c->maxlg; l++) launch_mg_mid(c->d_inst, c->t_pair[l], c->t_fine[l], l, true, s);
-    launch_coarse(c->d_inst, c->t_coarse, c->coarse_lds, c->t_fine[0], pt, fuse_update, s);
+    launch_coarse(c->d_inst, c->t_coarse, c->coarse_frm, c->coarse_lds, c->t_fine[0], pt, fuse_update, s);
     for (int l = c->maxlg - 1; l >= 1; l--) launch_mg_mid(c->d_inst, c->t_pair[l], c->t_fine[l], l, false, s);
 }
 
@@ -1394,6 +1394,8 @@ void build_tabs(pic_ctx *c)
     for (int l = 0; l < kMaxLev; l++) c->t_fine[l] = c->t_pair[l] = Tab{};
     c->maxlg = 0;
     c->coarse_lds = 0;
+    c->coarse_frm = 0;
+    bool formless = false;
     c->any_mg = 0;
     c->push_lds = 0;
     for (int k = 0; k < c->n; k++) {
@@ -1421,6 +1423,9 @@ void build_tabs(pic_ctx *c)
             }
             tab_add(c->t_coarse, k, 1);
             c->coarse_lds = std::max(c->coarse_lds, h.dev.coarse.lds_bytes);
+            const int form = coarse_form(h.dev.coarse);
+            formless = formless || !form;
+            c->coarse_frm = formless ? 0 : std::max(c->coarse_frm, form);
         }
         for (int s = 0; s < 2; s++) {
             tab_add(c->t_push, 2 * k + s, (int)L.max_blocks[s]);

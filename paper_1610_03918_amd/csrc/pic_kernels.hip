@@ -326,21 +326,20 @@ __device__ __forceinline__ float2 node_field(const Geom g, const uint8_t *nc, co
 {
     const int NX = g.NX, NY = g.NY;
     const long long n = (long long)i * NY + j;
-    const bool fixed = nc[n] != 0;
-    const double pc = phi[n];
-    bool hm = g.px || i > 0, hp = g.px || i < NX - 1;
-    int im = g.px ? wrap_lo(i - 1, NX) : i - 1, ip = g.px ? wrap_hi(i + 1, NX) : i + 1;
-    double pm = hm ? phi[(long long)im * NY + j] : 0.0;
-    double pp = hp ? phi[(long long)ip * NY + j] : 0.0;
-    bool fm = hm && nc[(long long)im * NY + j] == 0;
-    bool fp = hp && nc[(long long)ip * NY + j] == 0;
+    // all loads at once: a neighbour that is not there is the wrapped one, not used
+    const int im = wrap_lo(i - 1, NX), ip = wrap_hi(i + 1, NX), jm = wrap_lo(j - 1, NY), jp = wrap_hi(j + 1, NY);
+    const long long a = (long long)im * NY + j, c = (long long)ip * NY + j;
+    const long long d = (long long)i * NY + jm, e = (long long)i * NY + jp;
+    const uint8_t cn = nc[n], ca = nc[a], cc = nc[c], cd = nc[d], ce = nc[e];
+    const double pc = phi[n], pa = phi[a], pp_ = phi[c], pd = phi[d], pe = phi[e];
+    const bool fixed = cn != 0;
+    const bool hm = g.px || i > 0, hp = g.px || i < NX - 1;
+    const double pm = hm ? pa : 0.0, pp = hp ? pp_ : 0.0;
+    const bool fm = hm && ca == 0, fp = hp && cc == 0;
     double ex = axis_field(pm, pc, pp, hm, hp, fm, fp, fixed);
-    bool gm = g.py || j > 0, gp = g.py || j < NY - 1;
-    int jm = g.py ? wrap_lo(j - 1, NY) : j - 1, jp = g.py ? wrap_hi(j + 1, NY) : j + 1;
-    double qm = gm ? phi[(long long)i * NY + jm] : 0.0;
-    double qp = gp ? phi[(long long)i * NY + jp] : 0.0;
-    bool em = gm && nc[(long long)i * NY + jm] == 0;
-    bool ep = gp && nc[(long long)i * NY + jp] == 0;
+    const bool gm = g.py || j > 0, gp = g.py || j < NY - 1;
+    const double qm = gm ? pd : 0.0, qp = gp ? pe : 0.0;
+    const bool em = gm && cd == 0, ep = gp && ce == 0;
     double ey = axis_field(qm, pc, qp, gm, gp, em, ep, fixed);
     return make_float2((float)ex, (float)ey);
 }
@@ -417,29 +416,34 @@ __global__ void k_assemble(const Inst *insts, Tab t, const double *Vtab, const l
     const double *V = Vtab + (row * ninst + t.id[ku]) * 8;
     double bb = 0.0, sm = 0.0;
     if (inb) {
+        // all loads at once; a bounded edge's nodes are conductors, so that the
+        // wrapped neighbours there are not used
         const uint8_t *nc = I.node_cond;
-        const int c = nc[n];
+        const int im = wrap_lo(i - 1, NX), ip = wrap_hi(i + 1, NX);
+        const int jm = wrap_lo(j - 1, NY), jp = wrap_hi(j + 1, NY);
+        const int c = nc[n], c0 = nc[(long long)im * NY + j], c1 = nc[(long long)ip * NY + j];
+        const int c2 = nc[(long long)i * NY + jm], c3 = nc[(long long)i * NY + jp];
+        const unsigned long long n0 = I.rho[0][n], n1 = I.rho[1][n];
+        const uint8_t fixed = I.lev[0].fix[n];
+        const double v0 = V[c0], v1 = V[c1], v2 = V[c2], v3 = V[c3];
         if (c) {
             I.b[n] = V[c];
             I.phi[n] = V[c];
         } else {
-            long long Ni = (long long)I.rho[1][n];
+            long long Ni = (long long)n1;
             if (I.charge_mode == 2 && i == I.charge_row) {
                 const int jl = g.py ? wrap_lo(j - 1, g.ny) : j - 1;
                 if (j < g.ny) Ni += (long long)I.surf[j] << 31;
                 if (jl >= 0) Ni += (long long)I.surf[jl] << 31;
             }
-            double r = (double)(Ni - (long long)I.rho[0][n]) * I.qcharge;
+            double r = (double)(Ni - (long long)n0) * I.qcharge;
             if (I.charge_mode == 1 && i == I.charge_row && j >= I.sjl && j <= I.sjh) r += I.sden;
-            const int im = g.px ? wrap_lo(i - 1, NX) : i - 1, ip = g.px ? wrap_hi(i + 1, NX) : i + 1;
-            const int jm = g.py ? wrap_lo(j - 1, NY) : j - 1, jp = g.py ? wrap_hi(j + 1, NY) : j + 1;
-            int cn;
-            if ((cn = nc[(long long)im * NY + j])) r += V[cn];
-            if ((cn = nc[(long long)ip * NY + j])) r += V[cn];
-            if ((cn = nc[(long long)i * NY + jm])) r += V[cn];
-            if ((cn = nc[(long long)i * NY + jp])) r += V[cn];
+            r = c0 ? r + v0 : r;
+            r = c1 ? r + v1 : r;
+            r = c2 ? r + v2 : r;
+            r = c3 ? r + v3 : r;
             I.b[n] = r;
-            if (!I.lev[0].fix[n]) bb = r * r;
+            if (!fixed) bb = r * r;
             sm = r;
         }
     }
@@ -543,9 +547,11 @@ __global__ void k_extrapolate(const Inst *insts, Tab t, int have_prev)
 {
     GRID_BEGIN(t)
     NODE_IDX(I.g.NX, I.g.NY)
-    if (!inb || (I.lev[0].fix[n] && !(I.g.px && I.g.py))) return;
-    const double v = I.phi[n];
-    if (have_prev) I.phi[n] = 2.0 * v - I.phi_prev[n];
+    if (!inb) return;
+    const uint8_t fixed = I.lev[0].fix[n];
+    const double v = I.phi[n], u = have_prev ? I.phi_prev[n] : 0.0;
+    if (fixed && !(I.g.px && I.g.py)) return;
+    if (have_prev) I.phi[n] = 2.0 * v - u;
     I.phi_prev[n] = v;
 }
 
@@ -570,23 +576,22 @@ __global__ void k_resid64(const Inst *insts, Tab t, int after_pass, Part pt)
     const double *phi = I.phi;
     double rr = 0.0, bsq = 0.0;
     if (inb) {
-        if (fix[n]) {
-            I.lev[0].g[n] = 0.0f;
-        } else {
-            bsq = I.b[n] * I.b[n];
-            const int im = wrap_lo(i - 1, NX), ip = wrap_hi(i + 1, NX);
-            const int jm = wrap_lo(j - 1, NY), jp = wrap_hi(j + 1, NY);
-            const long long a = (long long)im * NY + j, c = (long long)ip * NY + j;
-            const long long d = (long long)i * NY + jm, e = (long long)i * NY + jp;
-            double s = 4.0 * phi[n];
-            if (!fix[a]) s -= phi[a];
-            if (!fix[c]) s -= phi[c];
-            if (!fix[d]) s -= phi[d];
-            if (!fix[e]) s -= phi[e];
-            const double r = I.b[n] - s;
-            I.lev[0].g[n] = (float)r;
-            rr = r * r;
-        }
+        // all loads at once (a neighbour's potential behind the test of its mask, four in turn: 5.7 us at 257 x 257)
+        const int im = wrap_lo(i - 1, NX), ip = wrap_hi(i + 1, NX);
+        const int jm = wrap_lo(j - 1, NY), jp = wrap_hi(j + 1, NY);
+        const long long a = (long long)im * NY + j, c = (long long)ip * NY + j;
+        const long long d = (long long)i * NY + jm, e = (long long)i * NY + jp;
+        const uint8_t fn = fix[n], fa = fix[a], fc = fix[c], fd = fix[d], fe = fix[e];
+        const double pn = phi[n], pa = phi[a], pc = phi[c], pd = phi[d], pe = phi[e], b = I.b[n];
+        double s = 4.0 * pn;
+        s = fa ? s : s - pa;
+        s = fc ? s : s - pc;
+        s = fd ? s : s - pd;
+        s = fe ? s : s - pe;
+        const double r = fn ? 0.0 : b - s;
+        I.lev[0].g[n] = (float)r;
+        bsq = fn ? 0.0 : b * b;
+        rr = r * r;
     }
     double v[2] = {rr, bsq};
     block_partials<2>(v, pt);
@@ -665,7 +670,10 @@ __global__ void k_phi_update(const Inst *insts, Tab t)
     GRID_BEGIN(t)
     if (I.F[F_SKIP] || I.F[F_CGABORT]) return;
     NODE_IDX(I.g.NX, I.g.NY)
-    if (inb && !I.lev[0].fix[n]) I.phi[n] += (double)I.e[n];
+    if (!inb) return;
+    const uint8_t fixed = I.lev[0].fix[n];
+    const double sum = I.phi[n] + (double)I.e[n];
+    if (!fixed) I.phi[n] = sum;
 }
 
 void launch_phi_update(const Inst *I, const Tab &t, hipStream_t s)
@@ -2878,19 +2886,17 @@ __global__ __launch_bounds__(kMgThreads, 2) void k_mg_solve(const Inst *insts, M
                 const int i = byb * kGridBY + r, n = i * NY + j;
                 x[r] = 0.0;
                 if (i >= NX || j >= NY) continue;
-                if (f0[n]) {
-                    L0.g[n] = 0.0f;
-                    continue;
-                }
                 const int im = wrap_lo(i - 1, NX), ip = wrap_hi(i + 1, NX);
                 const int jm = wrap_lo(j - 1, NY), jp = wrap_hi(j + 1, NY);
+                const int a = im * NY + j, c = ip * NY + j, d = i * NY + jm, e = i * NY + jp;
                 const double *phi = I.phi;
-                double s = 4.0 * phi[n];
-                if (!f0[im * NY + j]) s -= phi[im * NY + j];
-                if (!f0[ip * NY + j]) s -= phi[ip * NY + j];
-                if (!f0[i * NY + jm]) s -= phi[i * NY + jm];
-                if (!f0[i * NY + jp]) s -= phi[i * NY + jp];
-                const double res = I.b[n] - s;
+                const double pn = phi[n], pa = phi[a], pc = phi[c], pd = phi[d], pe = phi[e], b = I.b[n];
+                double s = 4.0 * pn;
+                s = f0[a] ? s : s - pa;
+                s = f0[c] ? s : s - pc;
+                s = f0[d] ? s : s - pd;
+                s = f0[e] ? s : s - pe;
+                const double res = f0[n] ? 0.0 : b - s;
                 L0.g[n] = (float)res;
                 x[r] = res * res;
             }

@@ -2467,7 +2467,7 @@ void launch_coarse(const Inst *I, const Tab &t, int form, int lds_bytes, const T
 //
 // Launched kernel by kernel a V-cycle of a small grid is three launches and a
 // pass several more, bound by the launches and by k_coarse on one CU (42 us a
-// V-cycle at 81 x 30 nodes, 34 us at 64 x 64; here 19.3 and 19.3).  Arithmetic
+// V-cycle at 81 x 30 nodes, 34 us at 64 x 64; here 17.9 and 19.2).  Arithmetic
 // and the order of every addition are those of k_mg_down, k_coarse, k_mg_up,
 // k_phi_update, k_resid64 and k_finalize, and the iterations a pass may take
 // follow the host's rule, so the potential is the same bit for bit.

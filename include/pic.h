@@ -103,7 +103,8 @@ typedef struct {
     int32_t sort_interval[2];    /* steps between re-binnings per species (0 = at init only) */
     int32_t tile_x, tile_y;      /* particle tile in cells (powers of two; 0 = 16) */
     int32_t halo;                /* cells of drift a tile absorbs before a global fallback (0 = 4) */
-    int32_t chunk;               /* most particles per thread block (0 = 8192; at most 8192); few particles get smaller blocks */
+    int32_t chunk;               /* particles per thread block, 256 .. 8192 (0 = 4096, or as many whole passes
+                                    of 1024 as give the chip 1024 blocks of all the context's particles) */
     int32_t push_unroll;         /* particles per thread per pass of the push loop: 1, 2, 4 (0 = 4;
                                     4 moves 4 consecutive particles with 16-byte accesses) */
     int32_t push_merge;          /* distinct cells summed per wavefront before LDS atomics: 0, 2, 4 */
@@ -277,6 +278,10 @@ pic_status pic_tune(pic_ctx *ctx, int32_t push_unroll, int32_t push_merge, int32
  * Waits for the stream and drops every captured graph.  PIC_ERR_ARG for on
  * outside {0, 1}. */
 pic_status pic_set_level_pairs(pic_ctx *ctx, int32_t on);
+
+/* Particles per thread block of instance `instance`'s pushes: the
+ * configuration's chunk, or what the library chose where that is 0. */
+pic_status pic_push_chunk(pic_ctx *ctx, int32_t instance, int32_t *chunk);
 
 /* How a context of one instance runs its CG solves: 1 (the default) in one
  * launch where the grid allows it (plain CG, i.e. solver 1 or a grid that

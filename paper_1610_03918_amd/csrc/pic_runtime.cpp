@@ -26,6 +26,9 @@ constexpr int kCoarseMaxNodes = 12288;  // largest level solved inside one work-
 constexpr int kCoarseMaxLds = 159 * 1024;   // dynamic LDS of the coarse kernel (160 KiB per work-group)
 constexpr int kDenseTruncNodes = 256;       // coarsest level at most this size (see make_layout)
 constexpr int kMaxTiming = 512;
+constexpr int kPushFill = 1024;    // push blocks that fill the chip: four a compute unit
+constexpr int kPushPass = 4 * kPushThreads;   // particles a block moves in one pass
+constexpr int kPushChunk = 4096;   // particles per block where there are enough of them
 
 struct Layout {
     int nx, ny, NX, NY, px, py;
@@ -34,9 +37,12 @@ struct Layout {
     int lg = 0;                             // first level handled by the coarse kernel
     bool mg = false;
     int dense_n = 0;                        // nodes of a coarsest level solved with its inverse (0: sweeps)
-    int TX, TY, lx, ly, tiles_x, tiles_y, ntiles, H, chunk;
+    int TX, TY, lx, ly, tiles_x, tiles_y, ntiles, H;
+    int chunk = 0;                          // particles per push block; where the caller leaves the choice,
+                                            //   set once the context's particles are known (set_chunk)
     int unroll, merge;                      // push kernel variant
-    long long max_blocks[2];
+    long long table_blocks[2];              // push blocks the workspace has room for
+    long long max_blocks[2];                // push blocks of a launch (set_chunk)
     int grid_blocks;                        // blocks of the largest grid kernel
 };
 
@@ -90,7 +96,7 @@ std::string validate(const pic_config *c, const int64_t *cap)
     if ((tx & (tx - 1)) || (ty & (ty - 1)) || tx > 256 || ty > 256) return "tile sizes must be powers of two <= 256";
     int H = c->halo ? c->halo : 4;
     if (H < 0 || H > 64) return "halo out of range";
-    int chunk = c->chunk ? c->chunk : 8192;
+    int chunk = c->chunk ? c->chunk : kPushChunk;
     if (chunk < 256 || chunk > 8192) return "chunk must be in 256..8192";
     if (c->push_unroll != 0 && c->push_unroll != 1 && c->push_unroll != 2 && c->push_unroll != 4)
         return "push_unroll must be 0 (default), 1, 2 or 4";
@@ -154,8 +160,32 @@ bool node_map(const pic_config *c, std::vector<uint8_t> &nc)
     return ok;
 }
 
-constexpr int kPushFill = 1024;    // push blocks that fill the chip: four a compute unit
-constexpr int kPushPass = 4 * kPushThreads;   // particles a block moves in one pass
+// Particles per push block of a context that holds `particles` in all
+// instances and species (one launch covers them): whole passes of a block,
+// as many as still give the chip kPushFill blocks.  us a push in blocks of
+// 1024 / 2048 / 3072 / 4096, one instance: the paper's 80 x 30 trench (420,000
+// particles) 19.1 / 23.4 / 27.3 / 32.2; trenches 256 x 128 of 1.4M 25.4 / 28.4 /
+// 31.7 / 34.4, of 2.3M 38.7 / 33.4 / 37.0 / 39.7, of 3.7M 50.7 / 48.5 / 48.0 / 47.2.
+// A step of six grids in one launch (90M particles) 1713 / 1519 / 1521 / 1513.
+int fill_chunk(long long particles)
+{
+    const long long passes = particles / ((long long)kPushFill * kPushPass);
+    return (int)std::min<long long>(kPushChunk, std::max<long long>(1, passes) * kPushPass);
+}
+
+long long push_blocks(const Layout &L, const pic_config *c, int species, long long capacity, int chunk)
+{
+    // appended electrons (secondary emission) get blocks of their own after
+    // the binned ones: at most two more than a full binning would need
+    return L.ntiles + (capacity + chunk - 1) / chunk + (species == 0 && see_on(c) ? 2 : 0);
+}
+
+// The push blocks of a launch, once the context's particles are known.
+void set_chunk(Layout &L, const pic_config *c, const int64_t *cap, long long particles)
+{
+    L.chunk = c->chunk ? c->chunk : fill_chunk(particles);
+    for (int s = 0; s < 2; s++) L.max_blocks[s] = push_blocks(L, c, s, cap[s], L.chunk);
+}
 
 Layout make_layout(const pic_config *c, const int64_t *cap)
 {
@@ -216,18 +246,11 @@ Layout make_layout(const pic_config *c, const int64_t *cap)
     L.tiles_y = (L.ny + L.TY - 1) / L.TY;
     L.ntiles = L.tiles_x * L.tiles_y;
     L.H = c->halo ? c->halo : 4;
-    // few particles: blocks of at most the caller's chunk that still give the
-    // chip kPushFill of them, and no less than one pass of a block (the paper's
-    // 80 x 30 trench, 480,000 particles: 120 blocks of 4096, 27.8 us a push; 470 of
-    // 1024, 16.7)
-    const long long fill = ((cap[0] + cap[1]) / kPushFill + 255) / 256 * 256;
-    L.chunk = (int)std::min<long long>(c->chunk ? c->chunk : 8192, std::max<long long>(kPushPass, fill));
     L.unroll = c->push_unroll ? c->push_unroll : 4;
     L.merge = c->push_merge;
-    for (int s = 0; s < 2; s++) L.max_blocks[s] = L.ntiles + (cap[s] + L.chunk - 1) / L.chunk;
-    // appended electrons (secondary emission) get blocks of their own after
-    // the binned ones: at most two more than a full binning would need
-    if (see_on(c)) L.max_blocks[0] += 2;
+    // where the library chooses, room for its smallest blocks
+    for (int s = 0; s < 2; s++)
+        L.table_blocks[s] = push_blocks(L, c, s, cap[s], c->chunk ? c->chunk : kPushPass);
     int maxrows = std::max(L.NX, L.nx), maxcols = std::max(L.NY, L.ny);
     L.grid_blocks = ((maxcols + kGridBX - 1) / kGridBX) * ((maxrows + kGridBY - 1) / kGridBY);
     return L;
@@ -497,7 +520,7 @@ void carve_inst(InstHost *h, Carve &w, const Layout &L, const pic_config *cfg, c
         offs[s] = w.take<unsigned>(L.ntiles);
         curs[s] = w.take<unsigned>(L.ntiles);
         boff[s] = w.take<unsigned>(L.ntiles);
-        table[s] = w.take<int4>((size_t)L.max_blocks[s]);
+        table[s] = w.take<int4>((size_t)L.table_blocks[s]);
         info[s] = w.take<long long>(8);
     }
     unsigned long long *tally = w.take<unsigned long long>(2 * kNClass);
@@ -1152,7 +1175,8 @@ pic_status check(pic_ctx *c)
     return PIC_OK;
 }
 
-pic_status init_instance(pic_ctx *c, int k, const pic_config *cfg, const pic_buffers *buf)
+// particles: of every instance and species of the context
+pic_status init_instance(pic_ctx *c, int k, const pic_config *cfg, const pic_buffers *buf, long long particles)
 {
     InstHost &h = c->in[k];
     const int64_t cap[2] = {buf->sp[0].capacity, buf->sp[1].capacity};
@@ -1164,6 +1188,7 @@ pic_status init_instance(pic_ctx *c, int k, const pic_config *cfg, const pic_buf
     if (!node_map(&h.cfg, h.node_cond))
         return fail(c, PIC_ERR_ARG, "two different conductors meet at a node");
     h.L = make_layout(&h.cfg, cap);
+    set_chunk(h.L, &h.cfg, cap, particles);
     const Layout &L = h.L;
     h.buf = *buf;
     h.g = Geom{L.nx, L.ny, L.NX, L.NY, L.px, L.py};
@@ -1510,8 +1535,10 @@ pic_status batch_init(int n, const pic_config *cfgs, const pic_buffers *bufs, vo
     HIPCHK(c, hipMemsetAsync(c->d_F, 0, sizeof(int) * n * F_NFLAG, s));
     c->flags_bytes = (size_t)((char *)(c->d_F + (size_t)n * F_NFLAG) - (char *)c->d_S);
     HIPCHK(c, hipHostMalloc((void **)&c->h_flags, c->flags_bytes, hipHostMallocDefault));
+    long long particles = 0;
+    for (int k = 0; k < n; k++) particles += bufs[k].sp[0].count + bufs[k].sp[1].count;
     for (int k = 0; k < n; k++) {
-        pic_status st = init_instance(c, k, &cfgs[k], &bufs[k]);
+        pic_status st = init_instance(c, k, &cfgs[k], &bufs[k], particles);
         if (st != PIC_OK) return st;
     }
     for (int k = 0; k < n; k++) {
@@ -1769,6 +1796,14 @@ pic_status pic_tune(pic_ctx *c, int32_t push_unroll, int32_t push_merge, int32_t
     // captured steps embed the push variant and the re-binning points
     for (auto &kv : c->step_graphs) (void)hipGraphExecDestroy(kv.second);
     c->step_graphs.clear();
+    return PIC_OK;
+}
+
+pic_status pic_push_chunk(pic_ctx *c, int32_t instance, int32_t *chunk)
+{
+    if (!c || !c->d_inst) return fail(c, PIC_ERR_STATE, "not initialised");
+    if (instance < 0 || instance >= c->n || !chunk) return fail(c, PIC_ERR_ARG, "bad instance or null chunk");
+    *chunk = c->in[instance].L.chunk;
     return PIC_OK;
 }
 

@@ -85,7 +85,8 @@ ENTRY_POINTS = ["pic_workspace_size", "pic_init", "pic_deposit", "pic_solve", "p
                 "pic_push", "pic_step", "pic_diagnostics", "pic_particles", "pic_read_hits",
                 "pic_sort", "pic_push_timing", "pic_set_timing", "pic_batch_workspace_size",
                 "pic_batch_init", "pic_batch_step", "pic_batch_diagnostics", "pic_batch_particles",
-                "pic_batch_solve_info", "pic_node_map", "pic_tune", "pic_set_level_pairs", "pic_set_cg_pass", "pic_inject_fault",
+                "pic_batch_solve_info", "pic_node_map", "pic_tune", "pic_set_level_pairs", "pic_set_cg_pass",
+                "pic_push_chunk", "pic_inject_fault",
                 "pic_destroy", "pic_last_error", "pic_version"]
 
 
@@ -124,6 +125,7 @@ def lib():
     L.pic_tune.argtypes = [P, i32, i32, i32, i32]
     L.pic_set_level_pairs.argtypes = [P, i32]
     L.pic_set_cg_pass.argtypes = [P, i32]
+    L.pic_push_chunk.argtypes = [P, i32, C.POINTER(i32)]
     L.pic_inject_fault.argtypes = [P, i32]
     L.pic_destroy.argtypes = [P]
     L.pic_destroy.restype = None
@@ -145,7 +147,7 @@ class PicError(RuntimeError):
 
 
 def make_config(w, *, solver=0, max_iter=2000, sort_interval=(8, 64), tile=(16, 16), halo=4,
-                chunk=4096, push_unroll=4, push_merge=0, hitlog_capacity=0,
+                chunk=0, push_unroll=4, push_merge=0, hitlog_capacity=0,
                 hitlog_species_mask=2, rtol=None, warm_start=1):
     """pic_config from a workload description (see synth.Workload)."""
     cc = np.ascontiguousarray(w.cell_cond, dtype=np.uint8)
@@ -274,6 +276,12 @@ class _Context:
 
     def pic_set_cg_pass(self, mode):
         self._chk(lib().pic_set_cg_pass(self.ctx, int(mode)))
+
+    def pic_push_chunk(self, i=0):
+        """Particles per thread block of instance i's pushes."""
+        n = C.c_int32()
+        self._chk(lib().pic_push_chunk(self.ctx, int(i), C.byref(n)))
+        return n.value
 
     def pic_inject_fault(self, what=1):
         """Test hook of the device error path (see pic.h)."""

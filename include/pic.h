@@ -288,10 +288,17 @@ pic_status pic_push_chunk(pic_ctx *ctx, int32_t instance, int32_t *chunk);
  * multigrid cannot coarsen: one launch per refinement pass; multigrid on a
  * small grid: one launch per solve), 0 as one launch per step of the
  * iteration, -1 as 1 but without waiting (for tests: where several
- * work-groups exchange data the launch gives up at once and the solve falls
- * back to 0, as it does when a wait takes over a second).  The potential is
- * the same bit for bit.  PIC_ERR_ARG for other values. */
+ * work-groups exchange data the launch gives up at once, as it does when a
+ * wait takes over a second).  After a launch gave up or was refused the
+ * solve goes on as with 0, and so do the next solves: 64, then twice as many
+ * each time in a row.  The potential is the same bit for bit.  PIC_ERR_ARG
+ * for other values. */
 pic_status pic_set_cg_pass(pic_ctx *ctx, int32_t mode);
+
+/* *one_launch: 1 where the next solve starts in one launch; *fallbacks: how
+ * often since pic_init such a launch gave up or was refused.  Either may be
+ * NULL. */
+pic_status pic_cg_pass_info(pic_ctx *ctx, int32_t *one_launch, int64_t *fallbacks);
 
 /* Re-bins species s now (tile sort; drops removed particles). */
 pic_status pic_sort(pic_ctx *ctx, int32_t species);

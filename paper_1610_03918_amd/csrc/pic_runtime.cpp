@@ -309,6 +309,7 @@ struct Carve {
 
 constexpr int kVWindow = 512;   // steps of conductor potentials held on the device
 constexpr long long kCgWait = 100000000ll; // ticks (1 s of the 100 MHz wall clock) a wait of a one-launch CG pass may take
+constexpr int kCgHold = 64;         // solves that the launched kernels run after a one-launch form gave up, at first
 constexpr int kContinueChunk = 64; // inner iterations per graph between stop tests (plain CG)
 
 } // namespace
@@ -360,6 +361,9 @@ struct pic_ctx {
     MgPlan mgs{};
     unsigned cg_epoch = 1;
     int cg_mode = 1;               // 1 one launch, 0 the launched kernels, -1 one launch that does not wait (tests)
+    int cg_rest = 0;               // solves left to the launched kernels since a one-launch form gave up
+    int cg_hold = kCgHold;         // of these after the next time
+    long long cg_fallbacks = 0;
     // graphs
     hipStream_t cap_stream = nullptr;
     std::map<int, hipGraphExec_t> outer_graphs;   // CG passes by K; sweep chunks by kSweepKey + count
@@ -803,13 +807,27 @@ pic_status launch_chunk(pic_ctx *c, int K, bool first)
     return PIC_OK;
 }
 
+// A one-launch form gave up waiting (its work-groups did not all get onto the
+// device) or its launch was refused: the launched kernels run this solve to
+// its end and the next ones, 64 at first and twice as many after every further
+// time in a row, so that a lasting cause costs a second (kCgWait) ever more
+// rarely and a passing one a few solves.
+pic_status cg_fell_back(pic_ctx *c)
+{
+    c->cg_fallbacks++;
+    c->cg_rest = c->cg_hold;
+    c->cg_hold = std::min(2 * c->cg_hold, 1 << 20);
+    // a pass that gave up left chain sums behind
+    if (c->in[0].d_cg_slots)
+        HIPCHK(c, hipMemsetAsync(c->in[0].d_cg_slots, 0xFF, sizeof(unsigned long long) * kCgSlotWords, c->stream));
+    return PIC_OK;
+}
+
 // One pass of plain CG as one launch: as many iterations as the launched
 // form's chunks (K, then kContinueChunk at a time until max_iter) could run.
-// False where the runtime refuses the launch: the context then runs the
-// launched kernels.
-bool run_cg_pass(pic_ctx *c, int K, int most, int max_iter)
+// *ran: the runtime took the launch.
+pic_status run_cg_pass(pic_ctx *c, int K, int most, int max_iter, bool *ran)
 {
-    if (!c->cg.ok || !c->cg_mode) return false;
     long long cap = K;
     if (most + cap < max_iter) cap += (max_iter - most - cap + kContinueChunk - 1) / kContinueChunk * kContinueChunk;
     cap = std::min<long long>(cap, 1 << 26);
@@ -817,10 +835,10 @@ bool run_cg_pass(pic_ctx *c, int K, int most, int max_iter)
     const hipError_t e = launch_cg_pass(c->d_inst, c->cg, c->cg_epoch, (int)cap, h.d_cg_rim, h.d_cg_slots,
                                         c->d_F + F_CGABORT, c->cg_mode < 0 ? -1 : kCgWait, c->stream);
     c->cg_epoch += 2 * (unsigned)cap + 2;
-    if (e == hipSuccess) return true;
+    *ran = e == hipSuccess;
+    if (*ran) return PIC_OK;
     (void)hipGetLastError();
-    c->cg_mode = 0;
-    return false;
+    return cg_fell_back(c);
 }
 
 pic_status read_flags(pic_ctx *c, std::vector<double> &S, std::vector<int> &F)
@@ -958,11 +976,10 @@ pic_status do_sweep_solve(pic_ctx *c, int kind, const double *guess)
     return PIC_OK;
 }
 
-// Every pass of a small grid's multigrid solve as one launch.  False where
-// the context does not run it so, or the runtime refuses the launch.
-bool run_mg_solve(pic_ctx *c, int max_iter)
+// Every pass of a small grid's multigrid solve as one launch.  *ran: the
+// runtime took the launch.
+pic_status run_mg_solve(pic_ctx *c, int max_iter, bool *ran)
 {
-    if (!c->mgs.ok || !c->cg_mode) return false;
     MgSolveArgs m{};
     m.chunk0 = c->pass_chunk[0];
     m.chunk1 = c->pass_chunk[1];
@@ -972,10 +989,10 @@ bool run_mg_solve(pic_ctx *c, int max_iter)
     m.abort_word = c->d_F + F_CGABORT;
     m.wait = c->cg_mode < 0 ? -1 : kCgWait;
     c->cg_epoch += kMgEpochs;
-    if (launch_mg_solve(c->d_inst, c->mgs, m, c->stream) == hipSuccess) return true;
+    *ran = launch_mg_solve(c->d_inst, c->mgs, m, c->stream) == hipSuccess;
+    if (*ran) return PIC_OK;
     (void)hipGetLastError();
-    c->cg_mode = 0;
-    return false;
+    return cg_fell_back(c);
 }
 
 pic_status do_solve(pic_ctx *c, int kind, const double *guess)
@@ -995,17 +1012,21 @@ pic_status do_solve(pic_ctx *c, int kind, const double *guess)
     // With multigrid the first pass is queued behind the start without a
     // look at its flags (its kernels skip an instance that already
     // converged), so a solve that needs one pass costs one host round trip.
-    bool have = false, launched = false;
+    bool have = false, one = (c->cg.ok || c->mgs.ok) && c->cg_mode && !c->cg_rest;
+    if (c->cg_rest) c->cg_rest--;
+    if (!plain_cg && one && (st = run_mg_solve(c, max_iter, &one)) != PIC_OK) return st;
     if (plain_cg) {
         if ((st = read_flags(c, S, F)) != PIC_OK) return st;
         have = true;
-    } else if (run_mg_solve(c, max_iter)) {
+    } else if (one) {
         if ((st = read_flags(c, S, F)) != PIC_OK) return st;
         have = true;
-        if (F[F_CGABORT]) {
-            // gave up waiting: the passes that ended stand, the launched
-            // kernels go on from there, and run every later solve
-            c->cg_mode = 0;
+        if (!F[F_CGABORT]) {
+            c->cg_hold = kCgHold;
+        } else {
+            // gave up waiting: the passes that ended stand, and the launched
+            // kernels go on from there
+            if ((st = cg_fell_back(c)) != PIC_OK) return st;
             F[F_CGABORT] = 0;
             HIPCHK(c, hipMemcpyAsync(c->d_F, F.data(), F.size() * sizeof(int), hipMemcpyHostToDevice, c->stream));
             HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -1035,7 +1056,8 @@ pic_status do_solve(pic_ctx *c, int kind, const double *guess)
             // the pass's CG in graph chunks until its stop test, then update.
             K = std::min(K, 128);
             K += K & 1;
-            if (launched || !run_cg_pass(c, K, most, max_iter)) {
+            if (one && (st = run_cg_pass(c, K, most, max_iter, &one)) != PIC_OK) return st;
+            if (!one) {
                 st = launch_chunk(c, K, true);
                 for (int guard = 0; st == PIC_OK && guard < (1 << 20); guard++) {
                     if ((st = read_flags(c, S, F)) != PIC_OK) break;
@@ -1062,18 +1084,17 @@ pic_status do_solve(pic_ctx *c, int kind, const double *guess)
         if (st != PIC_OK) return st;
         if (F[F_CGABORT]) {
             // the one-launch pass ended early and the pass's end was skipped:
-            // the potential and its residual are untouched.  A step was not
-            // finite: the launched kernels run the rest of this solve.  It
-            // gave up waiting (its work-groups did not all get onto the
-            // device): they run every solve of the context from here on
-            launched = true;
-            if (F[F_CGABORT] == 1) c->cg_mode = 0;
+            // the potential and its residual are untouched, and the launched
+            // kernels run the rest of this solve
+            one = false;
+            if (F[F_CGABORT] == 1 && (st = cg_fell_back(c)) != PIC_OK) return st;
             HIPCHK(c, hipMemcpyAsync(c->d_F, before.data(), before.size() * sizeof(int), hipMemcpyHostToDevice,
                                      c->stream));
             HIPCHK(c, hipStreamSynchronize(c->stream));
             F = before;
             continue;
         }
+        if (plain_cg && one) c->cg_hold = kCgHold;
         have = true;
         int need = 0, ran = 0;
         bool unfinished = false;
@@ -1829,10 +1850,17 @@ pic_status pic_set_cg_pass(pic_ctx *c, int32_t mode)
     pic_status st = check(c);
     if (st != PIC_OK) return st;
     if (mode < -1 || mode > 1) return fail(c, PIC_ERR_ARG, "mode must be -1, 0 or 1");
-    // a pass that gave up left words behind
-    if (mode && c->in[0].d_cg_slots)
-        HIPCHK(c, hipMemsetAsync(c->in[0].d_cg_slots, 0xFF, sizeof(unsigned long long) * kCgSlotWords, c->stream));
     c->cg_mode = mode;
+    c->cg_rest = 0;
+    c->cg_hold = kCgHold;
+    return PIC_OK;
+}
+
+pic_status pic_cg_pass_info(pic_ctx *c, int32_t *one_launch, int64_t *fallbacks)
+{
+    if (!c || !c->d_inst) return fail(c, PIC_ERR_STATE, "not initialised");
+    if (one_launch) *one_launch = (c->cg.ok || c->mgs.ok) && c->cg_mode && !c->cg_rest ? 1 : 0;
+    if (fallbacks) *fallbacks = c->cg_fallbacks;
     return PIC_OK;
 }
 

@@ -86,7 +86,7 @@ ENTRY_POINTS = ["pic_workspace_size", "pic_init", "pic_deposit", "pic_solve", "p
                 "pic_sort", "pic_push_timing", "pic_set_timing", "pic_batch_workspace_size",
                 "pic_batch_init", "pic_batch_step", "pic_batch_diagnostics", "pic_batch_particles",
                 "pic_batch_solve_info", "pic_node_map", "pic_tune", "pic_set_level_pairs", "pic_set_cg_pass",
-                "pic_push_chunk", "pic_inject_fault",
+                "pic_cg_pass_info", "pic_push_chunk", "pic_inject_fault",
                 "pic_destroy", "pic_last_error", "pic_version"]
 
 
@@ -125,6 +125,7 @@ def lib():
     L.pic_tune.argtypes = [P, i32, i32, i32, i32]
     L.pic_set_level_pairs.argtypes = [P, i32]
     L.pic_set_cg_pass.argtypes = [P, i32]
+    L.pic_cg_pass_info.argtypes = [P, C.POINTER(i32), C.POINTER(C.c_int64)]
     L.pic_push_chunk.argtypes = [P, i32, C.POINTER(i32)]
     L.pic_inject_fault.argtypes = [P, i32]
     L.pic_destroy.argtypes = [P]
@@ -276,6 +277,12 @@ class _Context:
 
     def pic_set_cg_pass(self, mode):
         self._chk(lib().pic_set_cg_pass(self.ctx, int(mode)))
+
+    def pic_cg_pass_info(self):
+        """(the next solve starts in one launch, how often such a launch gave up or was refused)."""
+        one, n = C.c_int32(), C.c_int64()
+        self._chk(lib().pic_cg_pass_info(self.ctx, C.byref(one), C.byref(n)))
+        return bool(one.value), n.value
 
     def pic_push_chunk(self, i=0):
         """Particles per thread block of instance i's pushes."""

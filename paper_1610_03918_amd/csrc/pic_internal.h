@@ -118,6 +118,7 @@ struct CoarseArgs {
     int off_p;                     // LDS: kCoarseWaves x n column partial sums of the exact solve
 };
 
+constexpr int kCoarseMaxLds = 159 * 1024; // dynamic LDS of the coarse kernel (160 KiB per work-group)
 constexpr int kCoarseWaves = 16;   // wavefronts of the coarse kernel's work-group (1024 threads)
 constexpr int kDenseMaxNodes = 768; // largest coarsest level given an explicit inverse (3 x 64 lanes x 4 floats)
 

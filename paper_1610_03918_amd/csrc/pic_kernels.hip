@@ -17,6 +17,7 @@
 #include "wave_ops.h"
 
 #include <algorithm>
+#include <atomic>
 
 namespace pic {
 
@@ -1671,7 +1672,7 @@ void launch_mg_mid(const Inst *I, const Tab &tp, const Tab &tf, int level, bool 
         t.n++;
     }
     if (!t.n) return;
-    static bool attr = false;
+    static std::atomic<bool> attr{false};
     if (!attr) {
         (void)hipFuncSetAttribute((const void *)k_mg_mid<true, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   kPairDnLds);
@@ -2449,10 +2450,11 @@ void launch_coarse(const Inst *I, const Tab &t, int form, int lds_bytes, const T
     const int f = form == 3 ? 1 : form == 5 ? 2 : 0;
     static const void *const kernel[3] = {(const void *)k_coarse<0>, (const void *)k_coarse<3>,
                                           (const void *)k_coarse<5>};
-    static int allowed[3] = {64 * 1024, 64 * 1024, 64 * 1024};
-    if (lds_bytes > allowed[f]) {
-        (void)hipFuncSetAttribute(kernel[f], hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
-        allowed[f] = lds_bytes;
+    // a kernel's limit is the process's: always the largest that any context asks for
+    static std::atomic<bool> allowed[3];
+    if (lds_bytes > 64 * 1024 && !allowed[f]) {
+        (void)hipFuncSetAttribute(kernel[f], hipFuncAttributeMaxDynamicSharedMemorySize, kCoarseMaxLds);
+        allowed[f] = true;
     }
     const dim3 g(t.n), b(1024);
     if (f == 1) hipLaunchKernelGGL(k_coarse<3>, g, b, lds_bytes, s, I, t, t0, pt, fuse ? 1 : 0);
@@ -3081,6 +3083,8 @@ __global__ __launch_bounds__(kMgThreads, 2) void k_mg_solve(const Inst *insts, M
         for (int c = tid; c < dense_n; c += nt) st_agent(m.words + c, tagged(0u, epoch | 0x80000000u));
 }
 
+constexpr int kMgSolveMaxLds = 150 * 1024;
+
 static const void *mg_solve_kernel(const MgPlan &p)
 {
     if (p.help) return p.R == 2 ? (const void *)k_mg_solve<2, true> : (const void *)k_mg_solve<4, true>;
@@ -3120,9 +3124,11 @@ MgPlan mg_solve_plan(int NX, int NY, const CoarseArgs &c, int lg)
         off = std::max(off, (kDenseRows + 1) * np * 4);
     }
     p.lds = off;
-    if (off > 150 * 1024) return p;
+    if (off > kMgSolveMaxLds) return p;
     const void *f = mg_solve_kernel(p);
-    if (off > 64 * 1024 && hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, off) != hipSuccess) {
+    // (the same limit for every context: it is the process's, and one of a smaller grid would lower it under a live one)
+    if (off > 64 * 1024 &&
+        hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kMgSolveMaxLds) != hipSuccess) {
         (void)hipGetLastError();
         return p;
     }

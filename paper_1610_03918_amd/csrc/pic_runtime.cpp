@@ -23,7 +23,6 @@ using namespace pic;
 namespace {
 
 constexpr int kCoarseMaxNodes = 12288;  // largest level solved inside one work-group
-constexpr int kCoarseMaxLds = 159 * 1024;   // dynamic LDS of the coarse kernel (160 KiB per work-group)
 constexpr int kDenseTruncNodes = 256;       // coarsest level at most this size (see make_layout)
 constexpr int kMaxTiming = 512;
 constexpr int kPushFill = 1024;    // push blocks that fill the chip: four a compute unit

@@ -295,7 +295,7 @@ __global__ __launch_bounds__(1024) void k_cg_pass(const Inst *insts, int bx, int
         epoch++;
         turn = turn == 2 ? 0u : turn + 1;
         if (give_up) {
-            if (tid == 0) __hip_atomic_store(abort_word, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (tid == 0) __hip_atomic_store(abort_word, (int)kAbortGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             return false;
         }
         return true;
@@ -383,7 +383,7 @@ __global__ __launch_bounds__(1024) void k_cg_pass(const Inst *insts, int bx, int
         const float alpha = (float)(rz / pq);
         if (!(fabsf(alpha) < INFINITY && fabsf(beta) < INFINITY)) {
             if (lead) {
-                *abort_word = 2;
+                *abort_word = kAbortNotFinite;
                 if (!SINGLE) slots[kTurnWord] = turn;
             }
             return;

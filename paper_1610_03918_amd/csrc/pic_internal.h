@@ -62,11 +62,14 @@ enum {
     F_ITER1,     // inner iterations of the solve's first pass
     F_ERR,       // sticky device error bits (kErrVWindow)
     F_UNCONV,    // sticky count of pushes whose potential had not met rtol
-    F_CGABORT,   // a one-launch CG pass ended early and does not count: 1 gave up waiting, 2 a step was not finite
+    F_CGABORT,   // a one-launch CG pass ended early and does not count (kAbort...)
     F_CHUNK0,    // a one-launch solve's iterations for the next first pass, and for later ones
     F_CHUNK1,
     F_NFLAG = 14
 };
+
+// Why a one-launch CG ended early (F_CGABORT): it gave up waiting, or a step length was not finite.
+enum { kAbortGaveUp = 1, kAbortNotFinite = 2 };
 
 // Device error bits (F_ERR): the assembly found the device step counter
 // outside the window of conductor potentials (it then reads row 0).

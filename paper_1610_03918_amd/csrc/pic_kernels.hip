@@ -2964,7 +2964,7 @@ __global__ __launch_bounds__(kMgThreads, 2) void k_mg_solve(const Inst *insts, M
                 epoch++;
                 if (give_up) {
                     // the passes before this one stand; the host goes on from there
-                    if (tid == 0) __hip_atomic_store(m.abort_word, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (tid == 0) __hip_atomic_store(m.abort_word, (int)kAbortGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     return;
                 }
             }

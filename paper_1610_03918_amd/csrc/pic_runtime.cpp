@@ -1086,7 +1086,7 @@ pic_status do_solve(pic_ctx *c, int kind, const double *guess)
             // the potential and its residual are untouched, and the launched
             // kernels run the rest of this solve
             one = false;
-            if (F[F_CGABORT] == 1 && (st = cg_fell_back(c)) != PIC_OK) return st;
+            if (F[F_CGABORT] == kAbortGaveUp && (st = cg_fell_back(c)) != PIC_OK) return st;
             HIPCHK(c, hipMemcpyAsync(c->d_F, before.data(), before.size() * sizeof(int), hipMemcpyHostToDevice,
                                      c->stream));
             HIPCHK(c, hipStreamSynchronize(c->stream));

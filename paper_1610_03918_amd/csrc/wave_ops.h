@@ -2,7 +2,7 @@
 // of one launch through device memory (gfx950).
 #pragma once
 
-#include <hip/hip_runtime.h>
+#include "pic_internal.h"
 
 namespace pic {
 
@@ -109,7 +109,8 @@ __device__ __forceinline__ void st_agent(u64 *p, u64 v)
 __device__ __forceinline__ u64 tagged(unsigned data, unsigned epoch) { return ((u64)epoch << 32) | data; }
 
 // True while a poll may go on; false once its time is up or another
-// work-group gave up.
+// work-group gave up.  (A step that is not finite ends the launch too, but
+// every word that is polled until then has been published by then.)
 struct Patience {
     long long start;
     int spins;
@@ -122,7 +123,7 @@ struct Patience {
         const long long now = wall_clock64();
         if (start == 0) start = now;
         if (now - start > wait) return false;
-        return __hip_atomic_load(abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
+        return __hip_atomic_load(abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != kAbortGaveUp;
     }
 };
 

@@ -48,3 +48,33 @@ def test_where_no_launch_fits_the_info_says_so():
     pic.start()
     assert pic.pic_cg_pass_info() == (False, 0)
     pic.close()
+
+
+def few_particles(nx, ny):
+    w = synth.trench(nx=nx, ny=ny, width=max(2, ny // 8), depth=nx // 8, ppc=1, seed=73, rtol=1e-6)
+    return w, [{k: v[::29].copy() for k, v in p.items()} for p in synth.load(w)]
+
+
+def same(x, y):
+    assert repr(x[0]) == repr(y[0])                # (repr: a residual may be NaN)
+    assert np.array_equal(x[1], y[1], equal_nan=True)
+
+
+# one work-group; several, with one to nine wavefronts each.  1e40: the float32 residual overflows, so that no step
+# length is finite.  1e-37: products r z = r^2 / 4 whose float32 z underflows
+@pytest.mark.parametrize("nx,ny", [(40, 24), (96, 56), (1024, 512)])
+@pytest.mark.parametrize("scale", [1e40, 1e-37])
+def test_extreme_sources_as_the_launched_kernels(nx, ny, scale):
+    """A pass whose step is not finite is left to the launched kernels, and counts as no fall-back."""
+    from paper_1610_03918_amd import Pic
+    w, few = few_particles(nx, ny)
+    out = {}
+    for mode in (0, 1):
+        pic = Pic(w, few, solver=1, max_iter=256, sort_interval=(0, 0))
+        pic.pic_set_cg_pass(mode)
+        pic.b.mul_(scale)
+        out[mode] = [(pic.pic_solve(0, allow_unconverged=True), pic.phi.cpu().numpy()) for _ in range(2)]
+        assert pic.pic_cg_pass_info() == (mode == 1, 0)
+        pic.close()
+    for x, y in zip(out[0], out[1]):
+        same(x, y)

@@ -1084,8 +1084,10 @@ pic_status do_solve(pic_ctx *c, int kind, const double *guess)
         if (F[F_CGABORT]) {
             // the one-launch pass ended early and the pass's end was skipped:
             // the potential and its residual are untouched, and the launched
-            // kernels run the rest of this solve
+            // kernels run the rest of this solve, this pass as the first of it
+            // again
             one = false;
+            pass--;
             if (F[F_CGABORT] == kAbortGaveUp && (st = cg_fell_back(c)) != PIC_OK) return st;
             HIPCHK(c, hipMemcpyAsync(c->d_F, before.data(), before.size() * sizeof(int), hipMemcpyHostToDevice,
                                      c->stream));

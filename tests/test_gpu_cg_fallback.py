@@ -78,3 +78,25 @@ def test_extreme_sources_as_the_launched_kernels(nx, ny, scale):
         pic.close()
     for x, y in zip(out[0], out[1]):
         same(x, y)
+
+
+@pytest.mark.parametrize("mode", [1, -1])
+def test_the_iteration_limit_after_a_pass_run_again(mode):
+    """Where max_iter cuts a solve short follows the lengths of earlier passes: a first pass that the launched kernels
+    ran in the one launch's place counts as a first pass."""
+    from paper_1610_03918_amd import Pic
+    w, few = few_particles(256, 200)
+    out = {}
+    for m in (0, mode):
+        pic = Pic(w, few, solver=1, max_iter=200, rtol=1e-12, sort_interval=(0, 0))
+        pic.pic_set_cg_pass(m)
+        b = pic.b.clone()
+        if mode == 1:
+            pic.b.mul_(1e40)
+            pic.pic_solve(0, allow_unconverged=True)
+            pic.b.copy_(b)
+        out[m] = [(pic.pic_solve(0, allow_unconverged=True), pic.phi.cpu().numpy()) for _ in range(3)]
+        pic.close()
+    assert not out[0][0][0]["converged"]
+    for x, y in zip(out[0], out[mode]):
+        same(x, y)

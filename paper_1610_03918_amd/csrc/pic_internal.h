@@ -109,7 +109,7 @@ struct CoarseArgs {
     int nlev;                      // levels handled in LDS
     int NX[kMaxLev], NY[kMaxLev];
     int off_u[kMaxLev], off_g[kMaxLev], off_f[kMaxLev]; // LDS byte offsets
-    int off_s;                     // LDS scratch: one float per node of the first LDS level
+    int off_s;                     // LDS scratch (scratch_floats of the first LDS level)
     Dev<const uint8_t> fix[kMaxLev];   // global masks of those levels
     Dev<float> u_top;                  // global u of the first LDS level (output)
     Dev<const float> g_top;            // global g of the first LDS level (input)
@@ -124,6 +124,11 @@ struct CoarseArgs {
 constexpr int kCoarseMaxLds = 159 * 1024; // dynamic LDS of the coarse kernel (160 KiB per work-group)
 constexpr int kCoarseWaves = 16;   // wavefronts of the coarse kernel's work-group (1024 threads)
 constexpr int kDenseMaxNodes = 768; // largest coarsest level given an explicit inverse (3 x 64 lanes x 4 floats)
+
+// Values of the two outermost rows and columns of a level; floats of the scratch that the levels from (NX, NY) on
+// use: one a node, or two sets of a coarsest level's edges.
+__host__ __device__ inline int edge_floats(int NX, int NY) { return 2 * (NX + NY); }
+inline int scratch_floats(int NX, int NY) { return NX * NY > 2 * edge_floats(NX, NY) ? NX * NY : 2 * edge_floats(NX, NY); }
 
 // Packed lower triangle of a symmetric n x n matrix: row r holds columns
 // 0 .. r padded with zeros to a multiple of 4 floats; its first float sits

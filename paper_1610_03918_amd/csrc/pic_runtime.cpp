@@ -212,7 +212,7 @@ Layout make_layout(const pic_config *c, const int64_t *cap)
             size_t n = (size_t)L.NXl[l] * L.NYl[l];
             lds += ((n * 4 + 15) & ~size_t(15)) * 2 + ((n + 15) & ~size_t(15));
         }
-        if (lg < L.nlev) lds += ((size_t)L.NXl[lg] * L.NYl[lg] * 4 + 15) & ~size_t(15);   // scratch
+        if (lg < L.nlev) lds += ((size_t)scratch_floats(L.NXl[lg], L.NYl[lg]) * 4 + 15) & ~size_t(15);
         return lds;
     };
     L.lg = 1;
@@ -1303,7 +1303,7 @@ pic_status init_instance(pic_ctx *c, int k, const pic_config *cfg, const pic_buf
             ca.fix[q] = h.d_fix[l];
         }
         ca.off_s = off;
-        off += (L.NXl[L.lg] * L.NYl[L.lg] * 4 + 15) & ~15;
+        off += (scratch_floats(L.NXl[L.lg], L.NYl[L.lg]) * 4 + 15) & ~15;
         ca.off_p = off;
         if (h.dense) off += (kCoarseWaves * L.dense_n * 4 + 15) & ~15;
         ca.lds_bytes = off;

@@ -283,9 +283,9 @@ void launch_coarse(const Inst *I, const Tab &t, int form, int lds_bytes, const T
                    hipStream_t s);
 // fused fine-level V-cycle halves (tables of 32 x 32 tiles of level l)
 constexpr int kMgTileHost = 32;
-// level 0, down: mode 1 at the start of an inner pass, modes 2 and 3 after a
-// CG step; par = buffer of the r / s pairs read
-void launch_mg_down(const Inst *I, const Tab &t, int mode, int par, Part pt, hipStream_t s);
+// level 0, down: at the start of an inner pass, or with a CG step; par = buffer
+// of the r / s pairs read
+void launch_mg_down(const Inst *I, const Tab &t, bool step, int par, Part pt, hipStream_t s);
 void launch_mg_up(const Inst *I, const Tab &t, int par, Part pt, hipStream_t s);
 // level l >= 1, down or up: the pairs (l, l + 1) of tp (tiles of level l + 1)
 // and the single levels of tf
@@ -320,7 +320,7 @@ struct MgSolveArgs {
     unsigned long long *words;         // mg_solve_words of the coarsest level's nodes, cleared once
     int *abort_word;
     long long wait;                    // as launch_cg_pass
-    int tiles, tiles_y, off_u, off_g, off_s, off_s2, off_f, off_v, help;   // of the plan
+    int tiles, tiles_y, off_u, off_g, off_s, off_s2, off_f, off_v;         // of the plan
 };
 constexpr unsigned kMgEpochs = 64 * 130;
 int mg_solve_words(int dense_n);

@@ -164,8 +164,6 @@ __device__ void apply_op(const Inst &I, int op, double t0, double t1)
     }
 }
 
-// One block per unit: totals of the unit's partials in block order, then the
-// scalar logic of the operation on that instance.
 // Sums of the partials b0 .. b1-1 of nq quantities by threads 0 .. 255 of a
 // block (others pass through): per-thread sums in a fixed order, then one
 // per wavefront into sh[q][0 .. 3].  The caller synchronises and adds the
@@ -219,8 +217,6 @@ template <class X> __device__ __forceinline__ X opaque(X x)
     asm volatile("" : "+v"(x));
     return x;
 }
-// a[k] by a vector load: a wait for a scalar load is one for all of them, those
-// for the addresses of the loads to come included.
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 // Ends the program where the flag is set, by an instruction beside the test: a
 // jump to the kernel's end fetches code from another page.
@@ -228,6 +224,8 @@ __device__ __forceinline__ void end_if(int flag)
 {
     if (__builtin_expect(uniform(flag), 1)) __builtin_amdgcn_endpgm();
 }
+// a[k] by a vector load: a wait for a scalar load is one for all of them, those
+// for the addresses of the loads to come included.
 template <class T> __device__ __forceinline__ T vload(const T *a, int k)
 {
     asm("" : "+v"(k));
@@ -253,6 +251,8 @@ __device__ __forceinline__ bool cg_coefficients(int iter, double gamma, double d
     return alpha > 0.0 && alpha < INFINITY && beta < INFINITY;
 }
 
+// One block per unit: totals of the unit's partials in block order, then the
+// scalar logic of the operation on that instance.
 __global__ __launch_bounds__(256) void k_finalize(const Inst *insts, Tab t, Part pt, int op)
 {
     const Inst &I = insts[t.id[blockIdx.x]];
@@ -1176,12 +1176,12 @@ __device__ __forceinline__ void mg_down_fine(const Inst &I, int level, int ti, i
 }
 
 // The same of level 0.
-// MODE 1: level 0 at the start of an inner pass: r = R[0], e = 0, ||r||^2
-//         (inner stop ratio and counters in the last block).
-// MODE 2: level 0 after a CG step: alpha and beta from the last V-cycle's
-//         dot products (partials pq), s' = w + beta s, r' = r - alpha s',
-//         p = z + beta p, e += alpha p (beta = 0 on the first step), r' and
-//         s' to the other buffers of the pair, ||r'||^2 partials (pt) for
+// MODE 1: at the start of an inner pass: r = R[0], e = 0, ||r||^2 partials (pt;
+//         k_finalize makes the inner stop ratio and clears the counters).
+// MODE 2: a CG step: alpha and beta from the last V-cycle's dot products
+//         (partials pq), s' = w + beta s, r' = r - alpha s', p = z + beta p,
+//         e += alpha p (beta = 0 on the first step), r' and s' to the other
+//         buffers of the pair, ||r'||^2 partials (pt), which k_coarse adds for
 //         the inner stop test.  par: buffer of the pair holding r and s.
 template <int NU, int MODE>
 __global__ __launch_bounds__(kMgThreads, 8) void k_mg_down(const Inst *insts, Tab t, int par, Part pt, Part pq)
@@ -1403,18 +1403,16 @@ __global__ __launch_bounds__(kMgThreads) void k_mg_up(const Inst *insts, Tab t, 
 // in between).
 static Part cg_dot_part(Part pt) { return Part{pt.p + 2 * (size_t)pt.stride, pt.stride}; }
 
-void launch_mg_down(const Inst *I, const Tab &t, int mode, int par, Part pt, hipStream_t s)
+void launch_mg_down(const Inst *I, const Tab &t, bool step, int par, Part pt, hipStream_t s)
 {
     if (!t.n) return;
     const dim3 g(tab_blocks(t)), b(kMgThreads);
     const Part pq = cg_dot_part(pt);
-    if (mode == 1) {
+    if (step) {
+        hipLaunchKernelGGL((k_mg_down<kMgSmooth, 2>), g, b, 0, s, I, t, par, pt, pq);
+    } else {
         hipLaunchKernelGGL((k_mg_down<kMgSmooth, 1>), g, b, 0, s, I, t, par, pt, pq);
         finalize(I, t, pt, OP_INIT, s);
-    } else {
-        // mode 3: the coarse kernel reduces the partials (fused update)
-        hipLaunchKernelGGL((k_mg_down<kMgSmooth, 2>), g, b, 0, s, I, t, par, pt, pq);
-        if (mode == 2) finalize(I, t, pt, OP_UPDATE, s);
     }
 }
 
@@ -3207,7 +3205,6 @@ hipError_t launch_mg_solve(const Inst *I, const MgPlan &p, MgSolveArgs m, hipStr
     m.off_f = p.off_f;
     m.off_s2 = p.off_s2;
     m.off_v = p.off_v;
-    m.help = p.help;
     const void *f = mg_solve_kernel(p);
     void *args[] = {&I, &m};
     if (p.help) return hipLaunchCooperativeKernel(f, dim3(1 + p.help), dim3(kMgThreads), args, p.lds, s);

@@ -708,7 +708,7 @@ void enqueue_pass_begin(pic_ctx *c, hipStream_t s)
     Part pt = part_of(c);
     launch_init_red0(c->d_inst, c->t_plain, pt, s);
     if (!c->any_mg) return;
-    launch_mg_down(c->d_inst, c->t_fine[0], 1, 0, pt, s);
+    launch_mg_down(c->d_inst, c->t_fine[0], false, 0, pt, s);
     enqueue_vcycle_mid(c, false, s);
     launch_mg_up(c->d_inst, c->t_fine[0], 0, pt, s);
 }
@@ -725,7 +725,7 @@ void enqueue_iters(pic_ctx *c, int K, bool first, hipStream_t s)
         launch_update_red0(c->d_inst, c->t_plain, (k + 1) & 1, pt, s);
         if (!c->any_mg) continue;
         // the CG step; its reduction and stop test run in the coarse kernel
-        launch_mg_down(c->d_inst, c->t_fine[0], 3, k & 1, pt, s);
+        launch_mg_down(c->d_inst, c->t_fine[0], true, k & 1, pt, s);
         enqueue_vcycle_mid(c, true, s);
         launch_mg_up(c->d_inst, c->t_fine[0], (k + 1) & 1, pt, s);
     }

@@ -17,8 +17,6 @@ constexpr int kNConv = 14;                 // 8 encoder/bottleneck + 6 decoder
 constexpr int kInCh = 3;
 constexpr int kKChunk = 32;                // channels per K step of the convolutions
 
-__host__ __device__ inline int pad32(int c) { return (c + 31) & ~31; }
-
 // What follows a convolution's sums (see k_conv).
 enum { EP_FWD = 0, EP_MASK, EP_UP, EP_DOWN };
 

@@ -527,6 +527,7 @@ def run_sweep(args):
     sort = tuple(sch["sort_interval"])
     b = PicBatch(ws, parts, sort_interval=sort, chunk=sch["chunk"], push_unroll=sch["push_unroll"],
                  push_merge=sch["push_merge"], tile=tuple(sch["tile"]), halo=sch["halo"])
+    sch["chunk"] = b.pic_push_chunk()
     b.start()
     # eager steps tell how many passes and iterations the captured schedule needs
     # (after the spin-up steps, which bring the instances to their long-run state)
@@ -620,7 +621,7 @@ def main():
     ap.add_argument("--unroll", type=int, default=4)
     ap.add_argument("--merge", type=int, default=0)
     ap.add_argument("--tile", default="16,16")
-    ap.add_argument("--chunk", type=int, default=4096)
+    ap.add_argument("--chunk", type=int, default=0, help="particles per push block (0: the library's choice)")
     ap.add_argument("--halo", type=int, default=4)
     ap.add_argument("--warm", type=int, default=1, help="0 previous phi, 1 extrapolated")
     ap.add_argument("--no-learned", action="store_true", help="skip the learned-start measurement")
@@ -750,7 +751,7 @@ def main():
         "data": "synthetic",
         "config": {"workload": w.name, "cells": [w.nx, w.ny], "ppc": w.species[0].ppc,
                    "particles": n0, "dt": w.dt, "rtol": w.rtol, "sort_interval": list(sort),
-                   "tile": list(tile), "chunk": args.chunk, "halo": args.halo,
+                   "tile": list(tile), "chunk": pic.pic_push_chunk(), "halo": args.halo,
                    "push_unroll": args.unroll, "push_merge": args.merge, "warm_start": args.warm,
                    "schedule_source": schedule_source, "spinup_steps": spinup,
                    "timed_from_step": start_step},

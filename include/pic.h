@@ -103,8 +103,8 @@ typedef struct {
     int32_t sort_interval[2];    /* steps between re-binnings per species (0 = at init only) */
     int32_t tile_x, tile_y;      /* particle tile in cells (powers of two; 0 = 16) */
     int32_t halo;                /* cells of drift a tile absorbs before a global fallback (0 = 4) */
-    int32_t chunk;               /* particles per thread block, 256 .. 8192 (0 = 4096, or as many whole passes
-                                    of 1024 as give the chip 1024 blocks of all the context's particles) */
+    int32_t chunk;               /* particles per thread block, 256 .. 8192 (0 = as few whole passes of 1024 as
+                                    make at most 1536 blocks of all the context's particles, 4096 at most) */
     int32_t push_unroll;         /* particles per thread per pass of the push loop: 1, 2, 4 (0 = 4;
                                     4 moves 4 consecutive particles with 16-byte accesses) */
     int32_t push_merge;          /* distinct cells summed per wavefront before LDS atomics: 0, 2, 4 */

@@ -25,7 +25,7 @@ namespace {
 constexpr int kCoarseMaxNodes = 12288;  // largest level solved inside one work-group
 constexpr int kDenseTruncNodes = 256;       // coarsest level at most this size (see make_layout)
 constexpr int kMaxTiming = 512;
-constexpr int kPushFill = 1024;    // push blocks that fill the chip: four a compute unit
+constexpr int kPushFill = 1536;    // push blocks that run at once: six a compute unit
 constexpr int kPushPass = 4 * kPushThreads;   // particles a block moves in one pass
 constexpr int kPushChunk = 4096;   // particles per block where there are enough of them
 
@@ -160,16 +160,17 @@ bool node_map(const pic_config *c, std::vector<uint8_t> &nc)
 }
 
 // Particles per push block of a context that holds `particles` in all
-// instances and species (one launch covers them): whole passes of a block,
-// as many as still give the chip kPushFill blocks.  us a push in blocks of
-// 1024 / 2048 / 3072 / 4096, one instance: the paper's 80 x 30 trench (420,000
-// particles) 19.1 / 23.4 / 27.3 / 32.2; trenches 256 x 128 of 1.4M 25.4 / 28.4 /
-// 31.7 / 34.4, of 2.3M 38.7 / 33.4 / 37.0 / 39.7, of 3.7M 50.7 / 48.5 / 48.0 / 47.2.
-// A step of six grids in one launch (90M particles) 1713 / 1519 / 1521 / 1513.
+// instances and species (one launch covers them): as few whole passes of a
+// block as let all blocks run at once.  us a push in blocks of 1024 / 2048 /
+// 3072 / 4096, one instance: 0.42M particles (the paper's trench) 19.6 / 22.8 /
+// 26.7 / 30.7, 1.4M 25.5 / 28.7 / 31.3 / 34.3, 1.6M 31.7 / 29.4 / 32.8 / 34.9, 2.3M
+// 37.8 / 32.8 / 36.5 / 38.5, 3.4M 45.1 / 44.2 / 44.8 / 44.4, 3.7M 50.3 / 48.0 / 46.6 /
+// 48.1.  A step of six grids in one launch (90M particles) 1713 / 1519 / 1521 / 1513.
 int fill_chunk(long long particles)
 {
-    const long long passes = particles / ((long long)kPushFill * kPushPass);
-    return (int)std::min<long long>(kPushChunk, std::max<long long>(1, passes) * kPushPass);
+    const long long at_once = (long long)kPushFill * kPushPass;
+    const long long passes = std::max(1ll, (particles + at_once - 1) / at_once);
+    return (int)std::min<long long>(kPushChunk, passes * kPushPass);
 }
 
 long long push_blocks(const Layout &L, const pic_config *c, int species, long long capacity, int chunk)

@@ -1,6 +1,6 @@
 """The particles per thread block of the push: what the caller asks for, or,
-where the choice is left to the library, whole passes of 1024 particles that
-still give the chip 1024 blocks of all the context's particles.  The block
+where the choice is left to the library, as few whole passes of 1024 particles
+as make at most 1536 blocks of all the context's particles.  The block
 size changes no result."""
 import ctypes as C
 
@@ -66,7 +66,7 @@ def test_the_librarys_choice_counts_the_contexts_particles():
     ws = [synth.periodic_square(n=64, ppc=90, seed=60 + k) for k in range(3)]
     parts = [synth.load(w) for w in ws]
     n = sum(p["cell"].size for p in parts[0])
-    assert n == 737_280                                       # 3 n is two passes for each of 1024 blocks
+    assert n == 737_280                                       # 3 n is more than one pass for each of 1536 blocks
     one = Pic(ws[0], parts[0], capacity=(3_000_000, 3_000_000))
     assert one.pic_push_chunk() == 1024
     one.close()

@@ -277,8 +277,9 @@ void launch_sweeps(const Inst *I, const Tab &t, int jacobi, int sweeps, hipStrea
 void launch_init_red0(const Inst *I, const Tab &t, Part pt, hipStream_t s);
 void launch_pupdate_Ap(const Inst *I, const Tab &t, int kold, int first, Part pt, hipStream_t s);
 void launch_update_red0(const Inst *I, const Tab &t, int knew, Part pt, hipStream_t s);
-// form: of every instance of t (coarse_form), or 0
+// form: of one instance, and of two forms that one launch serves
 int coarse_form(const CoarseArgs &c);
+int coarse_form(int a, int b);
 void launch_coarse(const Inst *I, const Tab &t, int form, int lds_bytes, const Tab &t0, Part pt, bool fuse,
                    hipStream_t s);
 // fused fine-level V-cycle halves (tables of 32 x 32 tiles of level l)
@@ -312,6 +313,7 @@ hipError_t launch_cg_pass(const Inst *I, const CgPlan &p, unsigned epoch, int ca
 struct MgPlan {
     int ok;
     int R, tiles, tiles_y, help;       // tiles a thread; work-groups that share the dense coarsest solve
+    int odd;                           // sweeps of the coarsest level cross an odd wrap
     int off_u, off_g, off_s, off_s2, off_f, off_v, lds;
 };
 struct MgSolveArgs {

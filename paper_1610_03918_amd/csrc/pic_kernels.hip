@@ -1736,10 +1736,10 @@ __device__ __forceinline__ void c_sweep(const CLev &L, int col, int first, int s
 // reads the other's value from before the half-sweep, or it would depend on
 // the wavefronts which of the two is updated first.  rd holds those values
 // (rows 0 and NX - 1, then columns 0 and NY - 1), wr takes the new ones for the
-// next sweep.  A V-cycle with c_sweep's race / so, us: periodic 62 x 62 (31 x 31
-// nodes) 30 / 35, 376 x 376 (47 x 47) 98 / 98, trench 416 x 488 (53 x 61) 115 / 122;
-// a solve, which takes fewer of them, 850 / 744, 2790 / 2453, 2000 / 1955.
-// (The last row and column after the others, with a barrier more: 50, 124, 154.)
+// next sweep.  A solve with c_sweep's race / so, us: periodic 62 x 62 (31 x 31
+// nodes) 850 / 700, 376 x 376 (47 x 47) 2790 / 2396 (23 iterations instead of 23 to
+// 29), trench 416 x 488 (53 x 61) 2000 / 1877; k_coarse there 71.6 / 72.3.  (The last
+// row and column after the others, with a barrier more: 1360, 3100, 2775.)
 template <int ox, int oy>
 __device__ __forceinline__ void c_sweep_odd(const CLev &L, const float *rd, float *wr, int col, int first, int step)
 {
@@ -1750,13 +1750,14 @@ __device__ __forceinline__ void c_sweep_odd(const CLev &L, const float *rd, floa
     const int lf0 = oy ? D + 2 * NY + NX : NY - 1, rt0 = oy ? D + 2 * NY : 0, si = oy ? 1 : NY;
     for (int q = first; q < NX * HW; q += step) {
         const int i = div_rcp(q, rcp), j = 2 * (q - i * HW) + ((i + col) & 1), k = i * NY + j;
-        if (j >= NY || L.f[k]) continue;
         const bool x0 = i == 0, x1 = i == NX - 1, y0 = j == 0, y1 = j == NY - 1;
+        const bool live = !L.f[k] && j < NY;      // (the other loads do not wait for it)
         float s = L.g[k];
         s += L.u[x0 ? up0 + j : k - NY];
         s += L.u[x1 ? dn0 + j : k + NY];
         s += L.u[y0 ? lf0 + i * si : k - 1];
         s += L.u[y1 ? rt0 + i * si : k + 1];
+        if (!live) continue;
         s *= 0.25f;
         L.u[k] = s;
         if (ox && (x0 || x1)) wr[(x0 ? 0 : NY) + j] = s;
@@ -2009,7 +2010,8 @@ constexpr int kCoarsePre = 4;   // 16-byte pieces per thread loaded before the l
 // kCoarseWaveNodes nodes, from the first such level to the coarsest and back,
 // are run by the first wavefront alone.  dense(): solves the coarsest level
 // exactly (called by every thread) and returns true, or returns false.
-template <class Lev, class Dense>
+// ODD: the coarsest level may be a swept one with an odd wrap.
+template <bool ODD, class Lev, class Dense>
 __device__ __forceinline__ void c_cycle(Lev lev, int nlev, float *sr, int px, int py, int sweeps, Dense dense, int tid,
                                         int nt)
 {
@@ -2070,15 +2072,14 @@ __device__ __forceinline__ void c_cycle(Lev lev, int nlev, float *sr, int px, in
         __syncthreads();
     } else {
         const CLev L = lev(nlev - 1);
-        const int ox = px & L.NX & 1, oy = py & L.NY & 1;
-        float *const e0 = sr, *const e1 = sr + edge_floats(L.NX, L.NY);
-        if (ox | oy) {
-            c_edges(L, e0, tid, nt);
-            c_edges(L, e1, tid, nt);
-            __syncthreads();
-        }
         auto solve = [&](auto x_, auto y_) __attribute__((always_inline)) {
             constexpr int X = decltype(x_)::value, Y = decltype(y_)::value;
+            float *const e0 = sr, *const e1 = sr + edge_floats(L.NX, L.NY);
+            if constexpr (X || Y) {
+                c_edges(L, e0, tid, nt);
+                c_edges(L, e1, tid, nt);
+                __syncthreads();
+            }
             for (int sw = 0; sw < sweeps; sw++) {
                 for (int col = 1; col >= 0; col--) {
                     if constexpr (X || Y) c_sweep_odd<X, Y>(L, sw & 1 ? e1 : e0, sw & 1 ? e0 : e1, col, tid, nt);
@@ -2087,6 +2088,7 @@ __device__ __forceinline__ void c_cycle(Lev lev, int nlev, float *sr, int px, in
                 }
             }
         };
+        const bool ox = ODD && (px & L.NX & 1), oy = ODD && (py & L.NY & 1);
         if (ox && oy) solve(Int<1>{}, Int<1>{});
         else if (ox) solve(Int<1>{}, Int<0>{});
         else if (oy) solve(Int<0>{}, Int<1>{});
@@ -2301,7 +2303,7 @@ template <int NC> struct Restrict {
 // the levels below 8000, the exact solve 7000, each piece of code fetched for
 // one pass through it.  257 x 257 nodes (first level 65 x 65): 17.7 -> 15.8 us,
 // 1024 x 513 (128 x 65): 26.2 -> 24.0 us.
-template <int NP>
+template <int NP, bool ODD>
 __global__ __launch_bounds__(1024) void k_coarse(const Inst *insts, Tab t, Tab t0, Part pt, int fuse)
 {
     const Inst &I = insts[t.id[blockIdx.x]];
@@ -2454,7 +2456,7 @@ __global__ __launch_bounds__(1024) void k_coarse(const Inst *insts, Tab t, Tab t
         __syncthreads();
         R1.run(sr, C.g, C.u, tid, 1024);
         __syncthreads();
-        c_cycle([&](int l) __attribute__((always_inline)) { return lev(l + 2); }, nlev - 2, sr, px, py, a.sweeps, dense,
+        c_cycle<ODD>([&](int l) __attribute__((always_inline)) { return lev(l + 2); }, nlev - 2, sr, px, py, a.sweeps, dense,
                 tid, nt);
         P1.correct_red(B.u, C.u, sr);
         __syncthreads();
@@ -2476,7 +2478,7 @@ __global__ __launch_bounds__(1024) void k_coarse(const Inst *insts, Tab t, Tab t
             A.u[k] = (!A.f[k] && ((i + j) & 1) == 0) ? A.g[k] * 0.25f : 0.0f;
         }
         __syncthreads();
-        c_cycle(lev, nlev, sr, px, py, a.sweeps, dense, tid, nt);
+        c_cycle<ODD>(lev, nlev, sr, px, py, a.sweeps, dense, tid, nt);
     }
     {
         const int N = A.NX * A.NY;
@@ -2485,11 +2487,22 @@ __global__ __launch_bounds__(1024) void k_coarse(const Inst *insts, Tab t, Tab t
     }
 }
 
+// The coarsest level is swept by a work-group and an odd number of its nodes
+// lie along a periodic axis.
+static bool odd_sweeps(const CoarseArgs &c)
+{
+    const int NX = c.NX[c.nlev - 1], NY = c.NY[c.nlev - 1];
+    return !c.dense_n && NX * NY > kCoarseWaveNodes && ((c.px & NX & 1) || (c.py & NY & 1));
+}
+
 // The form of k_coarse for one instance: pairs of the first level a thread, 0
 // where the first two levels are not there, do not fit the registers, or wrap
-// an odd number of columns.
+// an odd number of columns, 1 (ODD) where the coarsest level's sweeps cross an
+// odd wrap (a kernel of its own: that code within the others' cost them up to
+// 4 % on their grids).
 int coarse_form(const CoarseArgs &c)
 {
+    if (odd_sweeps(c)) return 1;
     if (c.nlev < 3 || (c.py && ((c.NY[0] | c.NY[1]) & 1))) return 0;
     const int p0 = c.NX[0] * ((c.NY[0] + 1) / 2), p1 = c.NX[1] * ((c.NY[1] + 1) / 2);
     const int n1 = c.NX[1] * c.NY[1], n2 = c.NX[2] * c.NY[2];
@@ -2499,23 +2512,27 @@ int coarse_form(const CoarseArgs &c)
     return 0;
 }
 
+// The form that serves instances of both.
+int coarse_form(int a, int b)
+{
+    if (a == 1 || b == 1) return 1;
+    return a && b ? std::max(a, b) : 0;
+}
+
 void launch_coarse(const Inst *I, const Tab &t, int form, int lds_bytes, const Tab &t0, Part pt, bool fuse,
                    hipStream_t s)
 {
     if (!t.n) return;
-    const int f = form == 3 ? 1 : form == 5 ? 2 : 0;
-    static const void *const kernel[3] = {(const void *)k_coarse<0>, (const void *)k_coarse<3>,
-                                          (const void *)k_coarse<5>};
+    const int f = form == 3 ? 1 : form == 5 ? 2 : form == 1 ? 3 : 0;
+    static void (*const kernel[4])(const Inst *, Tab, Tab, Part, int) = {k_coarse<0, false>, k_coarse<3, false>,
+                                                                         k_coarse<5, false>, k_coarse<0, true>};
     // a kernel's limit is the process's: always the largest that any context asks for
-    static std::atomic<bool> allowed[3];
+    static std::atomic<bool> allowed[4];
     if (lds_bytes > 64 * 1024 && !allowed[f]) {
-        (void)hipFuncSetAttribute(kernel[f], hipFuncAttributeMaxDynamicSharedMemorySize, kCoarseMaxLds);
+        (void)hipFuncSetAttribute((const void *)kernel[f], hipFuncAttributeMaxDynamicSharedMemorySize, kCoarseMaxLds);
         allowed[f] = true;
     }
-    const dim3 g(t.n), b(1024);
-    if (f == 1) hipLaunchKernelGGL(k_coarse<3>, g, b, lds_bytes, s, I, t, t0, pt, fuse ? 1 : 0);
-    else if (f == 2) hipLaunchKernelGGL(k_coarse<5>, g, b, lds_bytes, s, I, t, t0, pt, fuse ? 1 : 0);
-    else hipLaunchKernelGGL(k_coarse<0>, g, b, lds_bytes, s, I, t, t0, pt, fuse ? 1 : 0);
+    hipLaunchKernelGGL(kernel[f], dim3(t.n), dim3(1024), lds_bytes, s, I, t, t0, pt, fuse ? 1 : 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -2710,7 +2727,7 @@ __device__ void mg_dense_helper(const Inst &I, const MgSolveArgs &m, int h, unsi
     }
 }
 
-template <int NT, bool HELP>
+template <int NT, bool HELP, bool ODD>
 __global__ __launch_bounds__(kMgThreads, 2) void k_mg_solve(const Inst *insts, MgSolveArgs m)
 {
     const Inst &I = insts[0];
@@ -2867,7 +2884,7 @@ __global__ __launch_bounds__(kMgThreads, 2) void k_mg_solve(const Inst *insts, M
     // levels 2 and below, or the coarsest level alone
     auto deeper = [&](int l) __attribute__((always_inline)) {
         auto sub = [&](int k) __attribute__((always_inline)) { return lev(l + k); };
-        c_cycle(sub, nlev - l, l == 0 ? sr1 : (float *)(lds + m.off_s2), px, py, sweeps, dense, tid, nt);
+        c_cycle<ODD>(sub, nlev - l, l == 0 ? sr1 : (float *)(lds + m.off_s2), px, py, sweeps, dense, tid, nt);
     };
     // V-cycle of the right-hand side g0 from the red-from-zero start in u0
     auto cycle = [&]() __attribute__((always_inline)) {
@@ -3143,8 +3160,9 @@ constexpr int kMgSolveMaxLds = 150 * 1024;
 
 static const void *mg_solve_kernel(const MgPlan &p)
 {
-    if (p.help) return p.R == 2 ? (const void *)k_mg_solve<2, true> : (const void *)k_mg_solve<4, true>;
-    return p.R == 2 ? (const void *)k_mg_solve<2, false> : (const void *)k_mg_solve<4, false>;
+    if (p.help) return p.R == 2 ? (const void *)k_mg_solve<2, true, false> : (const void *)k_mg_solve<4, true, false>;
+    if (p.odd) return p.R == 2 ? (const void *)k_mg_solve<2, false, true> : (const void *)k_mg_solve<4, false, true>;
+    return p.R == 2 ? (const void *)k_mg_solve<2, false, false> : (const void *)k_mg_solve<4, false, false>;
 }
 
 MgPlan mg_solve_plan(int NX, int NY, const CoarseArgs &c, int lg)
@@ -3175,6 +3193,7 @@ MgPlan mg_solve_plan(int NX, int NY, const CoarseArgs &c, int lg)
     p.off_v = off;
     off += 3 * 2 * p.R * kMgThreads * 4;
     p.help = c.dense_n > kDenseOnePass ? kCoarseWaves : 0;
+    p.odd = odd_sweeps(c);
     if (p.help) {
         const int np = 4 * ((c.dense_n + 3) >> 2);
         off = std::max(off, (kDenseRows + 1) * np * 4);

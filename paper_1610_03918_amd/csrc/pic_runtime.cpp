@@ -341,7 +341,7 @@ struct pic_ctx {
     Tab t_plain{};                 // level-0 grid of the instances solved by plain CG
     Tab t_fine[kMaxLev] = {};      // 32 x 32 tiles of the fine multigrid levels handled one at a time
     Tab t_pair[kMaxLev] = {};      // 32 x 32 tiles of level l + 1 for levels l, l + 1 in one launch
-    int maxlg = 0, coarse_lds = 0, coarse_frm = 0, any_mg = 0;   // coarse_frm: coarse_form of every instance, or 0
+    int maxlg = 0, coarse_lds = 0, coarse_frm = 0, any_mg = 0;   // coarse_frm: coarse_form of all instances
     int pair_levels = 1;           // fine levels 1, 2 (3, 4, ...) two per launch
     size_t push_lds = 0;
     int unroll = 2, merge = 0;
@@ -1451,7 +1451,6 @@ void build_tabs(pic_ctx *c)
     c->maxlg = 0;
     c->coarse_lds = 0;
     c->coarse_frm = 0;
-    bool formless = false;
     c->any_mg = 0;
     c->push_lds = 0;
     for (int k = 0; k < c->n; k++) {
@@ -1480,8 +1479,7 @@ void build_tabs(pic_ctx *c)
             tab_add(c->t_coarse, k, 1);
             c->coarse_lds = std::max(c->coarse_lds, h.dev.coarse.lds_bytes);
             const int form = coarse_form(h.dev.coarse);
-            formless = formless || !form;
-            c->coarse_frm = formless ? 0 : std::max(c->coarse_frm, form);
+            c->coarse_frm = c->t_coarse.n > 1 ? coarse_form(c->coarse_frm, form) : form;
         }
         for (int s = 0; s < 2; s++) {
             tab_add(c->t_push, 2 * k + s, (int)L.max_blocks[s]);

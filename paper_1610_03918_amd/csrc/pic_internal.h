@@ -277,20 +277,20 @@ void launch_sweeps(const Inst *I, const Tab &t, int jacobi, int sweeps, hipStrea
 void launch_init_red0(const Inst *I, const Tab &t, Part pt, hipStream_t s);
 void launch_pupdate_Ap(const Inst *I, const Tab &t, int kold, int first, Part pt, hipStream_t s);
 void launch_update_red0(const Inst *I, const Tab &t, int knew, Part pt, hipStream_t s);
-// form: of one instance, and of two forms that one launch serves
+// many: the context holds several instances; form: of one instance, and of two forms that one launch serves
 int coarse_form(const CoarseArgs &c);
 int coarse_form(int a, int b);
-void launch_coarse(const Inst *I, const Tab &t, int form, int lds_bytes, const Tab &t0, Part pt, bool fuse,
-                   hipStream_t s);
+void launch_coarse(const Inst *I, const Tab &t, bool many, int form, int lds_bytes, const Tab &t0, Part pt,
+                   bool fuse, hipStream_t s);
 // fused fine-level V-cycle halves (tables of 32 x 32 tiles of level l)
 constexpr int kMgTileHost = 32;
 // level 0, down: at the start of an inner pass, or with a CG step; par = buffer
 // of the r / s pairs read
-void launch_mg_down(const Inst *I, const Tab &t, bool step, int par, Part pt, hipStream_t s);
-void launch_mg_up(const Inst *I, const Tab &t, int par, Part pt, hipStream_t s);
+void launch_mg_down(const Inst *I, const Tab &t, bool many, bool step, int par, Part pt, hipStream_t s);
+void launch_mg_up(const Inst *I, const Tab &t, bool many, int par, Part pt, hipStream_t s);
 // level l >= 1, down or up: the pairs (l, l + 1) of tp (tiles of level l + 1)
 // and the single levels of tf
-void launch_mg_mid(const Inst *I, const Tab &tp, const Tab &tf, int level, bool down, hipStream_t s);
+void launch_mg_mid(const Inst *I, const Tab &tp, const Tab &tf, bool many, int level, bool down, hipStream_t s);
 // One refinement pass of plain CG on a single instance as one launch
 // (cg_persist.hip).  Virtual blocks are the 4 x 64 node blocks of the grid
 // kernels; up to kCgSingleVb of them run in one work-group.

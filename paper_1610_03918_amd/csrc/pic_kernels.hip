@@ -886,9 +886,10 @@ __device__ __forceinline__ long long win_node(int NX, int NY, int px, int py, in
 // waits for any, the flag that may end it included (257 x 257 nodes, with each
 // part's loads after the one before: 10.3, 5.8, 5.9 and 7.2 us for the level-0
 // and level-1 down and the level-1 and level-0 up kernels; now 8.0, 5.0, 4.6
-// and 6.2).  Where a launch holds several instances, of which some have
+// and 6.2).  In a context of several instances (many), of which some have
 // finished, the flag comes first: loading for nothing cost a batch of six more
-// (8.5 -> 13.1 us for the level-0 down kernel) than the trip it saves.
+// (8.5 -> 13.1 us for the level-0 down kernel) than the trip it saves, and a
+// batch of one multigrid instance beside plain-CG ones 10 % of its solve.
 template <int W, int NT = kMgThreads> struct Window {
     static constexpr int R = (W * W + NT - 1) / NT;
     float uv[R], gv[R];
@@ -1184,7 +1185,7 @@ __device__ __forceinline__ void mg_down_fine(const Inst &I, int level, int ti, i
 //         buffers of the pair, ||r'||^2 partials (pt), which k_coarse adds for
 //         the inner stop test.  par: buffer of the pair holding r and s.
 template <int NU, int MODE>
-__global__ __launch_bounds__(kMgThreads, 8) void k_mg_down(const Inst *insts, Tab t, int par, Part pt, Part pq)
+__global__ __launch_bounds__(kMgThreads, 8) void k_mg_down(const Inst *insts, Tab t, int many, int par, Part pt, Part pq)
 {
     constexpr int HD = 2 * NU + 1, W = kMgTile + 2 * HD - 1;
     const int ku = unit_of(t, (int)blockIdx.x);
@@ -1200,7 +1201,7 @@ __global__ __launch_bounds__(kMgThreads, 8) void k_mg_down(const Inst *insts, Ta
     double rr = 0.0;
     Window0<W> win0;
     const float *r = par ? I.cg_r1 : F0.g;
-    if (MODE == 2 && t.n > 1 && F[F_DONE]) return;
+    if (MODE == 2 && many && F[F_DONE]) return;
     const int stop = vload(F, MODE == 1 ? F_CONV : F_DONE);
     PartialSums<3> ps;
     if (MODE == 2) ps.load(pq, t.boff[ku], t.boff[ku + 1], 2, (int)threadIdx.x);
@@ -1343,12 +1344,12 @@ __device__ __forceinline__ void mg_up_fine(const Inst &I, int level, int ti, int
 // around it, z to u (the CG's z), w = A z to cg_w, r.z and w.z partials.  par:
 // buffer of the pair holding the current residual.
 template <int NU>
-__global__ __launch_bounds__(kMgThreads) void k_mg_up(const Inst *insts, Tab t, int par, Part pt)
+__global__ __launch_bounds__(kMgThreads) void k_mg_up(const Inst *insts, Tab t, int many, int par, Part pt)
 {
     constexpr int HU = 2 * NU + 1, W = kMgTile + 2 * HU;
     const int ku = unit_of(t, (int)blockIdx.x);
     const Inst &I = insts[t.id[ku]];
-    if (t.n > 1) end_if(I.F[F_DONE]);
+    if (many) end_if(I.F[F_DONE]);
     const int done = vload((const int *)I.F, F_DONE);
     const int lb = (int)blockIdx.x - t.boff[ku];
     const int ti = lb / t.bx[ku], tj = lb - ti * t.bx[ku];
@@ -1403,24 +1404,25 @@ __global__ __launch_bounds__(kMgThreads) void k_mg_up(const Inst *insts, Tab t, 
 // in between).
 static Part cg_dot_part(Part pt) { return Part{pt.p + 2 * (size_t)pt.stride, pt.stride}; }
 
-void launch_mg_down(const Inst *I, const Tab &t, bool step, int par, Part pt, hipStream_t s)
+void launch_mg_down(const Inst *I, const Tab &t, bool many, bool step, int par, Part pt, hipStream_t s)
 {
     if (!t.n) return;
     const dim3 g(tab_blocks(t)), b(kMgThreads);
     const Part pq = cg_dot_part(pt);
     if (step) {
-        hipLaunchKernelGGL((k_mg_down<kMgSmooth, 2>), g, b, 0, s, I, t, par, pt, pq);
+        hipLaunchKernelGGL((k_mg_down<kMgSmooth, 2>), g, b, 0, s, I, t, many, par, pt, pq);
     } else {
-        hipLaunchKernelGGL((k_mg_down<kMgSmooth, 1>), g, b, 0, s, I, t, par, pt, pq);
+        hipLaunchKernelGGL((k_mg_down<kMgSmooth, 1>), g, b, 0, s, I, t, many, par, pt, pq);
         finalize(I, t, pt, OP_INIT, s);
     }
 }
 
-void launch_mg_up(const Inst *I, const Tab &t, int par, Part pt, hipStream_t s)
+void launch_mg_up(const Inst *I, const Tab &t, bool many, int par, Part pt, hipStream_t s)
 {
     if (!t.n) return;
     // the next level-0 down kernel turns the partials into alpha and beta
-    hipLaunchKernelGGL((k_mg_up<kMgSmooth>), dim3(tab_blocks(t)), dim3(kMgThreads), 0, s, I, t, par, cg_dot_part(pt));
+    hipLaunchKernelGGL((k_mg_up<kMgSmooth>), dim3(tab_blocks(t)), dim3(kMgThreads), 0, s, I, t, many, par,
+                       cg_dot_part(pt));
 }
 
 // ---------------------------------------------------------------------------
@@ -1640,14 +1642,14 @@ __device__ __forceinline__ void mg_up_pair(const Inst &I, int level, int ti, int
 // (a 32 x 32 tile is two nodes a thread, and the halo of a level's window then
 // takes three rounds of loads instead of two: 4.6 us up at 129 x 129 nodes).
 template <bool PAIRS, bool DOWN>
-__global__ __launch_bounds__(PAIRS ? kPairThreads : kMgThreads) void k_mg_mid(const Inst *insts, Tab t, int npair,
-                                                                             int level)
+__global__ __launch_bounds__(PAIRS ? kPairThreads : kMgThreads) void k_mg_mid(const Inst *insts, Tab t, int many,
+                                                                             int npair, int level)
 {
     extern __shared__ __align__(16) unsigned char lds[];
     const int ku = unit_of(t, (int)blockIdx.x);
     const bool pair = PAIRS && ku < npair;
     const Inst &I = insts[t.id[ku]];
-    if (t.n > 1) end_if(I.F[F_DONE]);
+    if (many) end_if(I.F[F_DONE]);
     const int done = vload((const int *)I.F, F_DONE);
     const int lb = (int)blockIdx.x - t.boff[ku];
     const int ti = lb / t.bx[ku], tj = lb - ti * t.bx[ku];
@@ -1660,7 +1662,7 @@ __global__ __launch_bounds__(PAIRS ? kPairThreads : kMgThreads) void k_mg_mid(co
     }
 }
 
-void launch_mg_mid(const Inst *I, const Tab &tp, const Tab &tf, int level, bool down, hipStream_t s)
+void launch_mg_mid(const Inst *I, const Tab &tp, const Tab &tf, bool many, int level, bool down, hipStream_t s)
 {
     Tab t = tp;
     for (int k = 0; k < tf.n; k++) {
@@ -1680,10 +1682,10 @@ void launch_mg_mid(const Inst *I, const Tab &tp, const Tab &tf, int level, bool 
     }
     const dim3 g(tab_blocks(t)), bp(kPairThreads), bf(kMgThreads);
     constexpr int fine = win_lds(kMgTile + 2 * (2 * kMgSmooth + 1) - 1);   // the down window, the larger one
-    if (tp.n && down) hipLaunchKernelGGL((k_mg_mid<true, true>), g, bp, kPairDnLds, s, I, t, tp.n, level);
-    else if (tp.n) hipLaunchKernelGGL((k_mg_mid<true, false>), g, bp, kPairUpLds, s, I, t, tp.n, level);
-    else if (down) hipLaunchKernelGGL((k_mg_mid<false, true>), g, bf, fine, s, I, t, tp.n, level);
-    else hipLaunchKernelGGL((k_mg_mid<false, false>), g, bf, fine, s, I, t, tp.n, level);
+    if (tp.n && down) hipLaunchKernelGGL((k_mg_mid<true, true>), g, bp, kPairDnLds, s, I, t, many, tp.n, level);
+    else if (tp.n) hipLaunchKernelGGL((k_mg_mid<true, false>), g, bp, kPairUpLds, s, I, t, many, tp.n, level);
+    else if (down) hipLaunchKernelGGL((k_mg_mid<false, true>), g, bf, fine, s, I, t, many, tp.n, level);
+    else hipLaunchKernelGGL((k_mg_mid<false, false>), g, bf, fine, s, I, t, many, tp.n, level);
 }
 
 // ---------------------------------------------------------------------------
@@ -2304,11 +2306,11 @@ template <int NC> struct Restrict {
 // one pass through it.  257 x 257 nodes (first level 65 x 65): 17.7 -> 15.8 us,
 // 1024 x 513 (128 x 65): 26.2 -> 24.0 us.
 template <int NP, bool ODD>
-__global__ __launch_bounds__(1024) void k_coarse(const Inst *insts, Tab t, Tab t0, Part pt, int fuse)
+__global__ __launch_bounds__(1024) void k_coarse(const Inst *insts, Tab t, Tab t0, Part pt, int many, int fuse)
 {
     const Inst &I = insts[t.id[blockIdx.x]];
     const int tid = threadIdx.x, nt = blockDim.x;
-    if (!fuse || t.n > 1) end_if(I.F[F_DONE]);
+    if (!fuse || many) end_if(I.F[F_DONE]);
     const CoarseArgs &a = I.coarse;
     extern __shared__ __align__(16) unsigned char lds[];
     __shared__ int tab[3][kMaxLev];
@@ -2519,12 +2521,12 @@ int coarse_form(int a, int b)
     return a && b ? std::max(a, b) : 0;
 }
 
-void launch_coarse(const Inst *I, const Tab &t, int form, int lds_bytes, const Tab &t0, Part pt, bool fuse,
-                   hipStream_t s)
+void launch_coarse(const Inst *I, const Tab &t, bool many, int form, int lds_bytes, const Tab &t0, Part pt,
+                   bool fuse, hipStream_t s)
 {
     if (!t.n) return;
     const int f = form == 3 ? 1 : form == 5 ? 2 : form == 1 ? 3 : 0;
-    static void (*const kernel[4])(const Inst *, Tab, Tab, Part, int) = {k_coarse<0, false>, k_coarse<3, false>,
+    static void (*const kernel[4])(const Inst *, Tab, Tab, Part, int, int) = {k_coarse<0, false>, k_coarse<3, false>,
                                                                          k_coarse<5, false>, k_coarse<0, true>};
     // a kernel's limit is the process's: always the largest that any context asks for
     static std::atomic<bool> allowed[4];
@@ -2532,7 +2534,7 @@ void launch_coarse(const Inst *I, const Tab &t, int form, int lds_bytes, const T
         (void)hipFuncSetAttribute((const void *)kernel[f], hipFuncAttributeMaxDynamicSharedMemorySize, kCoarseMaxLds);
         allowed[f] = true;
     }
-    hipLaunchKernelGGL(kernel[f], dim3(t.n), dim3(1024), lds_bytes, s, I, t, t0, pt, fuse ? 1 : 0);
+    hipLaunchKernelGGL(kernel[f], dim3(t.n), dim3(1024), lds_bytes, s, I, t, t0, pt, many, fuse);
 }
 
 // ---------------------------------------------------------------------------

@@ -696,9 +696,9 @@ void enqueue_deposit(pic_ctx *c, hipStream_t s)
 void enqueue_vcycle_mid(pic_ctx *c, bool fuse_update, hipStream_t s)
 {
     Part pt = part_of(c);
-    for (int l = 1; l < c->maxlg; l++) launch_mg_mid(c->d_inst, c->t_pair[l], c->t_fine[l], l, true, s);
-    launch_coarse(c->d_inst, c->t_coarse, c->coarse_frm, c->coarse_lds, c->t_fine[0], pt, fuse_update, s);
-    for (int l = c->maxlg - 1; l >= 1; l--) launch_mg_mid(c->d_inst, c->t_pair[l], c->t_fine[l], l, false, s);
+    for (int l = 1; l < c->maxlg; l++) launch_mg_mid(c->d_inst, c->t_pair[l], c->t_fine[l], c->n > 1, l, true, s);
+    launch_coarse(c->d_inst, c->t_coarse, c->n > 1, c->coarse_frm, c->coarse_lds, c->t_fine[0], pt, fuse_update, s);
+    for (int l = c->maxlg - 1; l >= 1; l--) launch_mg_mid(c->d_inst, c->t_pair[l], c->t_fine[l], c->n > 1, l, false, s);
 }
 
 // Start of a refinement pass: inner CG from e = 0.  Plain CG: first
@@ -709,9 +709,9 @@ void enqueue_pass_begin(pic_ctx *c, hipStream_t s)
     Part pt = part_of(c);
     launch_init_red0(c->d_inst, c->t_plain, pt, s);
     if (!c->any_mg) return;
-    launch_mg_down(c->d_inst, c->t_fine[0], false, 0, pt, s);
+    launch_mg_down(c->d_inst, c->t_fine[0], c->n > 1, false, 0, pt, s);
     enqueue_vcycle_mid(c, false, s);
-    launch_mg_up(c->d_inst, c->t_fine[0], 0, pt, s);
+    launch_mg_up(c->d_inst, c->t_fine[0], c->n > 1, 0, pt, s);
 }
 
 // K inner iterations; `first` when they open the pass.  Continuation chunks
@@ -726,9 +726,9 @@ void enqueue_iters(pic_ctx *c, int K, bool first, hipStream_t s)
         launch_update_red0(c->d_inst, c->t_plain, (k + 1) & 1, pt, s);
         if (!c->any_mg) continue;
         // the CG step; its reduction and stop test run in the coarse kernel
-        launch_mg_down(c->d_inst, c->t_fine[0], true, k & 1, pt, s);
+        launch_mg_down(c->d_inst, c->t_fine[0], c->n > 1, true, k & 1, pt, s);
         enqueue_vcycle_mid(c, true, s);
-        launch_mg_up(c->d_inst, c->t_fine[0], (k + 1) & 1, pt, s);
+        launch_mg_up(c->d_inst, c->t_fine[0], c->n > 1, (k + 1) & 1, pt, s);
     }
 }
 

@@ -890,6 +890,8 @@ __device__ __forceinline__ long long win_node(int NX, int NY, int px, int py, in
 // finished, the flag comes first: loading for nothing cost a batch of six more
 // (8.5 -> 13.1 us for the level-0 down kernel) than the trip it saves, and a
 // batch of one multigrid instance beside plain-CG ones 10 % of its solve.
+// (many comes before the tables in a launch's arguments: behind them it is a
+// trip for another line, 1 % of a step at 257 x 257 nodes.)
 template <int W, int NT = kMgThreads> struct Window {
     static constexpr int R = (W * W + NT - 1) / NT;
     float uv[R], gv[R];
@@ -1185,7 +1187,7 @@ __device__ __forceinline__ void mg_down_fine(const Inst &I, int level, int ti, i
 //         buffers of the pair, ||r'||^2 partials (pt), which k_coarse adds for
 //         the inner stop test.  par: buffer of the pair holding r and s.
 template <int NU, int MODE>
-__global__ __launch_bounds__(kMgThreads, 8) void k_mg_down(const Inst *insts, Tab t, int many, int par, Part pt, Part pq)
+__global__ __launch_bounds__(kMgThreads, 8) void k_mg_down(const Inst *insts, int many, Tab t, int par, Part pt, Part pq)
 {
     constexpr int HD = 2 * NU + 1, W = kMgTile + 2 * HD - 1;
     const int ku = unit_of(t, (int)blockIdx.x);
@@ -1344,7 +1346,7 @@ __device__ __forceinline__ void mg_up_fine(const Inst &I, int level, int ti, int
 // around it, z to u (the CG's z), w = A z to cg_w, r.z and w.z partials.  par:
 // buffer of the pair holding the current residual.
 template <int NU>
-__global__ __launch_bounds__(kMgThreads) void k_mg_up(const Inst *insts, Tab t, int many, int par, Part pt)
+__global__ __launch_bounds__(kMgThreads) void k_mg_up(const Inst *insts, int many, Tab t, int par, Part pt)
 {
     constexpr int HU = 2 * NU + 1, W = kMgTile + 2 * HU;
     const int ku = unit_of(t, (int)blockIdx.x);
@@ -1410,9 +1412,9 @@ void launch_mg_down(const Inst *I, const Tab &t, bool many, bool step, int par, 
     const dim3 g(tab_blocks(t)), b(kMgThreads);
     const Part pq = cg_dot_part(pt);
     if (step) {
-        hipLaunchKernelGGL((k_mg_down<kMgSmooth, 2>), g, b, 0, s, I, t, many, par, pt, pq);
+        hipLaunchKernelGGL((k_mg_down<kMgSmooth, 2>), g, b, 0, s, I, many, t, par, pt, pq);
     } else {
-        hipLaunchKernelGGL((k_mg_down<kMgSmooth, 1>), g, b, 0, s, I, t, many, par, pt, pq);
+        hipLaunchKernelGGL((k_mg_down<kMgSmooth, 1>), g, b, 0, s, I, many, t, par, pt, pq);
         finalize(I, t, pt, OP_INIT, s);
     }
 }
@@ -1421,7 +1423,7 @@ void launch_mg_up(const Inst *I, const Tab &t, bool many, int par, Part pt, hipS
 {
     if (!t.n) return;
     // the next level-0 down kernel turns the partials into alpha and beta
-    hipLaunchKernelGGL((k_mg_up<kMgSmooth>), dim3(tab_blocks(t)), dim3(kMgThreads), 0, s, I, t, many, par,
+    hipLaunchKernelGGL((k_mg_up<kMgSmooth>), dim3(tab_blocks(t)), dim3(kMgThreads), 0, s, I, many, t, par,
                        cg_dot_part(pt));
 }
 
@@ -1642,7 +1644,7 @@ __device__ __forceinline__ void mg_up_pair(const Inst &I, int level, int ti, int
 // (a 32 x 32 tile is two nodes a thread, and the halo of a level's window then
 // takes three rounds of loads instead of two: 4.6 us up at 129 x 129 nodes).
 template <bool PAIRS, bool DOWN>
-__global__ __launch_bounds__(PAIRS ? kPairThreads : kMgThreads) void k_mg_mid(const Inst *insts, Tab t, int many,
+__global__ __launch_bounds__(PAIRS ? kPairThreads : kMgThreads) void k_mg_mid(const Inst *insts, int many, Tab t,
                                                                              int npair, int level)
 {
     extern __shared__ __align__(16) unsigned char lds[];
@@ -1682,10 +1684,10 @@ void launch_mg_mid(const Inst *I, const Tab &tp, const Tab &tf, bool many, int l
     }
     const dim3 g(tab_blocks(t)), bp(kPairThreads), bf(kMgThreads);
     constexpr int fine = win_lds(kMgTile + 2 * (2 * kMgSmooth + 1) - 1);   // the down window, the larger one
-    if (tp.n && down) hipLaunchKernelGGL((k_mg_mid<true, true>), g, bp, kPairDnLds, s, I, t, many, tp.n, level);
-    else if (tp.n) hipLaunchKernelGGL((k_mg_mid<true, false>), g, bp, kPairUpLds, s, I, t, many, tp.n, level);
-    else if (down) hipLaunchKernelGGL((k_mg_mid<false, true>), g, bf, fine, s, I, t, many, tp.n, level);
-    else hipLaunchKernelGGL((k_mg_mid<false, false>), g, bf, fine, s, I, t, many, tp.n, level);
+    if (tp.n && down) hipLaunchKernelGGL((k_mg_mid<true, true>), g, bp, kPairDnLds, s, I, many, t, tp.n, level);
+    else if (tp.n) hipLaunchKernelGGL((k_mg_mid<true, false>), g, bp, kPairUpLds, s, I, many, t, tp.n, level);
+    else if (down) hipLaunchKernelGGL((k_mg_mid<false, true>), g, bf, fine, s, I, many, t, tp.n, level);
+    else hipLaunchKernelGGL((k_mg_mid<false, false>), g, bf, fine, s, I, many, t, tp.n, level);
 }
 
 // ---------------------------------------------------------------------------
@@ -2306,7 +2308,7 @@ template <int NC> struct Restrict {
 // one pass through it.  257 x 257 nodes (first level 65 x 65): 17.7 -> 15.8 us,
 // 1024 x 513 (128 x 65): 26.2 -> 24.0 us.
 template <int NP, bool ODD>
-__global__ __launch_bounds__(1024) void k_coarse(const Inst *insts, Tab t, Tab t0, Part pt, int many, int fuse)
+__global__ __launch_bounds__(1024) void k_coarse(const Inst *insts, int many, int fuse, Tab t, Tab t0, Part pt)
 {
     const Inst &I = insts[t.id[blockIdx.x]];
     const int tid = threadIdx.x, nt = blockDim.x;
@@ -2526,7 +2528,7 @@ void launch_coarse(const Inst *I, const Tab &t, bool many, int form, int lds_byt
 {
     if (!t.n) return;
     const int f = form == 3 ? 1 : form == 5 ? 2 : form == 1 ? 3 : 0;
-    static void (*const kernel[4])(const Inst *, Tab, Tab, Part, int, int) = {k_coarse<0, false>, k_coarse<3, false>,
+    static void (*const kernel[4])(const Inst *, int, int, Tab, Tab, Part) = {k_coarse<0, false>, k_coarse<3, false>,
                                                                          k_coarse<5, false>, k_coarse<0, true>};
     // a kernel's limit is the process's: always the largest that any context asks for
     static std::atomic<bool> allowed[4];
@@ -2534,7 +2536,7 @@ void launch_coarse(const Inst *I, const Tab &t, bool many, int form, int lds_byt
         (void)hipFuncSetAttribute((const void *)kernel[f], hipFuncAttributeMaxDynamicSharedMemorySize, kCoarseMaxLds);
         allowed[f] = true;
     }
-    hipLaunchKernelGGL(kernel[f], dim3(t.n), dim3(1024), lds_bytes, s, I, t, t0, pt, many, fuse);
+    hipLaunchKernelGGL(kernel[f], dim3(t.n), dim3(1024), lds_bytes, s, I, many, fuse, t, t0, pt);
 }
 
 // ---------------------------------------------------------------------------
